@@ -47,7 +47,7 @@ ChunkSizes per_sample(const nqs_ctx* c) {
   z.L = (size_t)c->K * c->G * 16;
   z.w = (size_t)c->K * c->G * 2 * real_size(c);
   z.t = (size_t)c->G * c->KM * 2 * real_size(c);
-  z.partial = (size_t)(c->G / 32) * 16;
+  z.partial = (size_t)(c->G / 16) * 16;
   z.partial2 = (size_t)c->NB * (c->G / 32) * 16;
   return z;
 }
@@ -845,6 +845,22 @@ nqs_status nqs_eloc_grad(nqs_ctx* c, const int8_t* spins, int64_t S, double* log
   nqs_status s = check_common(c, spins, S, ws, ws_bytes, NQS_OP_ELOC_GRAD);
   if (s != NQS_OK) return s;
   if (S > 0 && (!eloc_out || !O_out)) return fail(c, NQS_ERR_ARG, "eloc_out or O_out is NULL");
+  if (!fused_eloc(c, NQS_OP_ELOC) && !fused_grad(c, NQS_OP_GRAD) && !grad_wide_supported(c)) {
+    // both calls would run the same theta and log-sum-exp passes: run them once
+    const Work wk = plan(c, NQS_OP_ELOC, S, ws);
+    const size_t osz = (size_t)c->P * 2 * real_size(c);
+    for (int64_t s0 = 0; s0 < S; s0 += wk.chunk) {
+      const int64_t n = std::min(wk.chunk, S - s0);
+      const int8_t* sp = spins + s0 * c->N;
+      double* lp = logpsi_out ? logpsi_out + 2 * s0 : wk.lp;
+      hipError_t e = eloc_chunk(c, wk, sp, n, lp, eloc_out + 2 * s0, 2, st);
+      if (e == hipSuccess)
+        e = NQS_RUN(c, K_GRAD, st,
+                    launch_grad(c, sp, n, wk.t, wk.w, (char*)O_out + (size_t)s0 * osz, st));
+      if (e != hipSuccess) return hip_fail(c, e, "eloc_grad launch");
+    }
+    return NQS_OK;
+  }
   if (!shared_eloc_grad(c)) {
     s = nqs_eloc(c, spins, S, logpsi_out, eloc_out, ws, ws_bytes, st);
     return s == NQS_OK ? nqs_grad(c, spins, S, O_out, nullptr, ws, ws_bytes, st) : s;

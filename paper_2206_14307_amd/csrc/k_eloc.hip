@@ -448,14 +448,15 @@ hipError_t launch_eloc_bonds(const nqs_ctx* c, const int8_t* spins, int64_t S, c
   const hipError_t e = launch_eloc_bonds_reg(c, spins, S, t, w, partial, st);
   if (e != hipErrorNotSupported) return e;
   return c->prec == NQS_FP64 ? eloc_typed<double>(c, spins, S, t, w, partial, st)
-                             : eloc_typed<float>(c, spins, S, t, w, partial, st);
+                             : launch_eloc_rows(c, spins, S, t, w, partial, st);
 }
 
 hipError_t launch_eloc_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                               const double* partial, double* eloc_out, int eloc_stride,
                               hipStream_t st) {
   if (S <= 0) return hipSuccess;
-  eloc_finish_kernel<<<(unsigned)S, 64, 0, st>>>(spins, c->N, c->NB, c->G / 32, c->dev.bonds,
+  const int tile = c->prec != NQS_FP64 && !eloc_reg_supported(c) ? 16 : 32;
+  eloc_finish_kernel<<<(unsigned)S, 64, 0, st>>>(spins, c->N, c->NB, c->G / tile, c->dev.bonds,
                                                  c->dev.bond_J, partial, eloc_out, eloc_stride);
   return hipGetLastError();
 }

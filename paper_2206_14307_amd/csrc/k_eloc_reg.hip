@@ -476,6 +476,12 @@ hipError_t run_twohop(const nqs_ctx* c, const int8_t* spins, int64_t S, const vo
 
 }  // namespace
 
+bool eloc_reg_supported(const nqs_ctx* c) {
+  const int N = c->N, K = c->K, M = c->M;
+  return (N == 16 && ((K == 1 && M == 16) || (c->prec == NQS_FP64 && K == 2 && M == 8))) ||
+         (c->prec != NQS_FP64 && N == 36 && ((K == 1 && M == 72) || (K == 2 && M == 16)));
+}
+
 // Returns hipErrorNotSupported when no register-resident variant covers the model.
 hipError_t launch_eloc_bonds_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                                  const void* w, double* partial, hipStream_t st) {

@@ -151,6 +151,11 @@ hipError_t launch_lse(const nqs_ctx* c, const double* L, int64_t S, double* logp
 // Bond-exchange sums: partial[s][tile] = sum_{b anti} (J_b/2) sum_{g in tile, k} w R.
 hipError_t launch_eloc_bonds(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                              const void* w, double* partial, hipStream_t st);
+// Models with a register-resident bond kernel write one partial per 32 images;
+// the FP32 kernel of the others (launch_eloc_rows) one per 16.
+bool eloc_reg_supported(const nqs_ctx* c);
+hipError_t launch_eloc_rows(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
+                            const void* w, double* partial, hipStream_t st);
 hipError_t launch_eloc_bonds_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                                  const void* w, double* partial, hipStream_t st);
 // Fused theta + epilogue + bond exchanges (K*M <= 128 register-resident
