@@ -210,11 +210,7 @@ hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t, 
 // lane's units lies in 2^[-120, 120] (binary exponents summed exactly) on all
 // lanes of the wave; otherwise t is reloaded and the direct form runs.
 __device__ __forceinline__ int ilogb_bits(float v) { return ((__float_as_int(v) >> 23) & 0xff) - 127; }
-__device__ __forceinline__ int ilogb_bits(double v) {
-  return (int)((__double_as_longlong(v) >> 52) & 0x7ff) - 1023;
-}
 __device__ __forceinline__ float rcp_fast(float v) { return __builtin_amdgcn_rcpf(v); }
-__device__ __forceinline__ double rcp_fast(double v) { return 1.0 / v; }
 
 // (x of lanes 0..31) * (x of lanes 32..63), in every lane
 template <typename R>
@@ -499,19 +495,16 @@ hipError_t launch_eloc_bonds_reg(const nqs_ctx* c, const int8_t* spins, int64_t 
 
 bool twohop_reg_supported(const nqs_ctx* c) {
   if (c->K != 1) return false;
-  if (c->prec == NQS_FP64) return c->N == 16 && c->M == 16;
+  if (c->prec == NQS_FP64) return twohop16_supported(c);
   return (c->N == 16 && c->M == 16) || (c->N == 36 && c->M == 72);
 }
 
 hipError_t launch_twohop_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                              const void* w, double* partial2, hipStream_t st) {
   if (!twohop_reg_supported(c)) return hipErrorNotSupported;
-  if (c->prec == NQS_FP64) {
-    if (c->N == 16 && c->M == 16) return run_twohop<double, 16, 16>(c, spins, S, t, w, partial2, st);
-  } else {
-    if (c->N == 16 && c->M == 16) return run_twohop<float, 16, 16>(c, spins, S, t, w, partial2, st);
-    if (c->N == 36 && c->M == 72) return run_twohop<float, 36, 72>(c, spins, S, t, w, partial2, st);
-  }
+  if (twohop16_supported(c)) return launch_twohop16(c, spins, S, t, w, partial2, st);
+  if (c->N == 16 && c->M == 16) return run_twohop<float, 16, 16>(c, spins, S, t, w, partial2, st);
+  if (c->N == 36 && c->M == 72) return run_twohop<float, 36, 72>(c, spins, S, t, w, partial2, st);
   return hipErrorNotSupported;
 }
 
