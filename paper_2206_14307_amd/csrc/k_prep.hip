@@ -185,6 +185,45 @@ __global__ void prep_T_kernel(const double2* p, int Prbm, int M, int N, int KM, 
   row[2 * KM + 2 * h + 1] = (R)(-t.y);
 }
 
+// prod_h cosh(W_hp - W_hq) over RBM k's units, in every lane of a wavefront: the
+// lanes take the units in turn, then join their products.  (One thread walking
+// all M units made the tables' preparation a chain of M dependent products:
+// 60 us at M = 72, 310 us at M = 400.)
+__device__ inline double2 prod_cosh(const double2* p, int Prbm, int M, int N, int k, int sp, int sq,
+                                    int lane) {
+  double cr = 1.0, ci = 0.0;
+  for (int hh = lane; hh < M; hh += 64) {
+    const double2 wp = Wval(p, Prbm, M, N, k * M + hh, sp);
+    const double2 wq = Wval(p, Prbm, M, N, k * M + hh, sq);
+    const double2 c = ccosh64(wp.x - wq.x, wp.y - wq.y);
+    const double nr = cr * c.x - ci * c.y;
+    ci = cr * c.y + ci * c.x;
+    cr = nr;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const double br = __shfl_xor(cr, o, 64), bi = __shfl_xor(ci, o, 64);
+    const double nr = cr * br - ci * bi;
+    ci = cr * bi + ci * br;
+    cr = nr;
+  }
+  return make_double2(cr, ci);
+}
+
+// scale exp(s (a_p - a_q)) c
+__device__ inline double2 bond_F(const double2* p, int Prbm, int M, int N, int k, int sp, int sq,
+                                 int use_bias, double scale, double s, double2 c) {
+  double ar = 0.0, ai = 0.0;
+  if (use_bias) {
+    const double2 ap = p[(size_t)k * Prbm + (size_t)M * N + sp];
+    const double2 aq = p[(size_t)k * Prbm + (size_t)M * N + sq];
+    ar = ap.x - aq.x;
+    ai = ap.y - aq.y;
+  }
+  const double2 e = cexp64(s * ar, s * ai);
+  return make_double2(scale * (e.x * c.x - e.y * c.y), scale * (e.x * c.y + e.y * c.x));
+}
+
 // Bond rows of the fused E_loc kernel.  The hidden units of RBM k are split
 // into eight lane streams h = kM + 8j + r (r = 2q + u, j < M/8); the fused
 // kernel multiplies one stream per (lane, bond) and joins the eight streams
@@ -200,18 +239,22 @@ __global__ void prep_T_kernel(const double2* p, int Prbm, int M, int N, int KM, 
 // factors) x (suffix product of T), so that form is used only if every suffix
 // product |prod_{i >= j} T_i| lies in [2^lg_lo, 2^lg_hi]; flag[1] is set
 // otherwise.
+// One wavefront per (bond, RBM): its lanes take the units of prod cosh D in turn
+// and join their products, lanes 0..7 then walk the eight streams.
 template <typename R>
-__global__ void prep_fused_rows_kernel(const double2* p, int Prbm, int K, int M, int N, int NB,
-                                       int use_bias, const int32_t* bonds, const double* bond_J,
-                                       double lg_lo, double lg_hi, R* Tdir, R* Urec,
-                                       double* flag) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= NB * K * 8) return;
-  const int beta = idx / (K * 8), k = (idx / 8) % K, r = idx % 8;
+__global__ __launch_bounds__(256) void prep_fused_rows_kernel(
+    const double2* p, int Prbm, int K, int M, int N, int NB, int use_bias, const int32_t* bonds,
+    const double* bond_J, double lg_lo, double lg_hi, R* Tdir, R* Urec, double* flag) {
+  const int idx = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (idx >= NB * K) return;
+  const int beta = idx / K, k = idx % K;
   const int KM = K * M, TPR = M / 8, ROW = 2 * KM + 18 * K;
   const int bp = bonds[2 * beta], bq = bonds[2 * beta + 1];
   R* dir = Tdir + (size_t)beta * ROW;
   R* rec = Urec + (size_t)beta * ROW;
+  const double2 hc = prod_cosh(p, Prbm, M, N, k, bp, bq, lane);
+  if (lane >= 8) return;
+  const int r = lane;
   double cr = 1.0, ci = 0.0, lg = 0.0;
   bool ok = true;
   for (int j = TPR - 1; j >= 0; --j) {
@@ -231,133 +274,86 @@ __global__ void prep_fused_rows_kernel(const double2* p, int Prbm, int K, int M,
     rec[2 * h + 1] = a2 > 0.0 ? (R)(-t.y / a2) : (R)0;
   }
   if (!ok) flag[1] = 1.0;
-  double fr[2] = {1.0, 1.0}, fi[2] = {0.0, 0.0};
-  if (r == 0) {
-    double hr = 1.0, hi = 0.0;
-    for (int hh = 0; hh < M; ++hh) {
-      const double2 wp = Wval(p, Prbm, M, N, k * M + hh, bp);
-      const double2 wq = Wval(p, Prbm, M, N, k * M + hh, bq);
-      const double2 c = ccosh64(wp.x - wq.x, wp.y - wq.y);
-      const double nr = hr * c.x - hi * c.y;
-      hi = hr * c.y + hi * c.x;
-      hr = nr;
-    }
-    double ar = 0.0, ai = 0.0;
-    if (use_bias) {
-      const double2 ap = p[(size_t)k * Prbm + (size_t)M * N + bp];
-      const double2 aq = p[(size_t)k * Prbm + (size_t)M * N + bq];
-      ar = ap.x - aq.x;
-      ai = ap.y - aq.y;
-    }
-    const double hJ = 0.5 * bond_J[beta];
-    for (int s = 0; s < 2; ++s) {
-      const double sg = s == 0 ? 1.0 : -1.0;
-      const double2 e = cexp64(sg * ar, sg * ai);
-      fr[s] = hJ * (e.x * hr - e.y * hi);
-      fi[s] = hJ * (e.x * hi + e.y * hr);
-    }
-  }
+  double2 f[2] = {make_double2(1.0, 0.0), make_double2(1.0, 0.0)};
+  if (r == 0)
+    for (int s = 0; s < 2; ++s)
+      f[s] = bond_F(p, Prbm, M, N, k, bp, bq, use_bias, 0.5 * bond_J[beta], s == 0 ? 1.0 : -1.0, hc);
   const int st = 2 * KM + 16 * k + 2 * r;
-  dir[st] = (R)fr[0];
-  dir[st + 1] = (R)fi[0];
-  rec[st] = (R)(cr * fr[0] - ci * fi[0]);
-  rec[st + 1] = (R)(cr * fi[0] + ci * fr[0]);
+  dir[st] = (R)f[0].x;
+  dir[st + 1] = (R)f[0].y;
+  rec[st] = (R)(cr * f[0].x - ci * f[0].y);
+  rec[st + 1] = (R)(cr * f[0].y + ci * f[0].x);
   if (r == 0) {
     const int sn = 2 * KM + 16 * K + 2 * k;
-    dir[sn] = (R)fr[1];
-    dir[sn + 1] = (R)fi[1];
-    rec[sn] = (R)(cr * fr[1] - ci * fi[1]);
-    rec[sn + 1] = (R)(cr * fi[1] + ci * fr[1]);
+    dir[sn] = (R)f[1].x;
+    dir[sn + 1] = (R)f[1].y;
+    rec[sn] = (R)(cr * f[1].x - ci * f[1].y);
+    rec[sn + 1] = (R)(cr * f[1].y + ci * f[1].x);
   }
 }
 
 // F[k][beta][s] = (J_beta / 2) exp(s A_beta) prod_h cosh(D_h,beta), s = +1 (0), -1 (1).
 template <typename R>
-__global__ void prep_F_kernel(const double2* p, int Prbm, int K, int M, int N, int NB, int use_bias,
-                              const int32_t* bonds, const double* bond_J, R* F) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void prep_F_kernel(const double2* p, int Prbm, int K, int M,
+                                                     int N, int NB, int use_bias,
+                                                     const int32_t* bonds, const double* bond_J,
+                                                     R* F) {
+  const int idx = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (idx >= K * NB) return;
   const int k = idx / NB, beta = idx % NB;
   const int bp = bonds[2 * beta], bq = bonds[2 * beta + 1];
-  double cr = 1.0, ci = 0.0;
-  for (int hh = 0; hh < M; ++hh) {
-    const double2 wp = Wval(p, Prbm, M, N, k * M + hh, bp);
-    const double2 wq = Wval(p, Prbm, M, N, k * M + hh, bq);
-    const double2 c = ccosh64(wp.x - wq.x, wp.y - wq.y);
-    const double nr = cr * c.x - ci * c.y;
-    ci = cr * c.y + ci * c.x;
-    cr = nr;
-  }
-  double ar = 0.0, ai = 0.0;
-  if (use_bias) {
-    const double2 ap = p[(size_t)k * Prbm + (size_t)M * N + bp];
-    const double2 aq = p[(size_t)k * Prbm + (size_t)M * N + bq];
-    ar = ap.x - aq.x;
-    ai = ap.y - aq.y;
-  }
-  const double hJ = 0.5 * bond_J[beta];
-  for (int s = 0; s < 2; ++s) {
-    const double sg = s == 0 ? 1.0 : -1.0;
-    const double2 e = cexp64(sg * ar, sg * ai);
-    R* o = F + ((size_t)(k * NB + beta) * 2 + s) * 2;
-    o[0] = (R)(hJ * (e.x * cr - e.y * ci));
-    o[1] = (R)(hJ * (e.x * ci + e.y * cr));
+  const double2 c = prod_cosh(p, Prbm, M, N, k, bp, bq, lane);
+  if (lane < 2) {
+    const double2 f = bond_F(p, Prbm, M, N, k, bp, bq, use_bias, 0.5 * bond_J[beta],
+                             lane == 0 ? 1.0 : -1.0, c);
+    R* o = F + ((size_t)(k * NB + beta) * 2 + lane) * 2;
+    o[0] = (R)f.x;
+    o[1] = (R)f.y;
   }
 }
 
 // Site-pair tables of the sampler's exchange move (up site at image position
 // p, down site at q, so theta -> theta - (W_p - W_q)):
 // Tpair[p][q][h] = tanh(W_hp - W_hq), Fpair[k][p][q] = exp(-(a_p - a_q)) prod_h cosh(W_hp - W_hq).
+// (one wavefront per site pair p < q: both orders, tanh being odd)
 template <typename R>
-__global__ void prep_Tpair_kernel(const double2* p, int Prbm, int M, int N, int KM, R* Tpair) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)N * N * KM) return;
-  const int h = idx % KM;
-  const int pq = idx / KM;
-  const int sp = pq / N, sq = pq % N;
-  const double2 wp = Wval(p, Prbm, M, N, h, sp);
-  const double2 wq = Wval(p, Prbm, M, N, h, sq);
-  const double2 t = ctanh64(wp.x - wq.x, wp.y - wq.y);
-  Tpair[2 * idx] = (R)t.x;
-  Tpair[2 * idx + 1] = (R)t.y;
-}
-
-template <typename R>
-__global__ void prep_Fpair_kernel(const double2* p, int Prbm, int K, int M, int N, int use_bias,
-                                  R* Fpair) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= K * N * N) return;
-  const int k = idx / (N * N), sp = (idx / N) % N, sq = idx % N;
-  double cr = 1.0, ci = 0.0;
-  for (int hh = 0; hh < M; ++hh) {
-    const double2 wp = Wval(p, Prbm, M, N, k * M + hh, sp);
-    const double2 wq = Wval(p, Prbm, M, N, k * M + hh, sq);
-    const double2 c = ccosh64(wp.x - wq.x, wp.y - wq.y);
-    const double nr = cr * c.x - ci * c.y;
-    ci = cr * c.y + ci * c.x;
-    cr = nr;
+__global__ __launch_bounds__(256) void prep_pair_kernel(const double2* p, int Prbm, int K, int M,
+                                                        int N, int KM, int use_bias, R* Tpair,
+                                                        R* Fpair) {
+  const int idx = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (idx >= N * N) return;
+  const int sp = idx / N, sq = idx % N;
+  if (sp > sq) return;
+  R* t0 = Tpair + ((size_t)sp * N + sq) * KM * 2;
+  R* t1 = Tpair + ((size_t)sq * N + sp) * KM * 2;
+  for (int h = lane; h < KM; h += 64) {
+    const double2 wp = Wval(p, Prbm, M, N, h, sp);
+    const double2 wq = Wval(p, Prbm, M, N, h, sq);
+    const double2 t = ctanh64(wp.x - wq.x, wp.y - wq.y);
+    t0[2 * h] = (R)t.x;
+    t0[2 * h + 1] = (R)t.y;
+    if (sp != sq) {
+      t1[2 * h] = (R)(-t.x);
+      t1[2 * h + 1] = (R)(-t.y);
+    }
   }
-  double ar = 0.0, ai = 0.0;
-  if (use_bias) {
-    const double2 ap = p[(size_t)k * Prbm + (size_t)M * N + sp];
-    const double2 aq = p[(size_t)k * Prbm + (size_t)M * N + sq];
-    ar = ap.x - aq.x;
-    ai = ap.y - aq.y;
+  for (int k = 0; k < K; ++k) {
+    const double2 c = prod_cosh(p, Prbm, M, N, k, sp, sq, lane);
+    if (lane < 2) {
+      const int a = lane ? sq : sp, b = lane ? sp : sq;
+      const double2 f = bond_F(p, Prbm, M, N, k, a, b, use_bias, 1.0, -1.0, c);
+      R* o = Fpair + (((size_t)k * N + a) * N + b) * 2;
+      o[0] = (R)f.x;
+      o[1] = (R)f.y;
+    }
   }
-  const double2 e = cexp64(-ar, -ai);
-  Fpair[2 * idx] = (R)(e.x * cr - e.y * ci);
-  Fpair[2 * idx + 1] = (R)(e.x * ci + e.y * cr);
 }
 
 template <typename R>
 hipError_t prep_pairs_typed(const nqs_ctx* c, hipStream_t st) {
   const double2* p = reinterpret_cast<const double2*>(c->par.params);
-  const int64_t nT = (int64_t)c->N * c->N * c->KM;
-  prep_Tpair_kernel<R><<<(unsigned)((nT + 255) / 256), 256, 0, st>>>(p, c->P_rbm, c->M, c->N,
-                                                                       c->KM, (R*)c->par.Tpair);
-  const int nF = c->K * c->N * c->N;
-  prep_Fpair_kernel<R><<<(nF + 63) / 64, 64, 0, st>>>(p, c->P_rbm, c->K, c->M, c->N,
-                                                      c->d.use_bias, (R*)c->par.Fpair);
+  prep_pair_kernel<R><<<(unsigned)((c->N * c->N + 3) / 4), 256, 0, st>>>(
+      p, c->P_rbm, c->K, c->M, c->N, c->KM, c->d.use_bias, (R*)c->par.Tpair, (R*)c->par.Fpair);
   return hipGetLastError();
 }
 
@@ -396,15 +392,16 @@ hipError_t prep_typed(const nqs_ctx* c, hipStream_t st) {
   const int64_t nT = (int64_t)c->NB * c->KM;
   prep_T_kernel<R><<<(nT + 255) / 256, 256, 0, st>>>(p, c->P_rbm, c->M, c->N, c->KM, c->NB,
                                                       c->dev.bonds, (R*)c->par.Tpm);
-  prep_F_kernel<R><<<(c->K * c->NB + 63) / 64, 64, 0, st>>>(
+  prep_F_kernel<R><<<(c->K * c->NB + 3) / 4, 256, 0, st>>>(
       p, c->P_rbm, c->K, c->M, c->N, c->NB, c->d.use_bias, c->dev.bonds, c->dev.bond_J,
       (R*)c->par.F);
   // suffix-product range of the reciprocal form: FP32 keeps 2^+-96 clear of
   // overflow and of the denormal range; FP64 2^+-900
   const double lg = sizeof(R) == 4 ? 96.0 : 900.0;
-  prep_fused_rows_kernel<R><<<(c->NB * c->K * 8 + 63) / 64, 64, 0, st>>>(
-      p, c->P_rbm, c->K, c->M, c->N, c->NB, c->d.use_bias, c->dev.bonds, c->dev.bond_J, -lg, lg,
-      (R*)c->par.Tdir, (R*)c->par.Urec, c->par.flag);
+  if (eloc_fused_supported(c))                   // only the fused kernel reads these rows
+    prep_fused_rows_kernel<R><<<(c->NB * c->K + 3) / 4, 256, 0, st>>>(
+        p, c->P_rbm, c->K, c->M, c->N, c->NB, c->d.use_bias, c->dev.bonds, c->dev.bond_J, -lg, lg,
+        (R*)c->par.Tdir, (R*)c->par.Urec, c->par.flag);
   return hipGetLastError();
 }
 
