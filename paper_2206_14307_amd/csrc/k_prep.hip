@@ -239,13 +239,15 @@ __device__ inline double2 bond_F(const double2* p, int Prbm, int M, int N, int k
 // factors) x (suffix product of T), so that form is used only if every suffix
 // product |prod_{i >= j} T_i| lies in [2^lg_lo, 2^lg_hi]; flag[1] is set
 // otherwise.
-// One wavefront per (bond, RBM): its lanes take the units of prod cosh D in turn
-// and join their products, lanes 0..7 then walk the eight streams.
+// One wavefront per (bond, RBM): its lanes take the units in turn (tanh, and
+// prod cosh D, joined), lanes 0..7 then multiply up the eight streams.
+constexpr int kFusedMaxM = 128;                 // the fused kernel serves K M <= 128
 template <typename R>
 __global__ __launch_bounds__(256) void prep_fused_rows_kernel(
     const double2* p, int Prbm, int K, int M, int N, int NB, int use_bias, const int32_t* bonds,
     const double* bond_J, double lg_lo, double lg_hi, R* Tdir, R* Urec, double* flag) {
   const int idx = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  __shared__ double3 tl[4][kFusedMaxM];
   if (idx >= NB * K) return;
   const int beta = idx / K, k = idx % K;
   const int KM = K * M, TPR = M / 8, ROW = 2 * KM + 18 * K;
@@ -253,25 +255,32 @@ __global__ __launch_bounds__(256) void prep_fused_rows_kernel(
   R* dir = Tdir + (size_t)beta * ROW;
   R* rec = Urec + (size_t)beta * ROW;
   const double2 hc = prod_cosh(p, Prbm, M, N, k, bp, bq, lane);
+  // tanh and log2 |tanh| of the units, one per lane in turn, through LDS
+  double3* tw = tl[threadIdx.x >> 6];
+  for (int hh = lane; hh < M; hh += 64) {
+    const int h = k * M + hh;
+    const double2 wp = Wval(p, Prbm, M, N, h, bp);
+    const double2 wq = Wval(p, Prbm, M, N, h, bq);
+    const double2 t = ctanh64(wp.x - wq.x, wp.y - wq.y);
+    const double a2 = t.x * t.x + t.y * t.y;
+    tw[hh] = make_double3(t.x, t.y, 0.5 * log2(a2));   // -inf for T = 0
+    dir[2 * h] = (R)t.x;
+    dir[2 * h + 1] = (R)t.y;
+    rec[2 * h] = a2 > 0.0 ? (R)(t.x / a2) : (R)0;
+    rec[2 * h + 1] = a2 > 0.0 ? (R)(-t.y / a2) : (R)0;
+  }
+  wave_sync_lds();
   if (lane >= 8) return;
   const int r = lane;
   double cr = 1.0, ci = 0.0, lg = 0.0;
   bool ok = true;
   for (int j = TPR - 1; j >= 0; --j) {
-    const int h = k * M + 8 * j + r;
-    const double2 wp = Wval(p, Prbm, M, N, h, bp);
-    const double2 wq = Wval(p, Prbm, M, N, h, bq);
-    const double2 t = ctanh64(wp.x - wq.x, wp.y - wq.y);
-    const double a2 = t.x * t.x + t.y * t.y;
+    const double3 t = tw[8 * j + r];
     const double nr = cr * t.x - ci * t.y;
     ci = cr * t.y + ci * t.x;
     cr = nr;
-    lg += 0.5 * log2(a2);                         // -inf for T = 0
+    lg += t.z;
     ok = ok && lg >= lg_lo && lg <= lg_hi;
-    dir[2 * h] = (R)t.x;
-    dir[2 * h + 1] = (R)t.y;
-    rec[2 * h] = a2 > 0.0 ? (R)(t.x / a2) : (R)0;
-    rec[2 * h + 1] = a2 > 0.0 ? (R)(-t.y / a2) : (R)0;
   }
   if (!ok) flag[1] = 1.0;
   double2 f[2] = {make_double2(1.0, 0.0), make_double2(1.0, 0.0)};
@@ -398,7 +407,7 @@ hipError_t prep_typed(const nqs_ctx* c, hipStream_t st) {
   // suffix-product range of the reciprocal form: FP32 keeps 2^+-96 clear of
   // overflow and of the denormal range; FP64 2^+-900
   const double lg = sizeof(R) == 4 ? 96.0 : 900.0;
-  if (eloc_fused_supported(c))                   // only the fused kernel reads these rows
+  if (eloc_fused_supported(c) && c->M <= kFusedMaxM)   // only the fused kernel reads these rows
     prep_fused_rows_kernel<R><<<(c->NB * c->K + 3) / 4, 256, 0, st>>>(
         p, c->P_rbm, c->K, c->M, c->N, c->NB, c->d.use_bias, c->dev.bonds, c->dev.bond_J, -lg, lg,
         (R*)c->par.Tdir, (R*)c->par.Urec, c->par.flag);
