@@ -29,6 +29,8 @@ namespace {
 
 constexpr int kCgRows = 16;      // rows per block of the row GEMV
 constexpr int kRowParts = 8;     // most column parts of the complex64 row GEMV
+constexpr int kRowsFew = 4;      // rows per block where kCgRows gives too few blocks
+constexpr int kRowBlocks = 1024;
 constexpr int kCgThreads = 256;
 constexpr int kVecThreads = 1024;
 constexpr int kCgBatch = 4;      // CG iterations queued per read of the residual
@@ -108,16 +110,35 @@ __global__ __launch_bounds__(kCgThreads) void rows_kernel(const RO* __restrict__
   }
 }
 
+// us_part[slab] = sum of u over the slab's rows, by one wavefront of the block
+// that takes the slab's first columns (all its lanes call)
+__device__ __forceinline__ void slab_usum(const double* __restrict__ u, int64_t sb, int64_t se,
+                                          double* __restrict__ us_part) {
+  double sr = 0.0, si = 0.0;
+  for (int64_t s = sb + (threadIdx.x & 63); s < se; s += 64) {
+    sr += u[2 * s];
+    si += u[2 * s + 1];
+  }
+  sr = wave_sum(sr);
+  si = wave_sum(si);
+  if ((threadIdx.x & 63) == 0) {
+    us_part[2 * blockIdx.y] = sr;
+    us_part[2 * blockIdx.y + 1] = si;
+  }
+}
+
 // part[slab][k] = sum_{s in slab} conj(O[s][k]) u[s]  (u = NULL: u = 1).
 template <typename RO>
 __global__ __launch_bounds__(kCgThreads) void cols_kernel(const RO* __restrict__ O, int64_t S,
                                                           int64_t P, int64_t slab,
                                                           const double* __restrict__ u,
                                                           double* __restrict__ part,
+                                                          double* __restrict__ us_part,
                                                           const double* __restrict__ stop) {
   if (stopped(stop)) return;
   const int64_t k = (int64_t)blockIdx.x * kCgThreads + threadIdx.x;
   const int64_t sb = (int64_t)blockIdx.y * slab, se = std::min<int64_t>(S, sb + slab);
+  if (u && blockIdx.x == 0 && threadIdx.x < 64) slab_usum(u, sb, se, us_part);
   if (k >= P) return;
   double qr = 0.0, qi = 0.0;
   for (int64_t s = sb; s < se; ++s) {
@@ -132,27 +153,34 @@ __global__ __launch_bounds__(kCgThreads) void cols_kernel(const RO* __restrict__
 
 // complex64 O: every P here is even (N even, M a multiple of 8), so a row's
 // column pairs are 16-byte aligned and one float4 load brings two columns.
-// Block (x, y) takes rows x kCgRows .. and column part y of gridDim.y (at
-// most kRowParts) and writes its raw partial sums upart[y][s]: many more
-// blocks than the device holds at once, so the last round of blocks is a
-// small part of the pass.
+// Block (x, y) takes rows x ROWS .. and column part y of gridDim.y (at most
+// kRowParts).  With several parts it writes its raw partial sums upart[y][s]
+// (many more blocks than the device holds at once, so the last round of blocks
+// is a small part of the pass); with one part it writes u itself.  Sixteen rows
+// a block reuse each v most; where that gives fewer than kRowBlocks blocks (the
+// training sizes: S = 4000, P = 2700 is 250) four rows keep more loads in flight
+// per CU: 45 -> 18 us a pass.
+template <int ROWS>
 __global__ __launch_bounds__(kCgThreads) void rows2_kernel(const float* __restrict__ O, int64_t S,
                                                            int64_t P, const double* __restrict__ v,
+                                                           const double* __restrict__ mv,
+                                                           double inv_sqrt_s,
                                                            double* __restrict__ upart,
+                                                           double* __restrict__ u,
                                                            const double* __restrict__ stop) {
   if (stopped(stop)) return;
-  __shared__ double red[kCgRows][2][kCgThreads / 64];
-  const int64_t s0 = (int64_t)blockIdx.x * kCgRows;
+  __shared__ double red[ROWS][2][kCgThreads / 64];
+  const int64_t s0 = (int64_t)blockIdx.x * ROWS;
   const int64_t P2 = P / 2;
   const int64_t span = (P2 + gridDim.y - 1) / gridDim.y;
   const int64_t kb = (int64_t)blockIdx.y * span, ke = std::min<int64_t>(P2, kb + span);
-  double ar[kCgRows], ai[kCgRows];
+  double ar[ROWS], ai[ROWS];
 #pragma unroll
-  for (int r = 0; r < kCgRows; ++r) ar[r] = ai[r] = 0.0;
+  for (int r = 0; r < ROWS; ++r) ar[r] = ai[r] = 0.0;
   for (int64_t k2 = kb + threadIdx.x; k2 < ke; k2 += kCgThreads) {
     const double4 vv = reinterpret_cast<const double4*>(v)[k2];
 #pragma unroll
-    for (int r = 0; r < kCgRows; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
       if (s0 + r < S) {
         const float4 o = stream_load4(O + (size_t)(s0 + r) * P * 2 + 4 * k2);
         ar[r] = fma((double)o.x, vv.x, fma(-(double)o.y, vv.y, ar[r]));
@@ -164,7 +192,7 @@ __global__ __launch_bounds__(kCgThreads) void rows2_kernel(const float* __restri
   }
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-  for (int r = 0; r < kCgRows; ++r) {
+  for (int r = 0; r < ROWS; ++r) {
     const double sr = wave_sum(ar[r]), si = wave_sum(ai[r]);
     if (lane == 0) {
       red[r][0][wv] = sr;
@@ -172,7 +200,7 @@ __global__ __launch_bounds__(kCgThreads) void rows2_kernel(const float* __restri
     }
   }
   __syncthreads();
-  if (threadIdx.x < kCgRows && s0 + threadIdx.x < S) {
+  if (threadIdx.x < ROWS && s0 + threadIdx.x < S) {
     const int r = threadIdx.x;
     double sr = 0.0, si = 0.0;
 #pragma unroll
@@ -180,9 +208,14 @@ __global__ __launch_bounds__(kCgThreads) void rows2_kernel(const float* __restri
       sr += red[r][0][w];
       si += red[r][1][w];
     }
-    double* dst = upart + 2 * ((size_t)blockIdx.y * S + s0 + r);
-    dst[0] = sr;
-    dst[1] = si;
+    if (gridDim.y == 1) {
+      u[2 * (s0 + r)] = (sr - mv[0]) * inv_sqrt_s;
+      u[2 * (s0 + r) + 1] = (si - mv[1]) * inv_sqrt_s;
+    } else {
+      double* dst = upart + 2 * ((size_t)blockIdx.y * S + s0 + r);
+      dst[0] = sr;
+      dst[1] = si;
+    }
   }
 }
 
@@ -211,10 +244,12 @@ __global__ __launch_bounds__(kCgThreads) void cols2_kernel(const float* __restri
                                                            int64_t P, int64_t slab,
                                                            const double* __restrict__ u,
                                                            double* __restrict__ part,
+                                                           double* __restrict__ us_part,
                                                            const double* __restrict__ stop) {
   if (stopped(stop)) return;
   const int64_t k2 = (int64_t)blockIdx.x * kCgThreads + threadIdx.x;
   const int64_t sb = (int64_t)blockIdx.y * slab, se = std::min<int64_t>(S, sb + slab);
+  if (u && blockIdx.x == 0 && threadIdx.x < 64) slab_usum(u, sb, se, us_part);
   if (k2 >= P / 2) return;
   double q0r = 0.0, q0i = 0.0, q1r = 0.0, q1i = 0.0;
   int64_t s = sb;
@@ -266,19 +301,41 @@ __device__ double vsum(double v, double* red) {
 // Column sums over the slabs: out[k] = sum_slab part[slab][k], then one of
 //   mode 0: out = conj(part-sum) / S   (the mean m, from the u = 1 pass)
 //   mode 1: out = (part-sum - conj(m) usum) / sqrt(S) * a + lambda * p (A p)
-// where usum = scal[2..3] = sum_s u_s and a = 1; b is mode 1 with lambda = 0
-// and a = -dtau.
-__global__ __launch_bounds__(kCgThreads) void slab_sum_kernel(
-    const double* __restrict__ part, int nslab, int64_t P, int mode, double S_or_invsqrt,
-    const double* __restrict__ m, const double* __restrict__ usum, double scale, double lambda,
+// where usum = sum_s u_s (us_part per slab) and a = 1; b is mode 1 with
+// lambda = 0 and a = -dtau.  One wavefront a block and sixteen slabs' loads in
+// flight per thread (the sum in slab order): 16 -> 7.5 us at P = 2700, 63 slabs.
+__global__ __launch_bounds__(64) void slab_sum_kernel(
+    const double2* __restrict__ part, int nslab, int64_t P, int mode, double S_or_invsqrt,
+    const double* __restrict__ m, const double* __restrict__ us_part, double scale, double lambda,
     const double* __restrict__ p, double* __restrict__ out, const double* __restrict__ stop) {
   if (stopped(stop)) return;
-  const int64_t k = (int64_t)blockIdx.x * kCgThreads + threadIdx.x;
+  const int64_t k = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  double ur = 0.0, ui = 0.0;
+  if (mode != 0) {
+    for (int j = threadIdx.x; j < nslab; j += 64) {
+      ur += us_part[2 * j];
+      ui += us_part[2 * j + 1];
+    }
+    ur = wave_sum(ur);
+    ui = wave_sum(ui);
+  }
   if (k >= P) return;
   double qr = 0.0, qi = 0.0;
-  for (int j = 0; j < nslab; ++j) {
-    qr += part[2 * ((size_t)j * P + k)];
-    qi += part[2 * ((size_t)j * P + k) + 1];
+  int j = 0;
+  for (; j + 16 <= nslab; j += 16) {
+    double2 v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = part[(size_t)(j + i) * P + k];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      qr += v[i].x;
+      qi += v[i].y;
+    }
+  }
+  for (; j < nslab; ++j) {
+    const double2 v = part[(size_t)j * P + k];
+    qr += v.x;
+    qi += v.y;
   }
   if (mode == 0) {                          // the column kernel conjugates O
     out[2 * k] = qr / S_or_invsqrt;
@@ -286,8 +343,8 @@ __global__ __launch_bounds__(kCgThreads) void slab_sum_kernel(
     return;
   }
   // conj(m_k) * usum
-  const double cr = m[2 * k] * usum[0] + m[2 * k + 1] * usum[1];
-  const double ci = m[2 * k] * usum[1] - m[2 * k + 1] * usum[0];
+  const double cr = m[2 * k] * ur + m[2 * k + 1] * ui;
+  const double ci = m[2 * k] * ui - m[2 * k + 1] * ur;
   double rr = (qr - cr) * S_or_invsqrt * scale, ri = (qi - ci) * S_or_invsqrt * scale;
   if (p) {
     rr = fma(lambda, p[2 * k], rr);
@@ -297,10 +354,9 @@ __global__ __launch_bounds__(kCgThreads) void slab_sum_kernel(
   out[2 * k + 1] = ri;
 }
 
-// eps = (E - <E>) / sqrt(S); scal[2..3] = sum_s eps_s (zero up to rounding).
+// eps = (E - <E>) / sqrt(S).
 __global__ __launch_bounds__(kVecThreads) void eps_kernel(const double* __restrict__ e, int64_t S,
-                                                          double* __restrict__ eps,
-                                                          double* __restrict__ scal) {
+                                                          double* __restrict__ eps) {
   __shared__ double red[kVecThreads];
   double sr = 0.0, si = 0.0;
   for (int64_t i = threadIdx.x; i < S; i += kVecThreads) {
@@ -309,33 +365,18 @@ __global__ __launch_bounds__(kVecThreads) void eps_kernel(const double* __restri
   }
   const double mr = vsum(sr, red) / (double)S, mi = vsum(si, red) / (double)S;
   const double is = 1.0 / sqrt((double)S);
-  double tr = 0.0, ti = 0.0;
   for (int64_t i = threadIdx.x; i < S; i += kVecThreads) {
-    const double a = (e[2 * i] - mr) * is, b = (e[2 * i + 1] - mi) * is;
-    eps[2 * i] = a;
-    eps[2 * i + 1] = b;
-    tr += a;
-    ti += b;
-  }
-  tr = vsum(tr, red);
-  ti = vsum(ti, red);
-  if (threadIdx.x == 0) {
-    scal[2] = tr;
-    scal[3] = ti;
+    eps[2 * i] = (e[2 * i] - mr) * is;
+    eps[2 * i + 1] = (e[2 * i + 1] - mi) * is;
   }
 }
 
-// scal[0..1] = m . v (no conjugation) and scal[2..3] stays; sum of u set by
-// usum_kernel.
-__global__ __launch_bounds__(kVecThreads) void mdot_kernel(const double* __restrict__ m,
-                                                           const double* __restrict__ v, int64_t P,
-                                                           double* __restrict__ scal,
-                                                           const double* __restrict__ stop) {
-  if (stopped(stop)) return;
-  __shared__ double red[kVecThreads];
+// scal[0..1] = m . p (no conjugation), the centring term of O_bar p; one block.
+__device__ __forceinline__ void m_dot_p(const double* __restrict__ m, const double* p, int64_t P,
+                                        double* __restrict__ scal, double* red) {
   double sr = 0.0, si = 0.0;
   for (int64_t k = threadIdx.x; k < P; k += kVecThreads) {
-    const cd a = {m[2 * k], m[2 * k + 1]}, b = {v[2 * k], v[2 * k + 1]};
+    const cd a = {m[2 * k], m[2 * k + 1]}, b = {p[2 * k], p[2 * k + 1]};
     const cd c = cmul(a, b);
     sr += c.x;
     si += c.y;
@@ -348,31 +389,13 @@ __global__ __launch_bounds__(kVecThreads) void mdot_kernel(const double* __restr
   }
 }
 
-// scal[2..3] = sum_s u_s.
-__global__ __launch_bounds__(kVecThreads) void usum_kernel(const double* __restrict__ u, int64_t S,
-                                                           double* __restrict__ scal,
-                                                           const double* __restrict__ stop) {
-  if (stopped(stop)) return;
-  __shared__ double red[kVecThreads];
-  double sr = 0.0, si = 0.0;
-  for (int64_t i = threadIdx.x; i < S; i += kVecThreads) {
-    sr += u[2 * i];
-    si += u[2 * i + 1];
-  }
-  sr = vsum(sr, red);
-  si = vsum(si, red);
-  if (threadIdx.x == 0) {
-    scal[2] = sr;
-    scal[3] = si;
-  }
-}
-
-// CG start: x = 0, r = p = b; cg[0] = r^H r, cg[1] = b^H b.
+// CG start: x = 0, r = p = b; cg[0] = r^H r, cg[1] = b^H b; scal = m . p.
 __global__ __launch_bounds__(kVecThreads) void cg_init_kernel(const double* __restrict__ b,
                                                               int64_t P, double* __restrict__ x,
-                                                              double* __restrict__ r,
-                                                              double* __restrict__ p,
-                                                              double* __restrict__ cg) {
+                                                              double* __restrict__ r, double* p,
+                                                              double* __restrict__ cg,
+                                                              const double* __restrict__ m,
+                                                              double* __restrict__ scal) {
   __shared__ double red[kVecThreads];
   double s = 0.0;
   for (int64_t k = threadIdx.x; k < P; k += kVecThreads) {
@@ -390,19 +413,21 @@ __global__ __launch_bounds__(kVecThreads) void cg_init_kernel(const double* __re
     cg[3] = 0.0;
     cg[4] = 0.0;
   }
+  m_dot_p(m, p, P, scal, red);                // every thread reads the p it wrote
 }
 
 // One CG update given q = A p: alpha = rr / (p^H q), x += alpha p,
 // r -= alpha q, beta = rr' / rr, p = r + beta p.  cg[0] = rr', cg[2] = 1
 // if p^H q <= 0 (A not positive definite along p); cg[4] counts the
 // iterations and cg[3] = 1 stops the solve (not positive definite, or
-// rr' <= thr2 = tol^2 b^H b).
+// rr' <= thr2 = tol^2 b^H b); scal = m . p for the next iteration.
 __global__ __launch_bounds__(kVecThreads) void cg_step_kernel(double* __restrict__ x,
-                                                              double* __restrict__ r,
-                                                              double* __restrict__ p,
+                                                              double* __restrict__ r, double* p,
                                                               const double* __restrict__ q,
                                                               int64_t P, double* __restrict__ cg,
-                                                              double thr2) {
+                                                              double thr2,
+                                                              const double* __restrict__ m,
+                                                              double* __restrict__ scal) {
   if (cg[3] != 0.0) return;
   __shared__ double red[kVecThreads];
   double s = 0.0;
@@ -440,11 +465,12 @@ __global__ __launch_bounds__(kVecThreads) void cg_step_kernel(double* __restrict
     cg[4] += 1.0;
     if (!(rr2 > thr2)) cg[3] = 1.0;
   }
+  m_dot_p(m, p, P, scal, red);                // every thread reads the p it wrote
 }
 
 struct CgLayout {
   int64_t nslab, slab;
-  size_t m, eps, u, b, r, p, q, part, upart, scal, cg, bytes;
+  size_t m, eps, u, b, r, p, q, part, upart, us, scal, cg, bytes;
 };
 
 CgLayout cg_layout(const nqs_ctx* c, int64_t S) {
@@ -468,6 +494,7 @@ CgLayout cg_layout(const nqs_ctx* c, int64_t S) {
   L.q = off; off += al((size_t)P * 16);
   L.part = off; off += al((size_t)L.nslab * P * 16);
   L.upart = off; off += al((size_t)kRowParts * S * 16);
+  L.us = off; off += al((size_t)L.nslab * 16);
   L.scal = off; off += al(8 * 8);
   L.cg = off; off += al(8 * 8);
   L.bytes = off;
@@ -476,13 +503,13 @@ CgLayout cg_layout(const nqs_ctx* c, int64_t S) {
 
 template <typename RO>
 hipError_t cols_to(const RO* O, int64_t S, int64_t P, const CgLayout& L, const double* u,
-                   double* part, const double* stop, hipStream_t st) {
+                   double* part, double* us, const double* stop, hipStream_t st) {
   if constexpr (sizeof(RO) == 4) {
     const dim3 grid((unsigned)((P / 2 + kCgThreads - 1) / kCgThreads), (unsigned)L.nslab);
-    cols2_kernel<<<grid, kCgThreads, 0, st>>>(O, S, P, L.slab, u, part, stop);
+    cols2_kernel<<<grid, kCgThreads, 0, st>>>(O, S, P, L.slab, u, part, us, stop);
   } else {
     const dim3 grid((unsigned)((P + kCgThreads - 1) / kCgThreads), (unsigned)L.nslab);
-    cols_kernel<RO><<<grid, kCgThreads, 0, st>>>(O, S, P, L.slab, u, part, stop);
+    cols_kernel<RO><<<grid, kCgThreads, 0, st>>>(O, S, P, L.slab, u, part, us, stop);
   }
   return hipGetLastError();
 }
@@ -504,19 +531,21 @@ hipError_t cg_run(nqs_ctx* c, const RO* O, const double* eloc, int64_t S, double
   double* upart = (double*)(ws + L.upart);
   double* scal = (double*)(ws + L.scal);
   double* cg = (double*)(ws + L.cg);
-  const unsigned ptiles = (unsigned)((P + kCgThreads - 1) / kCgThreads);
+  double* us = (double*)(ws + L.us);
+  const unsigned ptiles = (unsigned)((P + 63) / 64);
   const double is = 1.0 / std::sqrt((double)S);
   hipError_t e;
   // mean m = <O>
-  if ((e = cols_to(O, S, P, L, nullptr, part, nullptr, st)) != hipSuccess) return e;
-  slab_sum_kernel<<<ptiles, kCgThreads, 0, st>>>(part, (int)L.nslab, P, 0, (double)S, nullptr,
-                                                 nullptr, 1.0, 0.0, nullptr, m, nullptr);
+  if ((e = cols_to(O, S, P, L, nullptr, part, us, nullptr, st)) != hipSuccess) return e;
+  const double2* part2 = (const double2*)part;
+  slab_sum_kernel<<<ptiles, 64, 0, st>>>(part2, (int)L.nslab, P, 0, (double)S, nullptr, nullptr,
+                                         1.0, 0.0, nullptr, m, nullptr);
   // eps and b = -dtau O_bar^H eps
-  eps_kernel<<<1, kVecThreads, 0, st>>>(eloc, S, eps, scal);
-  if ((e = cols_to(O, S, P, L, eps, part, nullptr, st)) != hipSuccess) return e;
-  slab_sum_kernel<<<ptiles, kCgThreads, 0, st>>>(part, (int)L.nslab, P, 1, is, m, scal + 2, -dtau,
-                                                 0.0, nullptr, b, nullptr);
-  cg_init_kernel<<<1, kVecThreads, 0, st>>>(b, P, x, r, p, cg);
+  eps_kernel<<<1, kVecThreads, 0, st>>>(eloc, S, eps);
+  if ((e = cols_to(O, S, P, L, eps, part, us, nullptr, st)) != hipSuccess) return e;
+  slab_sum_kernel<<<ptiles, 64, 0, st>>>(part2, (int)L.nslab, P, 1, is, m, us, -dtau, 0.0, nullptr,
+                                         b, nullptr);
+  cg_init_kernel<<<1, kVecThreads, 0, st>>>(b, P, x, r, p, cg, m, scal);
   double h[5];
   if ((e = hipMemcpyAsync(h, cg, 40, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
   if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
@@ -531,24 +560,29 @@ hipError_t cg_run(nqs_ctx* c, const RO* O, const double* eloc, int64_t S, double
       const int nb = std::min(kCgBatch, max_iter - issued);
       for (int j = 0; j < nb; ++j) {
         // q = A p
-        mdot_kernel<<<1, kVecThreads, 0, st>>>(m, p, P, scal, stop);
         if constexpr (sizeof(RO) == 4) {
           // column parts of at least four sweeps of the block over column pairs
           const int parts = (int)std::max<int64_t>(
               1, std::min<int64_t>(kRowParts, P / 2 / (4 * kCgThreads)));
-          const dim3 rgrid((unsigned)((S + kCgRows - 1) / kCgRows), (unsigned)parts);
-          rows2_kernel<<<rgrid, kCgThreads, 0, st>>>(O, S, P, p, upart, stop);
-          rows2_finish_kernel<<<(unsigned)((S + kCgThreads - 1) / kCgThreads), kCgThreads, 0,
-                                st>>>(upart, parts, S, scal, is, u, stop);
+          const int64_t blocks = (S + kCgRows - 1) / kCgRows;
+          if (blocks * parts >= kRowBlocks) {
+            rows2_kernel<kCgRows><<<dim3((unsigned)blocks, (unsigned)parts), kCgThreads, 0, st>>>(
+                O, S, P, p, scal, is, upart, u, stop);
+          } else {
+            rows2_kernel<kRowsFew><<<dim3((unsigned)((S + kRowsFew - 1) / kRowsFew), (unsigned)parts),
+                                     kCgThreads, 0, st>>>(O, S, P, p, scal, is, upart, u, stop);
+          }
+          if (parts > 1)
+            rows2_finish_kernel<<<(unsigned)((S + kCgThreads - 1) / kCgThreads), kCgThreads, 0,
+                                  st>>>(upart, parts, S, scal, is, u, stop);
         } else {
           rows_kernel<RO><<<(unsigned)((S + kCgRows - 1) / kCgRows), kCgThreads, 0, st>>>(
               O, S, P, p, scal, is, u, stop);
         }
-        usum_kernel<<<1, kVecThreads, 0, st>>>(u, S, scal, stop);
-        if ((e = cols_to(O, S, P, L, u, part, stop, st)) != hipSuccess) return e;
-        slab_sum_kernel<<<ptiles, kCgThreads, 0, st>>>(part, (int)L.nslab, P, 1, is, m, scal + 2,
-                                                       1.0, lambda, p, q, stop);
-        cg_step_kernel<<<1, kVecThreads, 0, st>>>(x, r, p, q, P, cg, thr2);
+        if ((e = cols_to(O, S, P, L, u, part, us, stop, st)) != hipSuccess) return e;
+        slab_sum_kernel<<<ptiles, 64, 0, st>>>(part2, (int)L.nslab, P, 1, is, m, us, 1.0, lambda, p,
+                                               q, stop);
+        cg_step_kernel<<<1, kVecThreads, 0, st>>>(x, r, p, q, P, cg, thr2, m, scal);
       }
       issued += nb;
       if ((e = hipGetLastError()) != hipSuccess) return e;
