@@ -64,6 +64,11 @@ bool composed_moments(const nqs_ctx* c, int op) {
          (eloc_fused_supported(c) || eloc_wide_supported(c));
 }
 size_t fused_part_bytes(const nqs_ctx* c) { return (size_t)(c->G / 16) * 6 * 8; }
+// of ch configurations, at most ch of them in one launch: a small launch of the
+// fused kernel splits its bond lists over at most its wavefront slots
+size_t part_bytes(const nqs_ctx* c, int64_t ch) {
+  return std::max(fused_part_bytes(c) * (size_t)ch, fused_max_split_items(c) * 6 * 8);
+}
 // nqs_eloc_grad shares the per-image log amplitudes of the wide E_loc kernel
 // with the wide gradient kernel (no theta pass of its own)
 bool shared_eloc_grad(const nqs_ctx* c) {
@@ -153,7 +158,7 @@ Work plan(const nqs_ctx* c, int op, int64_t S, void* ws) {
     ch = std::max<int64_t>(std::min<int64_t>(ch, std::max<int64_t>(S, 1) * c->NB), c->NB);
     wk.chunk = ch;
     wk.n_out = std::max<int64_t>(1, ch / c->NB);
-    wk.partial = (double*)cv.take(fused_part_bytes(c) * ch);
+    wk.partial = (double*)cv.take(part_bytes(c, ch));
     wk.nb_spins = (int8_t*)cv.take((size_t)ch * c->N);
     wk.nb_lp = (double*)cv.take((size_t)ch * 16);
     wk.nb_e1e2 = (double*)cv.take((size_t)ch * 32);
@@ -172,7 +177,7 @@ Work plan(const nqs_ctx* c, int op, int64_t S, void* ws) {
   const int64_t ch = chunk_of(c, op, S);
   wk.chunk = ch;
   if (op == NQS_OP_ELOC_GRAD) {
-    wk.partial = (double*)cv.take(fused_part_bytes(c) * ch);
+    wk.partial = (double*)cv.take(part_bytes(c, ch));
     wk.L = (double*)cv.take(2 * z.L * ch);
     wk.w = cv.take(z.w * ch);
     wk.lp = (double*)cv.take((size_t)16 * ch);
@@ -182,7 +187,7 @@ Work plan(const nqs_ctx* c, int op, int64_t S, void* ws) {
   }
   if (fused_grad(c, op)) return wk;
   if (fused_eloc(c, op)) {
-    wk.partial = (double*)cv.take(fused_part_bytes(c) * ch);
+    wk.partial = (double*)cv.take(part_bytes(c, ch));
     wk.lp = (double*)cv.take((size_t)16 * ch);
     wk.bytes = cv.off;
     return wk;

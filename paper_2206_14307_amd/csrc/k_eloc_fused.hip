@@ -21,6 +21,10 @@
 // the column blocks: log psi = M + log sum e^{m-M} den,
 // E_loc = diag + sum e^{m-M} Q / sum e^{m-M} den.
 //
+// Few work items (small calls) are split further, into shares of the bond list
+// (SPLIT), so that the launch fills the device; each share emits its own
+// partial.
+//
 // Persistent workgroups keep the bond rows and the W fragments in LDS for the
 // whole launch; the rows are placed (host side) so that the 16 images of a q
 // row read distinct LDS bank groups.
@@ -106,10 +110,10 @@ __device__ __forceinline__ void qprod_pair(R& pr, R& pi, R orr, R oi) {
   pi = vr * wi + vi * wr;
 }
 
-template <int N, int PREC, int K, int M, bool RECIP>
+template <int N, int PREC, int K, int M, bool RECIP, bool SPLIT>
 __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
-    const int8_t* __restrict__ spins, int64_t S, const uint8_t* __restrict__ perm, int G,
-    const typename ThetaTraits<PREC>::AFrag* __restrict__ wfrag,
+    const int8_t* __restrict__ spins, int64_t S, int nsplit, const uint8_t* __restrict__ perm,
+    int G, const typename ThetaTraits<PREC>::AFrag* __restrict__ wfrag,
     const typename ThetaTraits<PREC>::R* __restrict__ bias,
     const typename ThetaTraits<PREC>::R* __restrict__ avec, const int32_t* __restrict__ bonds,
     const int32_t* __restrict__ fmap, const int32_t* __restrict__ frow,
@@ -126,23 +130,62 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
   __shared__ __align__(16) AF Wl[NHT * NK * 64];
   __shared__ uint16_t lists[kFusedWaves][NB];
 
-  for (int idx = threadIdx.x; idx < NB * ROW; idx += blockDim.x) {
-    const int beta = idx / ROW, j = idx % ROW;
-    Tl[frow[beta] + j] = Ttab[(size_t)beta * ROW + j];
+  // bond rows into LDS, a pair of reals at a time, eight loads in flight
+  {
+    using V = c2_t<R>;
+    constexpr int RP = ROW / 2, NP = NB * RP, TH = 64 * kFusedWaves;
+    const V* src = reinterpret_cast<const V*>(Ttab);
+    for (int i0 = threadIdx.x; i0 < NP; i0 += 8 * TH) {
+      V v[8];
+      int at[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = min(i0 + e * TH, NP - 1), beta = i / RP;
+        v[e] = src[i];
+        at[e] = frow[beta] + 2 * (i - beta * RP);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) *reinterpret_cast<V*>(&Tl[at[e]]) = v[e];
+    }
   }
   for (int idx = threadIdx.x; idx < NHT * NK * 64; idx += blockDim.x) Wl[idx] = wfrag[idx];
   __syncthreads();
 
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int q = lane >> 4, c = lane & 15;
+  // work items: (configuration, column block), and with SPLIT a share of the
+  // bond list.  Item i goes to workgroup i mod gridDim, so that few items spread
+  // over the CUs; (s, cb) advance by the stride without a division
   const int cbs = G / 16;
-  const int64_t n_items = S * cbs;
+  const int64_t n_items = S * cbs * (SPLIT ? nsplit : 1);
   const int64_t stride = (int64_t)gridDim.x * kFusedWaves;
   uint16_t* list = lists[wv];
+  int64_t item = (int64_t)wv * gridDim.x + blockIdx.x;
+  int share = 0, d_share = 0;
+  int64_t blk = item, d_blk = stride;
+  if constexpr (SPLIT) {
+    blk = item / nsplit;
+    share = (int)(item - blk * nsplit);
+    d_blk = stride / nsplit;
+    d_share = (int)(stride - d_blk * nsplit);
+  }
+  int64_t s = blk / cbs;
+  int cb = (int)(blk - s * cbs);
+  const int64_t d_s = d_blk / cbs;
+  const int d_cb = (int)(d_blk - d_s * cbs);
 
-  for (int64_t item = (int64_t)blockIdx.x * kFusedWaves + wv; item < n_items; item += stride) {
-    const int64_t s = item / cbs;
-    const int g = (int)(item % cbs) * 16 + c;
+  for (; item < n_items; item += stride, s += d_s, cb += d_cb, share += d_share) {
+    if constexpr (SPLIT) {
+      if (share >= nsplit) {
+        share -= nsplit;
+        ++cb;
+      }
+    }
+    while (cb >= cbs) {
+      cb -= cbs;
+      ++s;
+    }
+    const int g = cb * 16 + c;
     const int8_t* srow = spins + s * N;
     const uint8_t* prow = perm + (size_t)g * N;
     typename T::BFrag bx[NK];
@@ -200,20 +243,23 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
 #pragma unroll
     for (int k = 0; k < K; ++k) Qr[k] = Qi[k] = 0.0;
     const int32_t* bm = fmap + (size_t)g * NB;
+    // this share's bonds [i_lo, i_hi): whole passes of the list
+    const int per = SPLIT ? 2 * (((nc + 1) / 2 + nsplit - 1) / nsplit) : nc;
+    const int i_lo = SPLIT ? share * per : 0, i_hi = SPLIT ? min(nc, i_lo + per) : nc;
     int en[2] = {0, 0}, vn[2] = {0, 0};
-    if (nc > 0) {
+    if (i_lo < i_hi) {
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
-        en[n] = list[n < nc ? n : 0];
+        en[n] = list[min(i_lo + n, i_hi - 1)];
         vn[n] = bm[en[n] & 0x7fff];
       }
     }
-    for (int i0 = 0; i0 < nc; i0 += 2) {
+    for (int i0 = i_lo; i0 < i_hi; i0 += 2) {
       const int e0 = en[0], e1 = en[1], v0 = vn[0], v1 = vn[1];
-      if (i0 + 2 < nc) {
+      if (i0 + 2 < i_hi) {
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
-          en[n] = list[i0 + 2 + n < nc ? i0 + 2 + n : i0 + 2];
+          en[n] = list[min(i0 + 2 + n, i_hi - 1)];
           vn[n] = bm[en[n] & 0x7fff];
         }
       }
@@ -224,7 +270,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
       const R* row1 = Tl + (v1 >> 1);
       const R* T0 = row0 + 4 * q;
       const R* T1 = row1 + 4 * q;
-      const bool valid1 = i0 + 1 < nc;
+      const bool valid1 = i0 + 1 < i_hi;
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         // stream starts: (a re, a im, b re, b im) of lane q; stream 0 (q = 0,
@@ -282,7 +328,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
     }
     qr *= 0.5;
     qi *= 0.5;
-    if (q != 0) {
+    if (q != 0 || (SPLIT && share != 0)) {
       denr = 0.0;
       deni = 0.0;
     }
@@ -342,17 +388,36 @@ __global__ __launch_bounds__(64) void fused_finish_kernel(
   }
 }
 
+}  // namespace
+
+// Shares of the bond list per (configuration, column block): where one
+// wavefront each leaves wavefront slots of the persistent grid empty, the
+// bonds are split as far as the slots go (at most eight: every share computes
+// theta again, about five bond passes' worth).  A call of nqs_eloc at 6x6
+// M = 72, with the rows staged eight loads at a time: 16 configurations
+// 56.6 -> 22.0 us (seven shares), one 57 -> 20 us.
+size_t fused_max_split_items(const nqs_ctx* c) {
+  return (size_t)kFusedWaves * (c->n_cu > 0 ? c->n_cu : 256);
+}
+int fused_nsplit(const nqs_ctx* c, int64_t S) {
+  const int64_t items = std::max<int64_t>(S, 1) * (c->G / 16);
+  const int64_t slots = (int64_t)fused_max_split_items(c);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(8, slots / items));
+}
+
+namespace {
+
 template <int N, int PREC, int K, int M, bool RECIP>
 hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, double* logpsi,
                double* eloc, int eloc_stride, hipStream_t st) {
   using T = ThetaTraits<PREC>;
   using R = typename T::R;
-  const int cbs = c->G / 16;
-  const int64_t items = S * cbs;
-  int64_t blocks = (items + kFusedWaves - 1) / kFusedWaves;
-  blocks = std::min<int64_t>(blocks, c->n_cu > 0 ? c->n_cu : 256);
-  eloc_fused_kernel<N, PREC, K, M, RECIP><<<(unsigned)blocks, 64 * kFusedWaves, 0, st>>>(
-      spins, S, c->dev.perm, c->G,
+  const int nsplit = fused_nsplit(c, S), cbs = c->G / 16 * nsplit;
+  const int64_t blocks = std::min<int64_t>(S * cbs, c->n_cu > 0 ? c->n_cu : 256);
+  auto kernel = nsplit > 1 ? eloc_fused_kernel<N, PREC, K, M, RECIP, true>
+                           : eloc_fused_kernel<N, PREC, K, M, RECIP, false>;
+  kernel<<<(unsigned)blocks, 64 * kFusedWaves, 0, st>>>(
+      spins, S, nsplit, c->dev.perm, c->G,
       (const typename T::AFrag*)(PREC == kPrecF32X3   ? c->par.wfrag3
                                  : PREC == kPrecF32S3 ? c->par.wfrag_s3
                                                       : c->par.wfrag),

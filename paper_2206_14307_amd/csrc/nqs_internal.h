@@ -159,7 +159,9 @@ hipError_t launch_eloc_rows(const nqs_ctx* c, const int8_t* spins, int64_t S, co
 hipError_t launch_eloc_bonds_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                                  const void* w, double* partial, hipStream_t st);
 // Fused theta + epilogue + bond exchanges (K*M <= 128 register-resident
-// variants); part holds S * (G/16) * 6 doubles.
+// variants); part holds S * (G/16) * fused_nsplit * 6 doubles.
+int fused_nsplit(const nqs_ctx* c, int64_t S);
+size_t fused_max_split_items(const nqs_ctx* c);   // most work items of a split launch
 bool eloc_fused_supported(const nqs_ctx* c);
 bool grad_fused_supported(const nqs_ctx* c);
 hipError_t launch_enum_sz0(const nqs_ctx* c, int64_t count, int8_t* out, hipStream_t st);
