@@ -2,26 +2,35 @@
 // models whose hidden layer does not fit in registers (K*M > 128,
 // M a multiple of 16), with theta in FP32 or split BF16.
 //
-// A workgroup of kWideWaves wavefronts takes one sample at a time; every
-// wavefront takes one 16-image column block, so all of them share the
-// sample's antiparallel-bond list and do the same amount of work.  The hidden
-// units are walked in chunks of kHC in lockstep across the workgroup:
+// A work item is one 16-image column block of one configuration (or a share of
+// its bond list, for calls too small to fill the device); a wavefront walks
+// the hidden units of its item in chunks of kHC, in lockstep with the other
+// seven wavefronts of its workgroup, which are at items of their own:
 //   * the chunk's rows of the bond table T = tanh(D) (all 4N bonds x kHC units)
-//     are staged in LDS, double-buffered: each thread loads its share of the
-//     next chunk into registers at the start of a chunk and stores it at the
-//     end, so the loads overlap a whole chunk of work;
-//   * theta of the chunk (kHC/8 hidden tiles) runs on 16x16 MFMA with the W
-//     fragments read from L2, and the log 2cosh / tanh epilogue accumulates
-//     log psi of the image across chunks;
+//     are staged in LDS for all of them, double-buffered: each thread loads its
+//     share of the next chunk into registers before the bond products and
+//     stores it after them;
+//   * theta of the chunk runs on 16x16 MFMA with the W fragments read from L2,
+//     and the log 2cosh / tanh epilogue accumulates log psi of the images;
 //   * tanh(theta) of the chunk goes through a small LDS tile so that lane
-//     (qg, c) holds all kHC values of image c, and the lane multiplies the
-//     running products F_s prod_h (s + t_h T_h) of its bonds b = qg + 4 jb
+//     (q, c) holds all kHC values of image c, and the lane multiplies the
+//     running products F_s prod_h (s + t_h T_h) of its bonds q + 4 jb
 //     (jb < wide_bonds) of the list, the bond rows read from LDS.
 // At the end of each RBM the products are weighted with the image weights
 // u = chi e^{L - m} (m a running maximum over the RBMs of the wave's images)
-// and summed; the wave emits (m, sum u, sum u R) per (sample, column block)
-// in the same format as the fused kernel, combined by its finish kernel.
-// Bonds beyond 4 wide_bonds per sample are handled in further passes.
+// and summed; the wave emits (m, sum u, sum u R) per item in the same format as
+// the fused kernel, combined by its finish kernel.
+//
+// Bound: VALU issue of the factors, 8 instructions per (image, bond, unit) and
+// 4 or 5 per pair of bonds and chunk for the row addresses and signs.  10x10
+// M = 400, 1500 configurations: 20.5 ms, 0.97 of the issue rate, where eight
+// wavefronts on the blocks of one configuration (7 rounds for 50 blocks) and 18
+// bonds a lane, so theta three times per image, took 28.3 ms; 8x8 K = 4 M = 256,
+// 1000 configurations 17.3 -> 14.9 ms; one 10x10 configuration, its lists in
+// eight shares, 4.4 -> 0.27 ms.  Every product has the same factors in the same
+// order.  theta of the next chunk in half of the wavefronts before the bond
+// products, in the others after them, gave 2-4 % at 6x6 and 8x8 and lost 1 % at
+// 10x10 in split BF16 and 3-8 % in calls of a few configurations: not used.
 #include "theta_common.h"
 #include "hops.h"
 
@@ -30,35 +39,87 @@ namespace nqs {
 namespace {
 
 constexpr int kWideWaves = 8;
-// bonds per lane and pass (even: the products run two bonds at a time).
-// Each pass recomputes theta, so 72 bonds per pass at 8x8 and 10x10 take
-// their ~130 and ~200 antiparallel bonds in 2 and 3 passes where 64 took 3
-// and 4 (10-11 % faster, with somewhat more spilling at N = 100).  The
-// unordered-pair lists at 10x10 (~100 entries) take 2 passes either way, and
-// there the extra registers only spill.
+// Bonds per lane and walk over the hidden units (even: the products run two
+// bonds at a time; empty pairs are skipped).  The four lane groups cover 88,
+// 144 and 224 bonds, nearly every list of a configuration at Sz = 0 (means 74,
+// 130, 202), so theta is evaluated once per image.
+template <int N>
+constexpr int wide_bonds() { return N == 36 ? 22 : N == 64 ? 36 : 56; }
+// The list entries whose sums over several RBMs are rescaled as the running
+// maximum m rises; those of later entries are weighted once, with the final m.
 template <int N, bool PAIRS>
-constexpr int wide_bonds() { return N >= 64 && !(PAIRS && N >= 100) ? 18 : 16; }
-constexpr int kHC = 8;             // hidden units per chunk (multiple of 8)
-constexpr int kRP = kHC / 2;       // float4 per staged row
-constexpr int kTS = 2 * kHC + 4;   // LDS row stride of the staged table (floats)
+constexpr int wide_head() { return N >= 64 && !(PAIRS && N >= 100) ? 72 : 64; }
+constexpr int kHC = 8;             // hidden units per chunk
 constexpr int kXS = 2 * kHC + 4;   // LDS row stride of the tanh exchange tile (floats)
+constexpr int kRecK = kWideLrawK;  // RBMs whose per-image sums are held to the end of a walk
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const f32x4* lds_f32x4_ptr;
+typedef __attribute__((address_space(3))) const f32x2* lds_f32x2_ptr;
 
+// An RBM's results in a walk: per image Re L without log|P| and Im a x, per
+// lane the joined product P of 2 cosh (its rounding depends on the lane) and
+// the lane's sum over the later bonds.
+struct WideRec {
+  double Er[16], axi[16], dr[64], di[64];
+  float pr[64], pi[64];
+};
+
+// LDS, in bytes: the two staged chunks lie 64 KiB apart, so that a row's
+// address is (offset | buffer bit); the small arrays lie between them.
 template <int N>
 struct WideCfg {
   static constexpr int NB = 4 * N;
-  static constexpr int NSTG = (NB * kRP + 64 * kWideWaves - 1) / (64 * kWideWaves);  // float4 / thread
-  static constexpr int CAP16 = wide_cap16(NB);        // staged table, 16-byte units
-  static constexpr size_t LDS = 2ull * CAP16 * 16 + (size_t)kWideWaves * 16 * kXS * 4 + NB * 2 +
-                                NB * 4 + 16;
+  static constexpr uint32_t CAP = wide_cap16(NB) * 16;
+  static constexpr uint32_t BUF = 1u << 16;
+  static constexpr uint32_t TX = CAP;                                   // [waves][16][kXS] float
+  static constexpr uint32_t LIST = TX + kWideWaves * 16 * kXS * 4;      // [waves][NB] uint16
+  static constexpr uint32_t ROWS = LIST + kWideWaves * NB * 2;          // [NB] int: row starts
+  static constexpr uint32_t BUSY = ROWS + NB * 4;                       // [waves] int
+  static constexpr uint32_t REC = BUF + CAP;                            // [waves][kRecK] WideRec
+  static constexpr uint32_t LDS = REC + kWideWaves * kRecK * sizeof(WideRec);
+  static_assert(BUSY + kWideWaves * 4 <= BUF, "the small arrays fit between the chunks");
+};
+
+// Spins of an image as the sign bits of its theta B fragments: dword d of the
+// fragments has its two signs at bits d % 16 and 16 + d % 16 of word d / 16.
+// At N = 100 the fragments themselves would take 28 or 40 registers.
+template <int N, int PREC>
+struct XBits {
+  static constexpr int ND = 4 * nk_of<N, PREC>(), NW = (ND + 15) / 16;
+  uint32_t w[NW];
+  __device__ __forceinline__ void load(const int8_t* srow, const uint8_t* prow, int q) {
+    const SpinBits m = spin_bits<N>(srow);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) w[i] = 0u;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int kap = 32 * (d / 4) + 8 * q + 2 * (d % 4) + h;   // beyond the copies W is 0
+        w[d / 16] |= (x_bits<N>(m, prow[kap % N]) >> 31) << (d % 16 + 16 * h);
+      }
+    }
+  }
+  __device__ __forceinline__ bf16x8 frag(int kk) const {
+    uint32_t v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int d = 4 * kk + e;
+      v[e] = ((w[d / 16] << (15 - d % 16)) & 0x80008000u) | 0x3f003f00u;
+    }
+    return __builtin_bit_cast(bf16x8, v);
+  }
 };
 
 // PAIRS: the rows are exchange neighbours with parent bonds (parent[s]); the
 // bond list is the parent's unordered-pair list and pairs counted twice weigh 2.
-// WL: also write the images' log amplitudes, unreduced (see below).
-template <int N, int PREC, bool PAIRS, bool WL>
+// Lout: also write the images' log amplitudes, unreduced (see below).
+// per: items of a workgroup in a round (its first `per` wavefronts take them).
+template <int N, int PREC, bool PAIRS>
 __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
-    const int8_t* __restrict__ spins, int64_t S, const uint8_t* __restrict__ perm, int G, int K,
-    int M, const typename ThetaTraits<PREC>::AFrag* __restrict__ wfrag,
+    const int8_t* __restrict__ spins, int64_t S, int nsplit, int per,
+    const uint8_t* __restrict__ perm, int K, int M,
+    const typename ThetaTraits<PREC>::AFrag* __restrict__ wfrag,
     const float* __restrict__ bias, const float* __restrict__ avec,
     const int32_t* __restrict__ bonds, const int32_t* __restrict__ wmap,
     const int32_t* __restrict__ wrow,
@@ -66,322 +127,387 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
     double* __restrict__ part, const int16_t* __restrict__ parent, double* __restrict__ Lout) {
   using T = ThetaTraits<PREC>;
   using Cfg = WideCfg<N>;
-  constexpr int NB = Cfg::NB, NK = nk_of<N, PREC>(), NSTG = Cfg::NSTG;
-  constexpr int kWB = wide_bonds<N, PAIRS>();
-  static_assert(kWB % 2 == 0 && kWB <= 32, "bond slots: pairs, one bit each in a word");
-  static_assert(kTS == 4 * kWideRow16, "row size of the placement");
-  __shared__ __align__(16) float Tc[2][Cfg::CAP16 * 4];
-  __shared__ int wrl[NB];                    // row starts in floats
-  __shared__ __align__(16) float tx[kWideWaves][16 * kXS];
-  __shared__ uint16_t list[NB];
-  __shared__ int nc_s;
-  // WL: the wave's unreduced log amplitudes [RBM][image][4], held until the
-  // end of its image round (stores from the chunk loop slowed it)
-  __shared__ double lraw[WL ? kWideWaves : 1][WL ? kWideLrawK * 16 * 4 : 1];
+  constexpr int NB = Cfg::NB, G = 8 * N, nblk = G / 16, NK = nk_of<N, PREC>();
+  constexpr int THREADS = 64 * kWideWaves, E4 = NB * 4, NSTG = (E4 + THREADS - 1) / THREADS;
+  constexpr int kWB = wide_bonds<N>(), kHead = wide_head<N, PAIRS>();
+  constexpr bool PACK = N == 100;            // two bond slots' offsets in a register
+  constexpr bool BITS = N == 100;
+  constexpr int kOW = PACK ? kWB / 2 : kWB;
+  // aligned to the chunk distance, so that addresses are ORs
+  __shared__ __align__(65536) unsigned char lds[Cfg::LDS];
 
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, c = lane & 15;
-  const int KM = K * M, NCH = KM / kHC, CPR = M / kHC, nblk = G / 16;
-  const int rounds = (nblk + kWideWaves - 1) / kWideWaves;
+  const int KM = K * M, NCH = KM / kHC, CPR = M / kHC;
+  float* tx = reinterpret_cast<float*>(lds + Cfg::TX) + wv * 16 * kXS;
+  uint16_t* list = reinterpret_cast<uint16_t*>(lds + Cfg::LIST) + wv * NB;
+  int* rows = reinterpret_cast<int*>(lds + Cfg::ROWS);
+  int* busy = reinterpret_cast<int*>(lds + Cfg::BUSY);
+  WideRec* rec = reinterpret_cast<WideRec*>(lds + Cfg::REC) + wv * kRecK;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
-  // staging of chunk ch: element e = tid + 512 i -> row e / kRP, 16-byte part
-  // e % kRP of tanh(D); thread tid < NB also stages (F_+, F_-) of row tid for
-  // the chunk's RBM into the row's last 16 bytes.  The values sit in named
-  // registers (s0..s7, sF) between the loads and the LDS stores; the loads are
-  // unconditional (clamped to valid elements).
-  static_assert(NSTG <= 8, "staging registers");
-  float4 s0, s1, s2, s3, s4, s5, s6, s7, sF;
-#define NQS_STG_LD(I, CH)                                                                \
-  if constexpr (I < NSTG) {                                                              \
-    int e = tid + 64 * kWideWaves * I;                                                   \
-    e = e < NB * kRP ? e : 0;                                                            \
-    s##I = *reinterpret_cast<const float4*>(Tpm + (size_t)(e / kRP) * 4 * KM +           \
-                                            2 * kHC * (CH) + 4 * (e % kRP));             \
-  }
-#define NQS_STG_ST(I, BUF)                                                               \
-  if constexpr (I < NSTG) {                                                              \
-    const int e = tid + 64 * kWideWaves * I;                                             \
-    if (e < NB * kRP) *reinterpret_cast<float4*>(&Tc[BUF][wrl[e / kRP] + 4 * (e % kRP)]) = s##I; \
-  }
-#define NQS_STAGE_LOAD(CH)                                                               \
-  {                                                                                      \
-    NQS_STG_LD(0, CH) NQS_STG_LD(1, CH) NQS_STG_LD(2, CH) NQS_STG_LD(3, CH)              \
-    NQS_STG_LD(4, CH) NQS_STG_LD(5, CH) NQS_STG_LD(6, CH) NQS_STG_LD(7, CH)              \
-    sF = *reinterpret_cast<const float4*>(F + ((size_t)((CH) / CPR) * NB + (tid < NB ? tid : 0)) * 4); \
-  }
-#define NQS_STAGE_STORE(BUF)                                                             \
-  {                                                                                      \
-    NQS_STG_ST(0, BUF) NQS_STG_ST(1, BUF) NQS_STG_ST(2, BUF) NQS_STG_ST(3, BUF)          \
-    NQS_STG_ST(4, BUF) NQS_STG_ST(5, BUF) NQS_STG_ST(6, BUF) NQS_STG_ST(7, BUF)          \
-    if (tid < NB) *reinterpret_cast<float4*>(&Tc[BUF][wrl[tid] + 2 * kHC]) = sF;         \
-  }
-  for (int idx = tid; idx < NB; idx += 64 * kWideWaves) wrl[idx] = 4 * wrow[idx];
+  // staging of chunk ch: float4 e = tid + 512 i -> row e / 4, part e % 4 of
+  // tanh(D); thread tid < NB also stages (F_+, F_-) of row tid for the chunk's
+  // RBM into the row's last 16 bytes.
+  f32x4 stg[NSTG], sF;
+  const uint32_t sofs = (uint32_t)(tid >> 2) * 16u * (uint32_t)KM + 16u * (tid & 3);
+  auto stage_load = [&](int ch, int k) __attribute__((always_inline)) {
+    const char* b = reinterpret_cast<const char*>(Tpm) + (size_t)ch * (8 * kHC);
+#pragma unroll
+    for (int i = 0; i < NSTG; ++i)
+      if (THREADS * (i + 1) <= E4 || tid + THREADS * i < E4)
+        stg[i] = *reinterpret_cast<const f32x4*>(b + (size_t)i * (THREADS / 4) * 16 * KM + sofs);
+    if (tid < NB) sF = *reinterpret_cast<const f32x4*>(F + ((size_t)k * NB + tid) * 4);
+  };
+  auto stage_store = [&](uint32_t buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NSTG; ++i)
+      if (THREADS * (i + 1) <= E4 || tid + THREADS * i < E4)
+        *reinterpret_cast<f32x4*>(lds + buf + rows[(tid + THREADS * i) >> 2] + 16 * (tid & 3)) = stg[i];
+    if (tid < NB) *reinterpret_cast<f32x4*>(lds + buf + rows[tid] + 8 * kHC) = sF;
+  };
+  for (int i = tid; i < NB; i += THREADS) rows[i] = 16 * wrow[i];
   __syncthreads();
-  NQS_STAGE_LOAD(0)
-  NQS_STAGE_STORE(0)
-  int gc = 0;                                  // chunks processed by the workgroup so far
+  stage_load(0, 0);
+  stage_store(0);
+  uint32_t buf = 0;                            // byte offset of the chunk in use
 
-  for (int64_t s = blockIdx.x; s < S; s += gridDim.x) {
-    const int8_t* srow = spins + s * N;
-    __syncthreads();                           // previous sample done with the list
-    if (wv == 0) {
-      // with a parent bond b1 (s is the exchange neighbour s0^{b1} of a
-      // two-hop sum): the unordered-pair list of the second hops (b1 itself
-      // excluded, bonds disjoint from b1 only above it, counted twice: flag 0x4000)
-      const int b1 = PAIRS ? (int)parent[s] : -1;
-      const int i1 = b1 >= 0 ? bonds[2 * b1] : -1, j1 = b1 >= 0 ? bonds[2 * b1 + 1] : -1;
-      int n = 0;
-      for (int base = 0; base < NB; base += 64) {
-        const int b = base + lane;
-        bool anti = false, twice = false;
-        int sp = 0;
-        if (b < NB) {
-          const int bi = bonds[2 * b], bj = bonds[2 * b + 1];
-          sp = srow[bi];
-          anti = sp != srow[bj];
-          if (anti && b1 >= 0) {
-            const bool shared = bi == i1 || bi == j1 || bj == i1 || bj == j1;
-            anti = b != b1 && (shared || b > b1);
-            twice = !shared;
+  const int64_t n_items = S * nblk * nsplit;
+  int64_t item = (int64_t)blockIdx.x * per + wv;
+  bool act = wv < per && item < n_items;
+
+  // state of the wavefront's item, carried from walk to walk
+  int64_t s = 0;
+  int blk = 0, share = 0, e0 = 0, e1 = 0;      // list entries [e0, e1) of this and later walks
+  bool first = true;                           // first walk of the item
+  float ch_g = 0.f;
+  double m_item = -INFINITY, Qr = 0.0, Qi = 0.0, denr = 0.0, deni = 0.0;
+  typename T::BFrag bx[BITS ? 1 : NK];
+  XBits<N, PREC> xb;
+
+  for (;;) {
+    if (lane == 0) busy[wv] = act;
+    __syncthreads();                           // also: the walk's first chunk is staged
+    if (__ballot(lane < kWideWaves && busy[lane & (kWideWaves - 1)] != 0) == 0ull) break;
+    // a walk over the hidden units: bonds e0 + q + 4 jb of the list
+    uint32_t offs[kOW];                        // row offset in bytes | twice << 1 | (s = -1)
+    int nv = 0, nvu = 0;                       // slots in use in the lane, and in lane group 0
+    int head = 0;                              // slots of the list's first kHead entries
+    if (act) {
+      if (first) {
+        const int64_t cb = nsplit > 1 ? item / nsplit : item;
+        share = (int)(item - cb * nsplit);
+        s = cb / nblk;
+        blk = (int)(cb - s * nblk);
+        const int8_t* srow = spins + s * N;
+        // with a parent bond b1 (s is the exchange neighbour s0^{b1} of a
+        // two-hop sum): the unordered-pair list of the second hops (b1 itself
+        // excluded, bonds disjoint from b1 only above it, counted twice: flag 0x4000)
+        const int b1 = PAIRS ? (int)parent[s] : -1;
+        const int i1 = b1 >= 0 ? bonds[2 * b1] : -1, j1 = b1 >= 0 ? bonds[2 * b1 + 1] : -1;
+        int n = 0;
+        for (int base = 0; base < NB; base += 64) {
+          const int b = base + lane;
+          bool anti = false, twice = false;
+          int sp = 0;
+          if (b < NB) {
+            const int bi = bonds[2 * b], bj = bonds[2 * b + 1];
+            sp = srow[bi];
+            anti = sp != srow[bj];
+            if (anti && b1 >= 0) {
+              const bool shared = bi == i1 || bi == j1 || bj == i1 || bj == j1;
+              anti = b != b1 && (shared || b > b1);
+              twice = !shared;
+            }
+          }
+          const unsigned long long msk = __ballot(anti);
+          const int pos = __popcll(msk & ((1ull << lane) - 1ull));
+          if (anti) list[n + pos] = (uint16_t)(b | (sp > 0 ? 0x8000 : 0) | (twice ? 0x4000 : 0));
+          n += __popcll(msk);
+        }
+        wave_sync_lds();
+        const int len = ((n + nsplit - 1) / nsplit + 7) & ~7;
+        e0 = min(n, share * len);
+        e1 = min(n, e0 + len);
+        const uint8_t* prow = perm + (size_t)(blk * 16 + c) * N;
+        if constexpr (BITS) xb.load(srow, prow, q);
+        else load_bfrag_gather<N, PREC>(srow, prow, q, bx);
+        ch_g = (float)chi[blk * 16 + c];
+        m_item = -INFINITY;
+        Qr = Qi = denr = deni = 0.0;
+      }
+      const int g = blk * 16 + c;
+      // more RBMs than the record holds: the first kHead entries take a walk of their own
+      const int lim = K > kRecK && e0 < kHead ? min(kWB, (kHead - e0) / 4) : kWB;
+      nv = e1 > e0 + q ? min(lim, (e1 - e0 - q + 3) / 4) : 0;
+      nvu = __builtin_amdgcn_readfirstlane(nv);
+      head = K == 1 || !first || K > kRecK ? kWB : max(0, min(kWB, (kHead - e0) / 4));
+#pragma unroll
+      for (int jb = 0; jb < kWB; ++jb) {
+        const int ii = e0 + q + 4 * jb;
+        const int e = jb < nv ? list[ii] : 0;    // padding entries use bond 0
+        const uint32_t v = (uint32_t)wmap[(size_t)g * NB + (e & 0x3fff)];   // 2 * floats + flip
+        const uint32_t o = 2u * (v & ~1u) | ((v ^ (uint32_t)(e >> 15)) & 1u) |
+                           (PAIRS ? (uint32_t)(e >> 13) & 2u : 0u);
+        if constexpr (!PACK) offs[jb] = o;
+        else if (jb & 1) offs[jb / 2] |= o << 16;
+        else offs[jb / 2] = o;
+      }
+      e0 += 4 * lim;
+    } else {
+#pragma unroll
+      for (int i = 0; i < kOW; ++i) offs[i] = 0u;
+    }
+
+    float Pr[kWB], Pi[kWB];
+    float lpr = 1.f, lpi = 0.f;
+    int lpe = 0;
+    uint32_t lpar = 0u;
+    double sax = 0.0;
+    int k = 0, cin = 0;                        // RBM, chunk within it
+    for (int ch = 0; ch < NCH; ++ch) {
+      const bool last = ch + 1 == NCH;
+      const uint32_t base = lds0 | buf;
+      // keep the comparisons with these in the loop: hoisted, they fill registers
+      nvu = __builtin_amdgcn_readfirstlane(nvu);
+      head = __builtin_amdgcn_readfirstlane(head);
+      asm volatile("" : "+s"(nvu), "+v"(nv), "+s"(head));
+      if (act) {
+        if (cin == 0) {                        // RBM start: products begin at F_s
+#pragma unroll
+          for (int jb = 0; jb < kWB; ++jb) {
+            const uint32_t o = PACK ? (jb & 1 ? offs[jb / 2] >> 16 : offs[jb / 2]) : offs[jb];
+            const f32x2 f = *(lds_f32x2_ptr)(((o & 0xfff0u) | base) + 8u * kHC + 8u * (o & 1u));
+            Pr[jb] = f.x;
+            Pi[jb] = f.y;
           }
         }
-        const unsigned long long msk = __ballot(anti);
-        const int pos = __popcll(msk & ((1ull << lane) - 1ull));
-        if (anti) list[n + pos] = (uint16_t)(b | (sp > 0 ? 0x8000 : 0) | (twice ? 0x4000 : 0));
-        n += __popcll(msk);
+        // theta of the chunk's hidden tile, epilogue, tanh to LDS
+        const int h0 = 8 * ch + 2 * q;
+        typename T::Acc acc = *reinterpret_cast<const f32x4*>(bias + 2 * h0);   // start from the biases
+        if constexpr (BITS) {
+#pragma unroll
+          for (int i = 0; i < XBits<N, PREC>::NW; ++i) asm volatile("" : "+v"(xb.w[i]));
+        }
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+          typename T::BFrag x;
+          if constexpr (BITS) x = xb.frag(kk);
+          else x = bx[kk];
+          acc = mfma(wfrag[((size_t)ch * NK + kk) * 64 + lane], x, acc);
+        }
+        float axs = 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          float tr, ti;
+          axs += logcosh_step<float, true>(acc[2 * u], acc[2 * u + 1], lpr, lpi, lpar, tr, ti);
+          tx[c * kXS + 2 * (2 * q + u)] = tr;
+          tx[c * kXS + 2 * (2 * q + u) + 1] = ti;
+        }
+        sax += (double)axs;
+        renorm(lpr, lpi, lpe);
+        wave_sync_lds();
       }
-      if (lane == 0) nc_s = n;
-    }
-    __syncthreads();
-    const int nc = nc_s;
-    const int npass = nc > 0 ? (nc + 4 * kWB - 1) / (4 * kWB) : 1;
-
-    for (int rd = 0; rd < rounds; ++rd) {
-      const int blk = rd * kWideWaves + wv;
-      const bool active = blk < nblk;
-      const int g = (active ? blk : 0) * 16 + c;
-      const uint8_t* prow = perm + (size_t)g * N;
-      typename T::BFrag bx[NK];
-      load_bfrag_gather<N, PREC>(srow, prow, q, bx);
-      const float ch_g = (float)chi[g];
-      double m_item = -INFINITY, Qr = 0.0, Qi = 0.0, denr = 0.0, deni = 0.0;
-
-      for (int pass = 0; pass < npass; ++pass) {
-        // this lane's bonds: list entries pass * 4 kWB + q + 4 jb
-        int offs[kWB];                  // 2 * (row offset in floats) + (sign < 0)
-        uint32_t twice = 0u;                   // bit jb: an unordered pair counted twice
-        const int i0 = pass * 4 * kWB + q;
-        const int nv = nc > i0 ? min(kWB, (nc - i0 + 3) / 4) : 0;
-        // bonds per lane of lane group 0 (the most of any group): a partly
-        // filled pass skips the empty pairs of slots
-        const int p0 = pass * 4 * kWB;
-        const int nvu = __builtin_amdgcn_readfirstlane(
-            nc > p0 ? min(kWB, (nc - p0 + 3) / 4) : 0);
+      f32x4 t[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = *reinterpret_cast<const f32x4*>(&tx[c * kXS + 4 * e]);
+      // lands during the bond products
+      stage_load(last ? 0 : ch + 1, last ? 0 : cin + 1 == CPR ? k + 1 : k);
+#pragma unroll
+      for (int jb = 0; jb < kWB; jb += 2) {
+        if (jb < nvu) {
+          uint32_t o0, o1;
+          if constexpr (PACK) {
+            asm volatile("" : "+v"(offs[jb / 2]));
+            o0 = offs[jb / 2];
+            o1 = o0 >> 16;
+          } else {
+            asm volatile("" : "+v"(offs[jb]), "+v"(offs[jb + 1]));
+            o0 = offs[jb];
+            o1 = offs[jb + 1];
+          }
+          const lds_f32x4_ptr r0 = (lds_f32x4_ptr)((PACK ? o0 & 0xfff0u : o0 & ~15u) | base);
+          const lds_f32x4_ptr r1 = (lds_f32x4_ptr)((o1 & ~15u) | base);
+          const float sg0 = __uint_as_float((o0 << 31) | 0x3f800000u);
+          const float sg1 = __uint_as_float((o1 << 31) | 0x3f800000u);
+          float ar = Pr[jb], ai = Pi[jb], br = Pr[jb + 1], bi = Pi[jb + 1];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const f32x4 x0 = r0[e];
+            const f32x4 x1 = r1[e];
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+              const float tr = t[e][2 * hh], ti = t[e][2 * hh + 1];
+              float pa = fmaf(tr, x0[2 * hh], fmaf(-ti, x0[2 * hh + 1], sg0));
+              float pb = fmaf(tr, x0[2 * hh + 1], ti * x0[2 * hh]);
+              float nr = fmaf(ar, pa, -(ai * pb));
+              ai = fmaf(ar, pb, ai * pa);
+              ar = nr;
+              pa = fmaf(tr, x1[2 * hh], fmaf(-ti, x1[2 * hh + 1], sg1));
+              pb = fmaf(tr, x1[2 * hh + 1], ti * x1[2 * hh]);
+              nr = fmaf(br, pa, -(bi * pb));
+              bi = fmaf(br, pb, bi * pa);
+              br = nr;
+            }
+          }
+          Pr[jb] = ar; Pi[jb] = ai; Pr[jb + 1] = br; Pi[jb + 1] = bi;
+        }
+      }
+      if (act && cin + 1 == CPR) {             // RBM k complete: weight and sum
+        apply_parity(lpr, lpi, lpar);
+        int E = lpe;
+        float pr = lpr, pi = lpi;
+        double sx = sax;
+#pragma unroll
+        for (int o = 16; o <= 32; o <<= 1) {
+          const float orr = __shfl_xor(pr, o, 64), oi = __shfl_xor(pi, o, 64);
+          const float nr = pr * orr - pi * oi;
+          pi = pr * oi + pi * orr;
+          pr = nr;
+          E += __shfl_xor(E, o, 64);
+          sx += __shfl_xor(sx, o, 64);
+        }
+        double axr = 0.0, axi = 0.0;
+        const float* ak = avec + (size_t)k * N * 2;
+        const int8_t* srow = spins + s * N;
+        const uint8_t* prow = perm + (size_t)(blk * 16 + c) * N;
+        for (int jj = q; jj < N; jj += 4) {
+          const double xj = 0.5 * (double)srow[prow[jj]];
+          axr += xj * (double)ak[2 * jj];
+          axi += xj * (double)ak[2 * jj + 1];
+        }
+        axr += __shfl_xor(axr, 16, 64);
+        axi += __shfl_xor(axi, 16, 64);
+        axr += __shfl_xor(axr, 32, 64);
+        axi += __shfl_xor(axi, 32, 64);
+        const double Er = axr + sx + (double)E * 0.69314718055994530942;
+        const double mk = wave_max(Er);
+        if (mk > m_item) {
+          const double sc = (double)exp_t((float)(m_item - mk));   // 0 at the first RBM
+          Qr *= sc; Qi *= sc; denr *= sc; deni *= sc;
+          m_item = mk;
+        }
+        const float e = ch_g * exp_t((float)(Er - m_item));
+        float sn, cs;
+        sincos_t((float)axi, &sn, &cs);
+        const float ur = e * (pr * cs - pi * sn), ui = e * (pr * sn + pi * cs);
+        double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
 #pragma unroll
         for (int jb = 0; jb < kWB; ++jb) {
-          const int ii = i0 + 4 * jb;
-          const int e = ii < nc ? list[ii] : 0;   // padding entries use bond 0
-          offs[jb] = wmap[(size_t)g * NB + (e & 0x3fff)] ^ (e >> 15);
-          if (PAIRS && (e & 0x4000)) twice |= 1u << jb;
+          if (jb < nvu) {
+            double wj = 1.0;
+            if constexpr (PAIRS) {
+              const uint32_t o = PACK ? (jb & 1 ? offs[jb / 2] >> 16 : offs[jb / 2]) : offs[jb];
+              wj = o & 2u ? 2.0 : 1.0;
+            }
+            const double vr = jb < nv ? wj * (double)Pr[jb] : 0.0;
+            const double vi = jb < nv ? wj * (double)Pi[jb] : 0.0;
+            if (jb < head) {
+              sr += vr;
+              si += vi;
+            } else {
+              dr += vr;
+              di += vi;
+            }
+          }
         }
-        float Pr[kWB], Pi[kWB];
-        float lpr = 1.f, lpi = 0.f;
-        int lpe = 0;
-        uint32_t lpar = 0u;
-        double sax = 0.0;
+        Qr += (double)ur * sr - (double)ui * si;
+        Qi += (double)ur * si + (double)ui * sr;
+        if (first && q == 0) {
+          denr += (double)ur;
+          deni += (double)ui;
+        }
+        if (first && K <= kRecK) {
+          WideRec& o = rec[k];
+          o.Er[c] = Er;                        // equal in the four lanes of an image
+          o.axi[c] = axi;
+          o.pr[lane] = pr;
+          o.pi[lane] = pi;
+          o.dr[lane] = dr;
+          o.di[lane] = di;
+        }
+        lpr = 1.f; lpi = 0.f; lpe = 0; lpar = 0u; sax = 0.0;
+      }
+      if (++cin == CPR) {
+        cin = 0;
+        ++k;
+      }
+      buf ^= Cfg::BUF;
+      stage_store(buf);
+      __syncthreads();
+    }
 
-        for (int ch = 0; ch < NCH; ++ch, ++gc) {
-          const int k = ch / CPR;
-          const int buf = gc & 1;
-          const int nxt = ch + 1 < NCH ? ch + 1 : 0;
-          if (ch % CPR == 0) {                 // RBM start: products begin at F_s
-#pragma unroll
-            for (int jb = 0; jb < kWB; ++jb) {
-              const float* f = Tc[buf] + (offs[jb] >> 1) + 2 * kHC + 2 * (offs[jb] & 1);
-              Pr[jb] = f[0];
-              Pi[jb] = f[1];
-            }
-          }
-          // theta of the chunk's hidden tiles, epilogue, tanh to LDS
-#pragma unroll
-          for (int tt = 0; tt < kHC / 8; ++tt) {
-            const int ht = (kHC / 8) * ch + tt;
-            const int h0 = 8 * ht + 2 * q;
-            typename T::Acc acc;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] = bias[2 * h0 + v];   // start from the biases
-#pragma unroll
-            for (int kk = 0; kk < NK; ++kk) acc = mfma(wfrag[((size_t)ht * NK + kk) * 64 + lane], bx[kk], acc);
-            float axs = 0.f;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-              float tr, ti;
-              axs += logcosh_step<float, true>(acc[2 * u], acc[2 * u + 1], lpr, lpi, lpar, tr, ti);
-              const int hl = 8 * tt + 2 * q + u;
-              tx[wv][c * kXS + 2 * hl] = tr;
-              tx[wv][c * kXS + 2 * hl + 1] = ti;
-            }
-            sax += (double)axs;
-          }
-          renorm(lpr, lpi, lpe);
-          wave_sync_lds();
-          float t[2 * kHC];
-#pragma unroll
-          for (int e = 0; e < kHC / 2; ++e) {
-            const float4 v = *reinterpret_cast<const float4*>(&tx[wv][c * kXS + 4 * e]);
-            t[4 * e] = v.x; t[4 * e + 1] = v.y; t[4 * e + 2] = v.z; t[4 * e + 3] = v.w;
-          }
-          NQS_STAGE_LOAD(nxt)                  // lands during the bond products
-          // bond products of the chunk, two bonds at a time
-#pragma unroll
-          for (int jb = 0; jb < kWB; jb += 2) {
-            if (jb < nvu) {
-            const float* r0 = Tc[buf] + (offs[jb] >> 1);
-            const float* r1 = Tc[buf] + (offs[jb + 1] >> 1);
-            const float sg0 = (offs[jb] & 1) ? -1.f : 1.f, sg1 = (offs[jb + 1] & 1) ? -1.f : 1.f;
-            float ar = Pr[jb], ai = Pi[jb], br = Pr[jb + 1], bi = Pi[jb + 1];
-#pragma unroll
-            for (int e = 0; e < kHC / 2; ++e) {
-              const float4 x0 = *reinterpret_cast<const float4*>(r0 + 4 * e);
-              const float4 x1 = *reinterpret_cast<const float4*>(r1 + 4 * e);
-#pragma unroll
-              for (int hh = 0; hh < 2; ++hh) {
-                const float tr = t[4 * e + 2 * hh], ti = t[4 * e + 2 * hh + 1];
-                const float T0r = hh ? x0.z : x0.x, T0i = hh ? x0.w : x0.y;
-                const float T1r = hh ? x1.z : x1.x, T1i = hh ? x1.w : x1.y;
-                float pa = fmaf(tr, T0r, fmaf(-ti, T0i, sg0)), pb = fmaf(tr, T0i, ti * T0r);
-                float nr = fmaf(ar, pa, -(ai * pb));
-                ai = fmaf(ar, pb, ai * pa);
-                ar = nr;
-                pa = fmaf(tr, T1r, fmaf(-ti, T1i, sg1));
-                pb = fmaf(tr, T1i, ti * T1r);
-                nr = fmaf(br, pa, -(bi * pb));
-                bi = fmaf(br, pb, bi * pa);
-                br = nr;
-              }
-            }
-            Pr[jb] = ar; Pi[jb] = ai; Pr[jb + 1] = br; Pi[jb + 1] = bi;
-            }
-          }
-          if (ch % CPR == CPR - 1) {           // RBM k complete: weight and sum
-            apply_parity(lpr, lpi, lpar);
-            int E = lpe;
-            float pr = lpr, pi = lpi;
-            double sx = sax;
-#pragma unroll
-            for (int o = 16; o <= 32; o <<= 1) {
-              const float orr = __shfl_xor(pr, o, 64), oi = __shfl_xor(pi, o, 64);
-              const float nr = pr * orr - pi * oi;
-              pi = pr * oi + pi * orr;
-              pr = nr;
-              E += __shfl_xor(E, o, 64);
-              sx += __shfl_xor(sx, o, 64);
-            }
-            double axr = 0.0, axi = 0.0;
-            const float* ak = avec + (size_t)k * N * 2;
-            for (int jj = q; jj < N; jj += 4) {
-              const double xj = 0.5 * (double)srow[prow[jj]];
-              axr += xj * (double)ak[2 * jj];
-              axi += xj * (double)ak[2 * jj + 1];
-            }
-            axr += __shfl_xor(axr, 16, 64);
-            axi += __shfl_xor(axi, 16, 64);
-            axr += __shfl_xor(axr, 32, 64);
-            axi += __shfl_xor(axi, 32, 64);
-            const double Er = axr + sx + (double)E * 0.69314718055994530942;
-            if (WL && pass == 0 && q == 0) {
-              // the image's log amplitude L_kg = log(prod_h 2 cosh theta) + a x,
-              // unreduced: (Er, a x imaginary part, the joined product P) with
-              // L = Er + log|P| + i (Im a x + arg P), for a gradient pass on the
-              // same configurations (the log and arg are taken there)
-              double* o = &lraw[wv][(k * 16 + c) * 4];
-              o[0] = Er;
-              o[1] = axi;
-              o[2] = (double)pr;
-              o[3] = (double)pi;
-            }
-            const double mk = wave_max(Er);
-            if (mk > m_item) {
-              const double sc = (double)exp_t((float)(m_item - mk));   // 0 at the first RBM
-              Qr *= sc; Qi *= sc; denr *= sc; deni *= sc;
-              m_item = mk;
-            }
-            const float e = ch_g * exp_t((float)(Er - m_item));
-            float sn, cs;
-            sincos_t((float)axi, &sn, &cs);
-            const float ur = e * (pr * cs - pi * sn), ui = e * (pr * sn + pi * cs);
-            double sr = 0.0, si = 0.0;
-#pragma unroll
-            for (int jb = 0; jb < kWB; ++jb) {
-              if constexpr (PAIRS) {
-                const double wj = ((twice >> jb) & 1u) ? 2.0 : 1.0;
-                sr += jb < nv ? wj * (double)Pr[jb] : 0.0;
-                si += jb < nv ? wj * (double)Pi[jb] : 0.0;
-              } else {
-                sr += jb < nv ? (double)Pr[jb] : 0.0;
-                si += jb < nv ? (double)Pi[jb] : 0.0;
-              }
-            }
-            Qr += (double)ur * sr - (double)ui * si;
-            Qi += (double)ur * si + (double)ui * sr;
-            if (pass == 0 && q == 0) {
-              denr += (double)ur;
-              deni += (double)ui;
-            }
-            lpr = 1.f; lpi = 0.f; lpe = 0; lpar = 0u; sax = 0.0;
-          }
-          NQS_STAGE_STORE(gc & 1 ? 0 : 1)
-          __syncthreads();
+    if (act) {
+      if (first && K > 1 && K <= kRecK) {
+        // the later entries' sums, weighted with the final m
+        wave_sync_lds();
+        for (int kk = 0; kk < K; ++kk) {
+          const WideRec& o = rec[kk];
+          const float pr = o.pr[lane], pi = o.pi[lane];
+          const float e = ch_g * exp_t((float)(o.Er[c] - m_item));
+          float sn, cs;
+          sincos_t((float)o.axi[c], &sn, &cs);
+          const float ur = e * (pr * cs - pi * sn), ui = e * (pr * sn + pi * cs);
+          Qr += (double)ur * o.dr[lane] - (double)ui * o.di[lane];
+          Qi += (double)ur * o.di[lane] + (double)ui * o.dr[lane];
         }
       }
-      Qr = wave_sum(Qr);
-      Qi = wave_sum(Qi);
-      denr = wave_sum(denr);
-      deni = wave_sum(deni);
-      if (WL && active) {
-        // the round's log amplitudes to [S][K][G][4]: 16 images x 4 reals per RBM
+      if (first && Lout != nullptr && share == 0) {
+        // the images' log amplitudes L = Er + log|P| + i (Im a x + arg P) to
+        // [S][K][G][4], unreduced, for a gradient pass on the same
+        // configurations (the log and arg are taken there)
+        wave_sync_lds();
         for (int e = lane; e < K * 64; e += 64) {
           const int kk = e >> 6, ci = (e >> 2) & 15, j = e & 3;
-          Lout[(((size_t)s * K + kk) * G + blk * 16 + ci) * 4 + j] = lraw[wv][e];
+          const WideRec& o = rec[kk];
+          Lout[(((size_t)s * K + kk) * G + blk * 16 + ci) * 4 + j] =
+              j == 0 ? o.Er[ci] : j == 1 ? o.axi[ci] : (double)(j == 2 ? o.pr[ci] : o.pi[ci]);
         }
       }
-      if (active && lane == 0) {
-        double* o = part + ((size_t)s * nblk + blk) * 6;
-        o[0] = m_item;
-        o[1] = denr;
-        o[2] = deni;
-        o[3] = Qr;
-        o[4] = Qi;
-        o[5] = 0.0;
+      first = false;
+      if (e0 >= e1) {                          // the item's last walk
+        Qr = wave_sum(Qr);
+        Qi = wave_sum(Qi);
+        denr = wave_sum(share == 0 ? denr : 0.0);
+        deni = wave_sum(share == 0 ? deni : 0.0);
+        if (lane == 0) {
+          double* o = part + item * 6;
+          o[0] = m_item;
+          o[1] = denr;
+          o[2] = deni;
+          o[3] = Qr;
+          o[4] = Qi;
+          o[5] = 0.0;
+        }
+        item += (int64_t)gridDim.x * per;
+        act = item < n_items;
+        first = true;
       }
     }
   }
 }
 
-#undef NQS_STG_LD
-#undef NQS_STG_ST
-#undef NQS_STAGE_LOAD
-#undef NQS_STAGE_STORE
-
 template <int N, int PREC>
 hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, hipStream_t st,
                const int16_t* parent, double* Lout) {
-#define NQS_WIDE_ARGS                                                                     \
-  spins, S, c->dev.perm, c->G, c->K, c->M, wf, (const float*)c->par.bias,                 \
-      (const float*)c->par.avec, c->dev.bonds, c->dev.wmap, c->dev.wrow, c->dev.chi,      \
-      (const float*)c->par.Tpm, (const float*)c->par.F, part
-  const int64_t blocks = std::min<int64_t>(S, c->n_cu > 0 ? c->n_cu : 256);
+  const int nsplit = parent ? 1 : wide_nsplit(c, S);
+  const int64_t n_cu = c->n_cu > 0 ? c->n_cu : 256, items = S * (c->G / 16) * nsplit;
+  // fewer items than wavefront slots: the same number in every workgroup
+  const int per = (int)std::min<int64_t>(kWideWaves, (items + n_cu - 1) / n_cu);
+  const int64_t blocks = std::min<int64_t>((items + per - 1) / per, n_cu);
   const auto* wf = (const typename ThetaTraits<PREC>::AFrag*)(PREC == kPrecF32X3 ? c->par.wfrag3
                                                                                  : c->par.wfrag);
+#define NQS_WIDE_ARGS                                                                     \
+  spins, S, nsplit, per, c->dev.perm, c->K, c->M, wf, (const float*)c->par.bias,          \
+      (const float*)c->par.avec, c->dev.bonds, c->dev.wmap, c->dev.wrow, c->dev.chi,      \
+      (const float*)c->par.Tpm, (const float*)c->par.F, part
   if (parent)
-    eloc_wide_kernel<N, PREC, true, false><<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
+    eloc_wide_kernel<N, PREC, true><<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
         NQS_WIDE_ARGS, parent, nullptr);
-  else if (Lout)
-    eloc_wide_kernel<N, PREC, false, true><<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
-        NQS_WIDE_ARGS, nullptr, Lout);
   else
-    eloc_wide_kernel<N, PREC, false, false><<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
-        NQS_WIDE_ARGS, nullptr, nullptr);
+    eloc_wide_kernel<N, PREC, false><<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
+        NQS_WIDE_ARGS, nullptr, Lout);
 #undef NQS_WIDE_ARGS
   return hipGetLastError();
 }
@@ -391,6 +517,16 @@ hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, h
 bool eloc_wide_supported(const nqs_ctx* c) {
   if (c->prec == NQS_FP64 || c->KM <= 128 || c->M % kHC != 0) return false;
   return c->N == 36 || c->N == 64 || c->N == 100;
+}
+
+// Shares of the bond list per (configuration, column block): as many as leave
+// each wavefront slot of the device at most one item, at most eight (every
+// share evaluates theta again).
+int wide_nsplit(const nqs_ctx* c, int64_t S) {
+  if (c->K > kRecK) return 1;
+  const int64_t items = std::max<int64_t>(S, 1) * (c->G / 16);
+  return (int)std::max<int64_t>(
+      1, std::min<int64_t>(8, (int64_t)fused_max_split_items(c) / items));
 }
 
 namespace {

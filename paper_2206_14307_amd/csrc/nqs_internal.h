@@ -170,6 +170,9 @@ bool eloc_wide_supported(const nqs_ctx* c);
 // reals each, see launch_lse), for a gradient pass on the same configurations
 hipError_t launch_eloc_wide(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
                             hipStream_t st, double* Lout = nullptr);
+// shares of the bond list per (configuration, column block) in a launch of S configurations
+int wide_nsplit(const nqs_ctx* c, int64_t S);
+// combines the partials of launch_eloc_wide
 hipError_t launch_fused_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                const double* part, double* logpsi, double* eloc, int eloc_stride,
                                hipStream_t st);
