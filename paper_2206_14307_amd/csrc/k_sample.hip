@@ -59,12 +59,6 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t
 // from the spins every segment)
 __device__ __forceinline__ float rcp_fast(float v) { return __builtin_amdgcn_rcpf(v); }
 
-// reciprocal of the squared modulus in the cache update: hardware rcp in
-// FP32 (the cache is rebuilt from the spins every segment), a division in
-// FP64
-__device__ __forceinline__ float recip_t(float v) { return rcp_fast(v); }
-__device__ __forceinline__ double recip_t(double v) { return 1.0 / v; }
-
 // one cache or row tile of 8 complex values, moved in 16-byte pieces (the
 // tiles are 64-byte aligned)
 template <typename R>
@@ -107,19 +101,22 @@ __device__ __forceinline__ int select128(uint64_t lo, uint64_t hi, int k) {
   return k < c ? select64(lo, k) : 64 + select64(hi, k - c);
 }
 
-template <typename R>
+// FP64 (small lattices, caches in L2): one proposal in a pass.  It is bound by
+// the update's divisions and not by the caches' traffic: the passes of several
+// proposals below gained 3 % at 4x4 M = 16 at an acceptance near 1 and took
+// 1.6 times as long at 0.3.
 __global__ __launch_bounds__(1024) void sample_kernel(
     int N, int G, int K, int M, int n_htiles, const uint8_t* __restrict__ perminv,
-    const R* __restrict__ Tpair, const R* __restrict__ Fpair, R* __restrict__ t, R* __restrict__ t2,
-    R* __restrict__ w, uint64_t* __restrict__ state, int n_prop, int phase, int64_t p0,
+    const double* __restrict__ Tpair, const double* __restrict__ Fpair, double* __restrict__ t,
+    double* __restrict__ t2, double* __restrict__ w, uint64_t* __restrict__ state, int n_prop, int phase, int64_t p0,
     const int32_t* nskip_dev,
     int n_skip_host, uint64_t seed, int8_t* __restrict__ spins_out, int64_t n_per_chain,
     int64_t* __restrict__ acc_out, int8_t* __restrict__ cur_spins) {
   extern __shared__ __align__(16) unsigned char smem[];
-  R* Rg = reinterpret_cast<R*>(smem);                                  // [G][K] complex
+  double* Rg = reinterpret_cast<double*>(smem);                        // [G][K] complex
   // per-wave ratio sums [2][32], double-buffered by proposal parity (see the
   // register kernel): one barrier per proposal
-  double* red = reinterpret_cast<double*>(smem + (size_t)G * K * 2 * sizeof(R));
+  double* red = reinterpret_cast<double*>(smem + (size_t)G * K * 2 * sizeof(double));
   const int64_t c = blockIdx.x;
   const int g = threadIdx.x, lane = g & 63, wv = g >> 6, nw = (blockDim.x + 63) >> 6;
   const bool active = g < G;
@@ -136,9 +133,9 @@ __global__ __launch_bounds__(1024) void sample_kernel(
   // ratio pass also writes the tanh-addition update of every entry to tn, and
   // an accepted proposal swaps the two (the acceptance rate is close to 1, so
   // this reads the cache once per proposal instead of twice)
-  R* tc = t + (size_t)c * n_htiles * G * 16;
-  R* tn = t2 + (size_t)c * n_htiles * G * 16;
-  R* wc = w + (size_t)c * K * G * 2;
+  double* tc = t + (size_t)c * n_htiles * G * 16;
+  double* tn = t2 + (size_t)c * n_htiles * G * 16;
+  double* wc = w + (size_t)c * K * G * 2;
   int64_t acc = 0;
   for (int r = 0; r < n_prop && valid; ++r) {
     uint64_t rnd[4];
@@ -152,71 +149,47 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     if (active) {
       l1 = perminv[(size_t)g * N + i];
       l2 = perminv[(size_t)g * N + j];
-      const R* Trow = Tpair + ((size_t)l1 * N + l2) * KM * 2;
+      const double* Trow = Tpair + ((size_t)l1 * N + l2) * KM * 2;
       for (int k = 0; k < K; ++k) {
-        R pr = 1, pi = 0;
+        double pr = 1, pi = 0;
         // tiles of 8 units: this image's 16 cache values (one contiguous
-        // piece of the [tile][G][16] layout) and 16 row values, each tile's
-        // loads issued one tile ahead of its use, its updates stored whole
+        // piece of the [tile][G][16] layout) and 16 row values
         const int nt = M / 8;
-        const R* tp = tc + ((size_t)(k * nt) * G + g) * 16;
-        R* up = tn + ((size_t)(k * nt) * G + g) * 16;
-        const R* Tq = Trow + (size_t)2 * k * M;
+        const double* tp = tc + ((size_t)(k * nt) * G + g) * 16;
+        double* up = tn + ((size_t)(k * nt) * G + g) * 16;
+        const double* Tq = Trow + (size_t)2 * k * M;
         // the 8 factors of a tile into the product, the updated tile stored
-        auto tile = [&](R (&tt)[16], const R (&TT)[16], R* dst) {
+        auto tile = [&](double (&tt)[16], const double (&TT)[16], double* dst) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const R tr = tt[2 * e], ti = tt[2 * e + 1];
-            const R Tr = TT[2 * e], Ti = TT[2 * e + 1];
-            const R a = fmaf_t(tr, Tr, fmaf_t(-ti, Ti, R(-1)));   // a + ib = t T - 1
-            const R b = fmaf_t(tr, Ti, ti * Tr);
-            const R nr = fmaf_t(pr, a, -(pi * b));
+            const double tr = tt[2 * e], ti = tt[2 * e + 1];
+            const double Tr = TT[2 * e], Ti = TT[2 * e + 1];
+            const double a = fmaf_t(tr, Tr, fmaf_t(-ti, Ti, -1.0));   // a + ib = t T - 1
+            const double b = fmaf_t(tr, Ti, ti * Tr);
+            const double nr = fmaf_t(pr, a, -(pi * b));
             pi = fmaf_t(pr, b, pi * a);
             pr = nr;
             // t' = (t - T) / (1 - t T) = (T - t) / (a + ib)
-            const R dr = Tr - tr, di = Ti - ti;
-            const R inv = recip_t(fmaf_t(a, a, b * b));
+            const double dr = Tr - tr, di = Ti - ti;
+            const double inv = 1.0 / fmaf_t(a, a, b * b);
             tt[2 * e] = (dr * a + di * b) * inv;
             tt[2 * e + 1] = (di * a - dr * b) * inv;
           }
           store_tile(dst, tt);
         };
-        // FP32: two register buffers, the next tile always in flight (FP64,
-        // for small lattices only, keeps one: its tiles would not fit twice
-        // in the 128 VGPRs of a 1024-lane workgroup)
-        R t0[16], T0[16], t1[16], T1[16];
-        if constexpr (sizeof(R) == 8) {
-          for (int ht = 0; ht < nt; ++ht) {
-            load_tile(t0, tp + (size_t)ht * G * 16);
-            load_tile(T0, Tq + 16 * ht);
-            tile(t0, T0, up + (size_t)ht * G * 16);
-          }
-        } else {
-          // the loop body is free of conditions (the last prefetch reads the
-          // last tile again): a conditional load is sunk to its use, and a
-          // conditional path makes the wait before a tile cover the next
-          // one's loads too
-          load_tile(t0, tp);
-          load_tile(T0, Tq);
-          int ht = 0;
-          for (; ht + 1 < nt; ht += 2) {
-            load_tile(t1, tp + (size_t)(ht + 1) * G * 16);
-            load_tile(T1, Tq + 16 * (ht + 1));
-            tile(t0, T0, up + (size_t)ht * G * 16);
-            const int h2 = min(ht + 2, nt - 1);
-            load_tile(t0, tp + (size_t)h2 * G * 16);
-            load_tile(T0, Tq + 16 * h2);
-            tile(t1, T1, up + (size_t)(ht + 1) * G * 16);
-          }
-          if (ht < nt) tile(t0, T0, up + (size_t)ht * G * 16);   // odd tile count
+        double tt[16], TT[16];
+        for (int ht = 0; ht < nt; ++ht) {
+          load_tile(tt, tp + (size_t)ht * G * 16);
+          load_tile(TT, Tq + 16 * ht);
+          tile(tt, TT, up + (size_t)ht * G * 16);
         }
-        const R* f = Fpair + (((size_t)k * N + l1) * N + l2) * 2;
-        const R rr = f[0] * pr - f[1] * pi, ri = f[0] * pi + f[1] * pr;
+        const double* f = Fpair + (((size_t)k * N + l1) * N + l2) * 2;
+        const double rr = f[0] * pr - f[1] * pi, ri = f[0] * pi + f[1] * pr;
         Rg[2 * (g * K + k)] = rr;
         Rg[2 * (g * K + k) + 1] = ri;
-        const R wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
-        cr += (double)(wr * rr - wi * ri);
-        ci += (double)(wr * ri + wi * rr);
+        const double wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
+        cr += wr * rr - wi * ri;
+        ci += wr * ri + wi * rr;
       }
     }
     cr = wave_sum(cr);
@@ -236,17 +209,17 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     const bool accept = u < sr * sr + si * si;
     if (accept) {
       ++acc;
-      R* const sw = tc;                        // the updated cache becomes current
+      double* const sw = tc;                   // the updated cache becomes current
       tc = tn;
       tn = sw;
       if (active) {
         const double den = sr * sr + si * si;
         for (int k = 0; k < K; ++k) {
-          const R wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
-          const R rr = Rg[2 * (g * K + k)], ri = Rg[2 * (g * K + k) + 1];
-          const double qr = (double)(wr * rr - wi * ri), qi = (double)(wr * ri + wi * rr);
-          wc[2 * (k * G + g)] = (R)((qr * sr + qi * si) / den);
-          wc[2 * (k * G + g) + 1] = (R)((qi * sr - qr * si) / den);
+          const double wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
+          const double rr = Rg[2 * (g * K + k)], ri = Rg[2 * (g * K + k) + 1];
+          const double qr = wr * rr - wi * ri, qi = wr * ri + wi * rr;
+          wc[2 * (k * G + g)] = (qr * sr + qi * si) / den;
+          wc[2 * (k * G + g) + 1] = (qi * sr - qr * si) / den;
         }
       }
       const int b0 = i < 64 ? i : i - 64, b1 = j < 64 ? j : j - 64;
@@ -269,6 +242,315 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     state[4 * c] = lo;
     state[4 * c + 1] = hi;
     state[4 * c + 2] = ctr;
+    acc_out[c] += valid ? acc : -((int64_t)1 << 40);   // marks a chain outside Sz = 0
+  }
+  if (g < N) {
+    const uint64_t bit = g < 64 ? (lo >> g) & 1ull : (hi >> (g - 64)) & 1ull;
+    cur_spins[(size_t)c * N + g] = bit ? 1 : -1;
+  }
+}
+
+// The FP32 cache-streaming kernel walks several proposals in one pass over a chain's
+// cache.  A pass reads every entry once, applies the accepted exchanges that the
+// stored cache does not hold yet (at most kMaxRows - 1, "pending"), and then
+// follows the proposals ahead under the outcome that the chain's acceptance
+// rate makes likely:
+//   accepted: each proposal's ratio is formed from the entry and the entry is
+//     updated by it; the entry after the last one is written to a second cache,
+//     and if all of them were accepted that cache becomes the current one;
+//   rejected: the ratios of the proposals are all formed from the same entry,
+//     and the entry after the pending exchanges (if any) is written.
+// The decisions are then taken in order, each from the weights the one before
+// left, up to the first that differs from the assumed outcome: proposals behind
+// it are drawn again by the next pass, and accepted exchanges that are not in
+// the current cache become pending.  Every ratio and every entry is formed by
+// the operations, in the order, of one proposal at a time.
+constexpr int kMaxRows = 4;        // pending exchanges and proposals in a pass
+
+// One pass over the cache of RBM k of an image: entries tp, rows T[NR] of the
+// site-pair table, products out (prod_h (t T - 1) per row).  The first NU rows
+// update the entry; the entry after NW of them is written to up (0: none).
+template <int NR, int NU, int NW>
+__device__ __forceinline__ void stream_rows(const float* __restrict__ tp, float* __restrict__ up,
+                                            const float* const (&T)[kMaxRows], int nt, size_t step,
+                                            float (&pr)[kMaxRows], float (&pi)[kMaxRows]) {
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    pr[r] = 1;
+    pi[r] = 0;
+  }
+  // the 8 factors of a row's tile into its product, the entries updated
+  auto tile = [&](float (&tt)[16], const float (&TT)[16], int r) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float tr = tt[2 * e], ti = tt[2 * e + 1];
+      const float Tr = TT[2 * e], Ti = TT[2 * e + 1];
+      const float a = fmaf(tr, Tr, fmaf(-ti, Ti, -1.f));   // a + ib = t T - 1
+      const float b = fmaf(tr, Ti, ti * Tr);
+      const float nr = fmaf(pr[r], a, -(pi[r] * b));
+      pi[r] = fmaf(pr[r], b, pi[r] * a);
+      pr[r] = nr;
+      if (r < NU) {
+        // t' = (t - T) / (1 - t T) = (T - t) / (a + ib)
+        const float dr = Tr - tr, di = Ti - ti;
+        const float inv = rcp_fast(fmaf(a, a, b * b));
+        tt[2 * e] = fmaf(dr, a, di * b) * inv;
+        tt[2 * e + 1] = fmaf(di, a, -(dr * b)) * inv;
+      }
+    }
+  };
+  // the next row's tile and the next entries are in flight while a tile is
+  // used.  The loop body is free of conditions (the last prefetch reads
+  // the last tile again): a conditional load is sunk to its use, and a
+  // conditional path makes the wait before a tile cover the next one's loads
+  float t0[16], t1[16], T0[16], T1[16];
+  auto tiles = [&](float (&tt)[16], float (&tn)[16], float (&TA)[16], float (&TB)[16], int ht,
+                   int hn) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      float (&Tc)[16] = (r & 1) ? TB : TA;
+      float (&Tn)[16] = (r & 1) ? TA : TB;
+      if (r + 1 < NR) load_tile(Tn, T[r + 1 < NR ? r + 1 : 0] + 16 * ht);
+      else load_tile(Tn, T[0] + 16 * hn);
+      if (r == 0) load_tile(tn, tp + (size_t)hn * step);
+      tile(tt, Tc, r);
+      if (r + 1 == NW) store_tile(up + (size_t)ht * step, tt);
+    }
+  };
+  load_tile(t0, tp);
+  load_tile(T0, T[0]);
+  int ht = 0;
+  for (; ht + 1 < nt; ht += 2) {
+    const int h2 = min(ht + 2, nt - 1);
+    tiles(t0, t1, T0, T1, ht, ht + 1);
+    if constexpr (NR & 1) tiles(t1, t0, T1, T0, ht + 1, h2);
+    else tiles(t1, t0, T0, T1, ht + 1, h2);
+  }
+  if (ht < nt) tiles(t0, t1, T0, T1, ht, ht);              // odd tile count
+}
+
+// a value that is the same in every lane, or lane l's, as a scalar
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+__device__ __forceinline__ uint64_t lane64(uint64_t v, int l) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+
+__global__ __launch_bounds__(1024) void sample_stream_kernel(
+    int N, int G, int K, int M, int n_htiles, int max_rows, const uint8_t* __restrict__ perminv,
+    const float* __restrict__ Tpair, const float* __restrict__ Fpair, float* __restrict__ t,
+    float* __restrict__ t2, float* __restrict__ w, uint64_t* __restrict__ state, int n_prop, int phase, int64_t p0,
+    const int32_t* nskip_dev,
+    int n_skip_host, uint64_t seed, int8_t* __restrict__ spins_out, int64_t n_per_chain,
+    int64_t* __restrict__ acc_out, int8_t* __restrict__ cur_spins) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  // per-wave ratio sums [2][32], double-buffered by proposal parity (see the
+  // register kernel): one barrier per proposal
+  double* red = reinterpret_cast<double*>(smem);
+  float* Rg = reinterpret_cast<float*>(red + 64);                      // [max_rows][G][K] complex
+  const int64_t c = blockIdx.x;
+  const int g = threadIdx.x, lane = g & 63, wv = g >> 6, nw = (blockDim.x + 63) >> 6;
+  const bool active = g < G;
+  uint64_t lo = uniform64(state[4 * c]), hi = uniform64(state[4 * c + 1]);
+  const uint64_t ctr = uniform64(state[4 * c + 2]), id = uniform64(state[4 * c + 3]);
+  const uint64_t nmask_lo = N >= 64 ? ~0ull : ((1ull << N) - 1ull);
+  const uint64_t nmask_hi = N > 64 ? ((1ull << (N - 64)) - 1ull) : 0ull;
+  const int half = N / 2;
+  const bool valid = (__popcll(lo & nmask_lo) + __popcll(hi & nmask_hi) == half) &&
+                     ((lo & ~nmask_lo) == 0) && ((hi & ~nmask_hi) == 0);
+  const int n_skip = phase == 1 ? (nskip_dev ? *nskip_dev : n_skip_host) : 1;
+  const int KM = K * M, nt = M / 8;
+  float* tc = t + (size_t)c * n_htiles * G * 16;   // tanh(theta), without the pending exchanges
+  float* tn = t2 + (size_t)c * n_htiles * G * 16;
+  float* wc = w + (size_t)c * K * G * 2;
+  int64_t acc = 0;
+  // accepted so far in this phase
+  const int64_t acc0 = p0 > 0 ? (int64_t)uniform64((uint64_t)acc_out[c]) : 0;
+  // Philox depends only on the proposal index: lane l draws the words of
+  // proposal rbase + l
+  uint64_t rnd[4];
+  int rbase = -64;
+  // the exchanges of a pass, pending ones first: sites i (up) and j (down)
+  int ei[kMaxRows], ej[kMaxRows];
+  int np = 0;                                  // pending
+  uint64_t slo = lo, shi = hi;                 // spins under the assumed outcomes
+  auto flip = [](uint64_t& a, uint64_t& b, int i) __attribute__((always_inline)) {
+    a ^= i < 64 ? 1ull << (i & 63) : 0ull;
+    b ^= i < 64 ? 0ull : 1ull << (i & 63);
+  };
+  for (int r = 0; r < n_prop && valid;) {
+    // Proposals of the pass by the acceptance rate a so far (three accepted of
+    // four at the start): following acceptances four above 0.8, three above 2/3
+    // and two from 1/2 on, following rejections (which write nothing unless an
+    // exchange is pending) four below 1/6, three below 1/3 and two between:
+    // each advances by 1.5 to 3.7 proposals on the average.  What a pass costs
+    // is its rows (from the last-level cache) and a read and a write of the
+    // cache.  10x10 M = 400, 256 chains, 124 proposals: 52.5 ms at any a with
+    // one proposal in a pass; now 25.2 ms at a = 1, 34.5 at 0.92, 41.2 at 0.17,
+    // 33.5 at 0.07.
+    const int64_t na = acc0 + acc + 3, nn = p0 + r + 4;
+    const bool chain = 2 * na >= nn || max_rows < kMaxRows;   // assume acceptance
+    const int want = chain ? (5 * na > 4 * nn ? 4 : 3 * na > 2 * nn ? 3 : 2 * na >= nn ? 2 : 1)
+                           : (6 * na < nn ? 4 : 3 * na < nn ? 3 : 2);
+    const int nd = min(min(want, max_rows - np), n_prop - r);
+    if (r + kMaxRows > rbase + 64) {
+      rbase = r;
+      philox4x64_10(ctr + (uint64_t)(r + lane), 0, 0, 0, seed, id, rnd);
+    }
+    slo = lo;
+    shi = hi;
+#pragma unroll
+    for (int q = 0; q < kMaxRows; ++q) {
+      if (q >= np && q < np + nd) {
+        const uint64_t r0 = lane64(rnd[0], r + q - np - rbase);
+        const uint64_t r1 = lane64(rnd[1], r + q - np - rbase);
+        const int kup = (int)(((r0 >> 11) * (uint64_t)half) >> 53);
+        const int kdn = (int)(((r1 >> 11) * (uint64_t)half) >> 53);
+        ei[q] = select128(slo, shi, kup);
+        ej[q] = select128(~slo & nmask_lo, ~shi & nmask_hi, kdn);
+        if (chain) {
+          flip(slo, shi, ei[q]);
+          flip(slo, shi, ej[q]);
+        }
+      }
+    }
+    const int rows = np + nd;
+    if (active) {
+      int l[kMaxRows];                         // row l1 N + l2 of the site-pair tables
+#pragma unroll
+      for (int q = 0; q < kMaxRows; ++q)
+        l[q] = q < rows ? (int)perminv[(size_t)g * N + ei[q]] * N + perminv[(size_t)g * N + ej[q]]
+                        : l[0];
+      for (int k = 0; k < K; ++k) {
+        const float* Tq[kMaxRows];
+#pragma unroll
+        for (int q = 0; q < kMaxRows; ++q) Tq[q] = Tpair + ((size_t)l[q] * KM + (size_t)k * M) * 2;
+        const float* tp = tc + ((size_t)(k * nt) * G + g) * 16;
+        float* to = tn + ((size_t)(k * nt) * G + g) * 16;
+        const size_t step = (size_t)G * 16;
+        float pr[kMaxRows], pi[kMaxRows];
+        if (chain) {
+          if (rows == 1) stream_rows<1, 1, 1>(tp, to, Tq, nt, step, pr, pi);
+          else if (rows == 2) stream_rows<2, 2, 2>(tp, to, Tq, nt, step, pr, pi);
+          else if (rows == 3) stream_rows<3, 3, 3>(tp, to, Tq, nt, step, pr, pi);
+          else stream_rows<4, 4, 4>(tp, to, Tq, nt, step, pr, pi);
+        } else if (np == 0) {
+          if (rows == 1) stream_rows<1, 0, 0>(tp, to, Tq, nt, step, pr, pi);
+          else if (rows == 2) stream_rows<2, 0, 0>(tp, to, Tq, nt, step, pr, pi);
+          else if (rows == 3) stream_rows<3, 0, 0>(tp, to, Tq, nt, step, pr, pi);
+          else stream_rows<4, 0, 0>(tp, to, Tq, nt, step, pr, pi);
+        } else if (np == 1) {
+          if (rows == 2) stream_rows<2, 1, 1>(tp, to, Tq, nt, step, pr, pi);
+          else if (rows == 3) stream_rows<3, 1, 1>(tp, to, Tq, nt, step, pr, pi);
+          else stream_rows<4, 1, 1>(tp, to, Tq, nt, step, pr, pi);
+        } else if (np == 2) {
+          if (rows == 3) stream_rows<3, 2, 2>(tp, to, Tq, nt, step, pr, pi);
+          else stream_rows<4, 2, 2>(tp, to, Tq, nt, step, pr, pi);
+        } else {
+          stream_rows<4, 3, 3>(tp, to, Tq, nt, step, pr, pi);
+        }
+#pragma unroll
+        for (int q = 0; q < kMaxRows; ++q)
+          if (q >= np && q < rows) {
+            const float* f = Fpair + ((size_t)k * N * N + l[q]) * 2;
+            float* o = Rg + ((size_t)((q - np) * G + g) * K + k) * 2;
+            o[0] = f[0] * pr[q] - f[1] * pi[q];
+            o[1] = f[0] * pi[q] + f[1] * pr[q];
+          }
+      }
+    }
+    // the decisions, in order
+    int d = 0, n_acc = 0;
+    bool expected = true;
+    for (; d < nd && expected; ++d, ++r) {
+      const float* Rd = Rg + ((size_t)(d * G + g) * K) * 2;
+      double cr = 0.0, ci = 0.0;
+      if (active) {
+        for (int k = 0; k < K; ++k) {
+          const float rr = Rd[2 * k], ri = Rd[2 * k + 1];
+          const float wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
+          cr += (double)(wr * rr - wi * ri);
+          ci += (double)(wr * ri + wi * rr);
+        }
+      }
+      cr = wave_sum(cr);
+      ci = wave_sum(ci);
+      double* rb = red + 32 * (r & 1);
+      if (lane == 0) {
+        rb[wv] = cr;
+        rb[16 + wv] = ci;
+      }
+      __syncthreads();
+      double sr = 0.0, si = 0.0;
+      for (int q = 0; q < nw; ++q) {
+        sr += rb[q];
+        si += rb[16 + q];
+      }
+      const double u = (double)(lane64(rnd[2], r - rbase) >> 11) * (1.0 / 9007199254740992.0);
+      // every lane holds the same sums: a wave-uniform decision
+      const bool accept = __builtin_amdgcn_readfirstlane((int)(u < sr * sr + si * si)) != 0;
+      if (accept) {
+        ++acc;
+        ++n_acc;
+        if (active) {
+          const double den = sr * sr + si * si;
+          for (int k = 0; k < K; ++k) {
+            const float wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
+            const float rr = Rd[2 * k], ri = Rd[2 * k + 1];
+            const double qr = (double)(wr * rr - wi * ri), qi = (double)(wr * ri + wi * rr);
+            wc[2 * (k * G + g)] = (float)((qr * sr + qi * si) / den);
+            wc[2 * (k * G + g) + 1] = (float)((qi * sr - qr * si) / den);
+          }
+        }
+        int i = ei[0], j = ej[0];
+#pragma unroll
+        for (int q = 1; q < kMaxRows; ++q) {
+          i = q == np + d ? ei[q] : i;
+          j = q == np + d ? ej[q] : j;
+        }
+        flip(lo, hi, i);
+        flip(lo, hi, j);
+      }
+      expected = accept == chain;
+      if (phase == 1) {
+        const int64_t idx = p0 + r + 1;
+        if (idx % n_skip == 0) {
+          const int64_t m = idx / n_skip - 1;
+          if (m < n_per_chain && g < N) {
+            const uint64_t bit = g < 64 ? (lo >> g) & 1ull : (hi >> (g - 64)) & 1ull;
+            spins_out[((size_t)c * n_per_chain + m) * N + g] = bit ? 1 : -1;
+          }
+        }
+      }
+    }
+    // what the current cache holds
+    if (chain ? expected : np > 0) {
+      float* const sw = tc;
+      tc = tn;
+      tn = sw;
+      np = 0;
+    }
+    if (!chain) {
+      if (n_acc) {                             // the last proposal decided: d - 1
+#pragma unroll
+        for (int q = 0; q < kMaxRows; ++q)
+          if (q == rows - nd + d - 1) {
+            ei[0] = ei[q];
+            ej[0] = ej[q];
+          }
+        np = 1;
+      }
+    } else if (!expected) {
+      np += n_acc;                             // the accepted ones follow the pending ones
+    }
+  }
+  if (g == 0) {
+    state[4 * c] = lo;
+    state[4 * c + 1] = hi;
+    state[4 * c + 2] = ctr + (valid ? (uint64_t)n_prop : 0ull);
     acc_out[c] += valid ? acc : -((int64_t)1 << 40);   // marks a chain outside Sz = 0
   }
   if (g < N) {
@@ -910,7 +1192,11 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
     e = hipGetLastError();
   }
   const int threads = std::max(64, (c->G + 63) / 64 * 64);
-  const size_t lds = (size_t)c->G * c->K * 2 * rs + 64 * sizeof(double);
+  // the streaming kernel's ratios: rows of a pass as far as they fit 64 KiB
+  const size_t row_lds = (size_t)c->G * c->K * 2 * rs;
+  const int max_rows = (int)std::max<size_t>(1, std::min<size_t>(
+      c->prec == NQS_FP64 ? 1 : kMaxRows, 65024 / row_lds));
+  const size_t lds = max_rows * row_lds + 64 * sizeof(double);
   auto refresh = [&]() -> hipError_t {
     hipError_t r = launch_theta(c, cur, n_chains, L, t, st);
     if (r == hipSuccess) r = launch_lse(c, L, n_chains, lp, w, st);
@@ -927,14 +1213,14 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
                   n_per_chain, acc, cur, st);
       if (r == hipErrorNotSupported) {
         if (c->prec == NQS_FP64)
-          sample_kernel<double><<<(unsigned)n, threads, lds, st>>>(
+          sample_kernel<<<(unsigned)n, threads, lds, st>>>(
               c->N, c->G, c->K, c->M, c->n_htiles, c->dev.perminv, (const double*)c->par.Tpair,
               (const double*)c->par.Fpair, (double*)t, (double*)t2, (double*)w, chain_state, cnt,
               phase, p0,
               ns_dev, ns_host, seed, spins_out, n_per_chain, acc, cur);
         else
-          sample_kernel<float><<<(unsigned)n, threads, lds, st>>>(
-              c->N, c->G, c->K, c->M, c->n_htiles, c->dev.perminv, (const float*)c->par.Tpair,
+          sample_stream_kernel<<<(unsigned)n, threads, lds, st>>>(
+              c->N, c->G, c->K, c->M, c->n_htiles, max_rows, c->dev.perminv, (const float*)c->par.Tpair,
               (const float*)c->par.Fpair, (float*)t, (float*)t2, (float*)w, chain_state, cnt,
               phase, p0,
               ns_dev, ns_host, seed, spins_out, n_per_chain, acc, cur);
