@@ -2,21 +2,24 @@
 // and image weights w, FP32, any number of hidden units: the models without a
 // register-resident bond kernel.
 //
-// Same work split as the wide kernel (k_eloc_wide.hip): a workgroup of eight
-// wavefronts takes one configuration, a wavefront one 16-image block; lane
-// (q, c) holds image c and the bonds q + 4 jb of the antiparallel list; the
-// hidden units are walked in chunks of 8, the chunk's rows of the bond table
-// T = tanh(D) staged in LDS for all wavefronts (double-buffered through
+// Same work split as the wide kernel (k_eloc_wide.hip): a wavefront takes one
+// (configuration, 16-image block); lane (q, c) holds image c and the bonds
+// q + 4 jb of the antiparallel list; the eight wavefronts of a workgroup walk
+// the hidden units in lockstep in chunks of 8, the chunk's rows of the bond
+// table T = tanh(D) staged in LDS for all of them (double-buffered through
 // registers).  t of the chunk is one 64-byte run per image, read one chunk
 // ahead.
 //
 // Bound: VALU issue of the factors F prod_h (s + t_h T_h), 8 instructions each,
-// 130 per pair of bonds and chunk with the two addresses and signs.  At 8x8
-// M = 128, 2003 configurations: 4.7 ms (0.73 of the issue bound) where the
-// kernel before it, which read every T row from L2 per (image, bond), took
-// 18.6 ms; 10x10 M = 104, 500 configurations 2.4 against 8.0 ms.  Every product is
-// formed in the order and with the roundings of F prod_h (1 + t_h (+-T_h)).
-// Placing the rows by bank group, as the wide kernel does, measured the same.
+// 132 per pair of bonds and chunk with the two addresses and signs.  At 8x8
+// M = 128, 2003 configurations: 4.3 ms (0.81 of the issue bound) where a kernel
+// that reads every T row from L2 per (image, bond) took 18.6 ms, and one whose
+// eight wavefronts share a configuration 4.7 ms; nqs_eloc at 10x10 M = 104, 500
+// configurations 8.4, 2.9 and 2.7 ms; 6x6 K = 3 M = 24, 3000 configurations 4.2,
+// 2.1 and 1.6 ms; seven at 6x6 M = 40 117, 59 and 44 us.
+// Every product is formed in the order and with the roundings of
+// F prod_h (1 + t_h (+-T_h)).  Placing the rows by bank group, as the wide
+// kernel does, measured the same.
 #include "device_common.h"
 #include "nqs_internal.h"
 
@@ -30,183 +33,243 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) const f32x2* lds_f32x2_ptr;
 constexpr int kRowBytes = 80;             // staged row: T of 8 units, F_+, F_- (an odd number
                                           // of 16-byte units: rows spread over the bank groups)
-constexpr uint32_t kBufStride = 1u << 16;   // bytes between the two staged chunks
 
-// Bond slots per lane (even), four lane groups: they cover the antiparallel bonds of nearly
-// every Sz = 0 configuration (mean 2 N N / (N - 1): 34, 74, 130, 202) in one
-// pass, at 10x10 in two; each pass reads t and the bond table again.
+// Bond slots per lane (even), four lane groups: 40, 88, 144 and 224 bonds cover
+// the antiparallel bonds of nearly every Sz = 0 configuration (mean
+// 2 N N / (N - 1): 34, 74, 130, 202), so t and the bond table are read once.
 template <int N>
-constexpr int row_bonds() { return N == 16 ? 10 : N == 36 ? 20 : N == 64 ? 36 : 28; }
+constexpr int row_bonds() { return N == 16 ? 10 : N == 36 ? 22 : N == 64 ? 36 : 56; }
 
+// Workgroups per compute unit: at 4x4 a walk is short (five pairs of slots a
+// chunk), and a second workgroup fills its list building and barriers
+// (nqs_eloc at M = 64, 5000 configurations: 0.61 -> 0.47 ms).
 template <int N>
-__global__ __launch_bounds__(64 * kRowWaves) void eloc_rows_kernel(
-    const int8_t* __restrict__ spins, int64_t S, int rsplit, int K, int M,
-    const int32_t* __restrict__ bonds,
-    const int32_t* __restrict__ bmap, const float* __restrict__ t, const float* __restrict__ w, const float* __restrict__ Tpm,
+constexpr int row_wgs() { return N == 16 ? 2 : 1; }
+
+// LDS, in bytes: the staged chunks lie a power of two apart, so that a row's
+// address is (offset | buffer bit); the small arrays lie between them.
+template <int N>
+struct RowsCfg {
+  static constexpr int NB = 4 * N;
+  static constexpr uint32_t CAP = NB * kRowBytes;
+  static constexpr uint32_t BUF = N == 16 ? 1u << 13 : N == 36 ? 1u << 14 : N == 64 ? 1u << 15 : 1u << 16;
+  static constexpr uint32_t LIST = CAP;                        // [waves][NB] uint16
+  static constexpr uint32_t BUSY = LIST + kRowWaves * NB * 2;  // [waves] int
+  static constexpr uint32_t LDS = BUF + CAP;
+  static_assert(BUSY + kRowWaves * 4 <= BUF, "the small arrays fit between the chunks");
+};
+
+// per: items of a workgroup in a round (its first `per` wavefronts take them)
+template <int N>
+__global__ __launch_bounds__(64 * kRowWaves, 2 * row_wgs<N>()) void eloc_rows_kernel(
+    const int8_t* __restrict__ spins, int64_t S, int per, int K, int M,
+    const int32_t* __restrict__ bonds, const int32_t* __restrict__ bmap,
+    const float* __restrict__ t, const float* __restrict__ w, const float* __restrict__ Tpm,
     const float* __restrict__ F, double* __restrict__ partial) {
-  constexpr int NB = 4 * N, G = 8 * N, nblk = G / 16, THREADS = 64 * kRowWaves;
+  using Cfg = RowsCfg<N>;
+  constexpr int NB = Cfg::NB, G = 8 * N, nblk = G / 16, THREADS = 64 * kRowWaves;
   constexpr int WB = row_bonds<N>();
   constexpr int E4 = NB * 4, NSTG = (E4 + THREADS - 1) / THREADS;   // float4 of a chunk
-  constexpr int rounds = (nblk + kRowWaves - 1) / kRowWaves;
   static_assert(WB % 2 == 0, "the products run two bonds at a time");
-  constexpr int CAP = NB * kRowBytes;        // bytes of a staged chunk
-  static_assert(CAP <= (int)kBufStride, "a chunk fits below the second buffer");
-  // chunk buffers 64 KiB apart, so that a row's LDS address is (offset | buffer
-  // bit) without an addition per bond; the space between holds nothing
-  __shared__ __align__(16) unsigned char Tc[kBufStride + CAP];
-  __shared__ uint16_t list[NB];
-  __shared__ int nc_s;
+  constexpr bool PACK = N == 100;              // two bond slots' offsets in a register
+  constexpr int OW = PACK ? WB / 2 : WB;
+  // aligned to the chunk distance, so that addresses are ORs
+  __shared__ __align__(Cfg::BUF) unsigned char lds[Cfg::LDS];
 
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, c = lane & 15;
   const int KM = K * M, NCH = KM / 8, CPR = M / 8;
+  uint16_t* list = reinterpret_cast<uint16_t*>(lds + Cfg::LIST) + wv * NB;
+  int* busy = reinterpret_cast<int*>(lds + Cfg::BUSY);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
+  // staging of chunk ch: float4 e = tid + 512 i -> row e / 4, part e % 4 of
+  // tanh(D); thread tid < NB also stages (F_+, F_-) of row tid for its RBM k
   f32x4 stg[NSTG], sF;
-  auto stage_load = [&](int ch) __attribute__((always_inline)) {
+  const uint32_t sofs = (uint32_t)(tid >> 2) * 16u * (uint32_t)KM + 16u * (tid & 3);
+  auto stage_load = [&](int ch, int k) __attribute__((always_inline)) {
+    const char* b = reinterpret_cast<const char*>(Tpm) + (size_t)ch * 64;
 #pragma unroll
-    for (int i = 0; i < NSTG; ++i) {
-      const int e = min(tid + THREADS * i, E4 - 1);
-      stg[i] = *reinterpret_cast<const f32x4*>(Tpm + (size_t)(e / 4) * 4 * KM + 16 * ch + 4 * (e % 4));
-    }
-    sF = *reinterpret_cast<const f32x4*>(F + ((size_t)(ch / CPR) * NB + (tid < NB ? tid : 0)) * 4);
+    for (int i = 0; i < NSTG; ++i)
+      if (THREADS * (i + 1) <= E4 || tid + THREADS * i < E4)
+        stg[i] = *reinterpret_cast<const f32x4*>(b + (size_t)i * (THREADS / 4) * 16 * KM + sofs);
+    if (tid < NB) sF = *reinterpret_cast<const f32x4*>(F + ((size_t)k * NB + tid) * 4);
   };
-  auto stage_store = [&](int buf) __attribute__((always_inline)) {
+  auto stage_store = [&](uint32_t buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NSTG; ++i) {
-      const int e = tid + THREADS * i;
-      if (e < E4)
-        *reinterpret_cast<f32x4*>(&Tc[buf * kBufStride + kRowBytes * (e / 4) + 16 * (e % 4)]) = stg[i];
-    }
-    if (tid < NB) *reinterpret_cast<f32x4*>(&Tc[buf * kBufStride + kRowBytes * tid + 64]) = sF;
+    for (int i = 0; i < NSTG; ++i)
+      if (THREADS * (i + 1) <= E4 || tid + THREADS * i < E4)
+        *reinterpret_cast<f32x4*>(lds + buf + kRowBytes * ((tid + THREADS * i) >> 2) +
+                                  16 * (tid & 3)) = stg[i];
+    if (tid < NB) *reinterpret_cast<f32x4*>(lds + buf + kRowBytes * tid + 64) = sF;
   };
-  stage_load(0);
+  stage_load(0, 0);
   stage_store(0);
-  const uint32_t tc0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)Tc;
-  int gc = 0;                                  // chunks processed by the workgroup so far
+  uint32_t buf = 0;                            // byte offset of the chunk in use
 
-  // work items: configurations, or (rsplit) rounds of eight image blocks of them
-  const int64_t n_items = rsplit ? S * rounds : S;
-  for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
-    const int64_t s = rsplit ? item / rounds : item;
-    const int rd0 = rsplit ? (int)(item - s * rounds) : 0, rd1 = rsplit ? rd0 + 1 : rounds;
-    const int8_t* srow = spins + s * N;
-    __syncthreads();                           // previous configuration done with the list
-    if (wv == 0) {
-      int n = 0;
-      for (int base = 0; base < NB; base += 64) {
-        const int b = base + lane;
-        bool anti = false;
-        int sp = 0;
-        if (b < NB) {
-          sp = srow[bonds[2 * b]];
-          anti = sp != srow[bonds[2 * b + 1]];
+  const int64_t n_items = S * nblk;
+  int64_t item = (int64_t)blockIdx.x * per + wv;
+  bool act = wv < per && item < n_items;
+  bool first = true;                           // first walk of the item
+  int64_t s = 0;
+  int blk = 0, e0 = 0, nc = 0;                 // list entries from e0 on in this and later walks
+  double Qr = 0.0, Qi = 0.0;
+
+  for (;;) {
+    if (lane == 0) busy[wv] = act;
+    __syncthreads();                           // also: the walk's first chunk is staged
+    if (__ballot(lane < kRowWaves && busy[lane & (kRowWaves - 1)] != 0) == 0ull) break;
+    // a walk over the hidden units: bonds e0 + q + 4 jb of the list
+    uint32_t offs[OW];                         // row offset in bytes, bit 0: s = -1
+    int nv = 0, nvu = 0;                       // slots in use in the lane, and in lane group 0
+    const f32x4* tg = reinterpret_cast<const f32x4*>(t);
+    f32x4 tn[4];
+    if (act) {
+      if (first) {
+        s = item / nblk;
+        blk = (int)(item - s * nblk);
+        const int8_t* srow = spins + s * N;
+        int n = 0;
+        for (int base = 0; base < NB; base += 64) {
+          const int b = base + lane;
+          bool anti = false;
+          int sp = 0;
+          if (b < NB) {
+            sp = srow[bonds[2 * b]];
+            anti = sp != srow[bonds[2 * b + 1]];
+          }
+          const unsigned long long msk = __ballot(anti);
+          const int pos = __popcll(msk & ((1ull << lane) - 1ull));
+          if (anti) list[n + pos] = (uint16_t)(b | (sp > 0 ? 0x8000 : 0));
+          n += __popcll(msk);
         }
-        const unsigned long long msk = __ballot(anti);
-        const int pos = __popcll(msk & ((1ull << lane) - 1ull));
-        if (anti) list[n + pos] = (uint16_t)(b | (sp > 0 ? 0x8000 : 0));
-        n += __popcll(msk);
+        wave_sync_lds();
+        nc = n;
+        e0 = 0;
+        Qr = Qi = 0.0;
       }
-      if (lane == 0) nc_s = n;
+      const int g = blk * 16 + c;
+      tg += ((size_t)s * NCH * G + g) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tn[e] = tg[e];
+      nv = nc > e0 + q ? min(WB, (nc - e0 - q + 3) / 4) : 0;
+      nvu = __builtin_amdgcn_readfirstlane(nv);
+#pragma unroll
+      for (int jb = 0; jb < WB; ++jb) {
+        const int e = jb < nv ? list[e0 + q + 4 * jb] : 0;   // padding entries use bond 0
+        const uint32_t v = (uint32_t)(bmap[(size_t)g * NB + (e & 0x7fff)] ^ (e >> 15));
+        const uint32_t o = kRowBytes * (v >> 1) | (v & 1u);
+        if constexpr (!PACK) offs[jb] = o;
+        else if (jb & 1) offs[jb / 2] |= o << 16;
+        else offs[jb / 2] = o;
+      }
+      e0 += 4 * WB;
+    } else {
+#pragma unroll
+      for (int i = 0; i < OW; ++i) offs[i] = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tn[e] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    __syncthreads();
-    const int nc = nc_s;
-    const int npass = nc > 0 ? (nc + 4 * WB - 1) / (4 * WB) : 1;
 
-    for (int rd = rd0; rd < rd1; ++rd) {
-      const int blk = rd * kRowWaves + wv;
-      const bool active = blk < nblk;
-      const int g = (active ? blk : 0) * 16 + c;
-      double Qr = 0.0, Qi = 0.0;
-      const f32x4* tg = reinterpret_cast<const f32x4*>(t) + ((size_t)s * NCH * G + g) * 4;
-
-      for (int pass = 0; pass < npass; ++pass) {
-        uint32_t offs[WB];                     // row offset in bytes, bit 0: s = -1
-        const int i0 = pass * 4 * WB + q;
-        const int nv = nc > i0 ? min(WB, (nc - i0 + 3) / 4) : 0;
-        // bonds of lane group 0 (the most of any group): a partly filled pass
-        // skips the empty pairs of slots
-        const int p0 = pass * 4 * WB;
-        const int nvu = __builtin_amdgcn_readfirstlane(nc > p0 ? min(WB, (nc - p0 + 3) / 4) : 0);
+    float Pr[WB], Pi[WB];
+    int k = 0, cin = 0;                        // RBM, chunk within it
+    for (int ch = 0; ch < NCH; ++ch) {
+      const bool last = ch + 1 == NCH;
+      const uint32_t base = lds0 | buf;
+      // keep the comparisons with these in the loop: hoisted, they fill registers
+      nvu = __builtin_amdgcn_readfirstlane(nvu);
+      asm volatile("" : "+s"(nvu), "+v"(nv));
+      if (cin == 0) {                          // RBM start: products begin at F_s
 #pragma unroll
         for (int jb = 0; jb < WB; ++jb) {
-          const int ii = i0 + 4 * jb;
-          const int e = ii < nc ? list[ii] : 0;   // padding entries use bond 0
-          const int v = bmap[(size_t)g * NB + (e & 0x7fff)] ^ (e >> 15);
-          offs[jb] = (uint32_t)(kRowBytes * (v >> 1)) | (uint32_t)(v & 1);
+          const uint32_t o = PACK ? (jb & 1 ? offs[jb / 2] >> 16 : offs[jb / 2]) : offs[jb];
+          const f32x2 f = *(lds_f32x2_ptr)(((o & 0xfff0u) | base) + 64u + 8u * (o & 1u));
+          Pr[jb] = f.x;
+          Pi[jb] = f.y;
         }
-        float Pr[WB], Pi[WB];
-        f32x4 tn[4];
+      }
+      f32x4 tv[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) tn[e] = tg[e];
-
-        for (int ch = 0; ch < NCH; ++ch, ++gc) {
-          const int buf = gc & 1;
-          const int nxt = ch + 1 < NCH ? ch + 1 : 0;
-          const uint32_t base = tc0 + (buf ? kBufStride : 0u);
-          if (ch % CPR == 0) {                 // RBM start: products begin at F_s
+      for (int e = 0; e < 4; ++e) tv[e] = tn[e];
+      if (act) {
 #pragma unroll
-            for (int jb = 0; jb < WB; ++jb) {
-              const f32x2 f = *(lds_f32x2_ptr)((offs[jb] & ~1u) + base + 64u + 8u * (offs[jb] & 1u));
-              Pr[jb] = f.x;
-              Pi[jb] = f.y;
-            }
+        for (int e = 0; e < 4; ++e) tn[e] = tg[(size_t)(last ? 0 : ch + 1) * G * 4 + e];
+      }
+      // lands during the bond products
+      stage_load(last ? 0 : ch + 1, last ? 0 : cin + 1 == CPR ? k + 1 : k);
+#pragma unroll
+      for (int jb = 0; jb < WB; jb += 2) {
+        if (jb < nvu) {
+          uint32_t o0, o1;
+          if constexpr (PACK) {
+            asm volatile("" : "+v"(offs[jb / 2]));
+            o0 = offs[jb / 2];
+            o1 = o0 >> 16;
+          } else {
+            asm volatile("" : "+v"(offs[jb]), "+v"(offs[jb + 1]));
+            o0 = offs[jb];
+            o1 = offs[jb + 1];
           }
-          f32x4 tv[4];
+          const lds_f32x4_ptr r0 = (lds_f32x4_ptr)((PACK ? o0 & 0xfff0u : o0 & ~15u) | base);
+          const lds_f32x4_ptr r1 = (lds_f32x4_ptr)((o1 & ~15u) | base);
+          const float sg0 = __uint_as_float((o0 << 31) | 0x3f800000u);
+          const float sg1 = __uint_as_float((o1 << 31) | 0x3f800000u);
+          float ar = Pr[jb], ai = Pi[jb], br = Pr[jb + 1], bi = Pi[jb + 1];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            tv[e] = tn[e];
-            tn[e] = tg[(size_t)nxt * G * 4 + e];
-          }
-          stage_load(nxt);                     // lands during the bond products
+            const f32x4 x0 = r0[e];
+            const f32x4 x1 = r1[e];
 #pragma unroll
-          for (int jb = 0; jb < WB; jb += 2) {
-            if (jb < nvu) {
-              const lds_f32x4_ptr r0 = (lds_f32x4_ptr)((offs[jb] & ~1u) + base);
-              const lds_f32x4_ptr r1 = (lds_f32x4_ptr)((offs[jb + 1] & ~1u) + base);
-              const float sg0 = __uint_as_float((offs[jb] << 31) | 0x3f800000u);
-              const float sg1 = __uint_as_float((offs[jb + 1] << 31) | 0x3f800000u);
-              float ar = Pr[jb], ai = Pi[jb], br = Pr[jb + 1], bi = Pi[jb + 1];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const f32x4 x0 = r0[e];
-                const f32x4 x1 = r1[e];
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) {
-                  const float tr = tv[e][2 * hh], ti = tv[e][2 * hh + 1];
-                  float pa = fmaf(tr, x0[2 * hh], fmaf(-ti, x0[2 * hh + 1], sg0));
-                  float pb = fmaf(tr, x0[2 * hh + 1], ti * x0[2 * hh]);
-                  float nr = fmaf(ar, pa, -(ai * pb));
-                  ai = fmaf(ar, pb, ai * pa);
-                  ar = nr;
-                  pa = fmaf(tr, x1[2 * hh], fmaf(-ti, x1[2 * hh + 1], sg1));
-                  pb = fmaf(tr, x1[2 * hh + 1], ti * x1[2 * hh]);
-                  nr = fmaf(br, pa, -(bi * pb));
-                  bi = fmaf(br, pb, bi * pa);
-                  br = nr;
-                }
-              }
-              Pr[jb] = ar; Pi[jb] = ai; Pr[jb + 1] = br; Pi[jb + 1] = bi;
+            for (int hh = 0; hh < 2; ++hh) {
+              const float tr = tv[e][2 * hh], ti = tv[e][2 * hh + 1];
+              float pa = fmaf(tr, x0[2 * hh], fmaf(-ti, x0[2 * hh + 1], sg0));
+              float pb = fmaf(tr, x0[2 * hh + 1], ti * x0[2 * hh]);
+              float nr = fmaf(ar, pa, -(ai * pb));
+              ai = fmaf(ar, pb, ai * pa);
+              ar = nr;
+              pa = fmaf(tr, x1[2 * hh], fmaf(-ti, x1[2 * hh + 1], sg1));
+              pb = fmaf(tr, x1[2 * hh + 1], ti * x1[2 * hh]);
+              nr = fmaf(br, pa, -(bi * pb));
+              bi = fmaf(br, pb, bi * pa);
+              br = nr;
             }
           }
-          if (ch % CPR == CPR - 1) {           // RBM k complete: weight and sum
-            const float* wk = w + (((size_t)s * K + ch / CPR) * G + g) * 2;
-            const float wr = wk[0], wi = wk[1];
+          Pr[jb] = ar; Pi[jb] = ai; Pr[jb + 1] = br; Pi[jb + 1] = bi;
+        }
+      }
+      if (++cin == CPR) {                      // RBM k complete: weight and sum
+        if (act) {
+          const float* wk = w + (((size_t)s * K + k) * G + blk * 16 + c) * 2;
+          const float wr = wk[0], wi = wk[1];
 #pragma unroll
-            for (int jb = 0; jb < WB; ++jb) {
+          for (int jb = 0; jb < WB; ++jb) {
+            if (jb < nvu) {
               Qr += jb < nv ? (double)(wr * Pr[jb] - wi * Pi[jb]) : 0.0;
               Qi += jb < nv ? (double)(wr * Pi[jb] + wi * Pr[jb]) : 0.0;
             }
           }
-          stage_store(buf ^ 1);
-          __syncthreads();
         }
+        cin = 0;
+        ++k;
       }
-      Qr = wave_sum(Qr);
-      Qi = wave_sum(Qi);
-      if (active && lane == 0) {
-        double* o = partial + ((size_t)s * nblk + blk) * 2;
-        o[0] = Qr;
-        o[1] = Qi;
+      buf ^= Cfg::BUF;
+      stage_store(buf);
+      __syncthreads();
+    }
+
+    if (act) {
+      first = false;
+      if (e0 >= nc) {                          // the item's last walk
+        Qr = wave_sum(Qr);
+        Qi = wave_sum(Qi);
+        if (lane == 0) {
+          partial[2 * item] = Qr;
+          partial[2 * item + 1] = Qi;
+        }
+        item += (int64_t)gridDim.x * per;
+        act = item < n_items;
+        first = true;
       }
     }
   }
@@ -215,13 +278,14 @@ __global__ __launch_bounds__(64 * kRowWaves) void eloc_rows_kernel(
 template <int N>
 hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t, const void* w,
                double* partial, hipStream_t st) {
-  // few configurations: their rounds of image blocks go to different workgroups
-  const int n_cu = c->n_cu > 0 ? c->n_cu : 256, rounds = (c->G / 16 + kRowWaves - 1) / kRowWaves;
-  const int rsplit = S < 4 * (int64_t)n_cu && rounds > 1;
-  const int64_t blocks = std::min<int64_t>(rsplit ? S * rounds : S, n_cu);
+  if (S <= 0) return hipSuccess;
+  const int64_t n_wg = (c->n_cu > 0 ? c->n_cu : 256) * row_wgs<N>(), items = S * (c->G / 16);
+  // fewer items than wavefront slots: the same number in every workgroup
+  const int per = (int)std::min<int64_t>(kRowWaves, (items + n_wg - 1) / n_wg);
+  const int64_t blocks = std::min<int64_t>((items + per - 1) / per, n_wg);
   eloc_rows_kernel<N><<<(unsigned)blocks, 64 * kRowWaves, 0, st>>>(
-      spins, S, rsplit, c->K, c->M, c->dev.bonds, c->dev.bmap, (const float*)t, (const float*)w,
-       (const float*)c->par.Tpm, (const float*)c->par.F, partial);
+      spins, S, per, c->K, c->M, c->dev.bonds, c->dev.bmap, (const float*)t, (const float*)w,
+      (const float*)c->par.Tpm, (const float*)c->par.F, partial);
   return hipGetLastError();
 }
 

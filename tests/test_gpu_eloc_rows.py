@@ -1,8 +1,8 @@
 """E_loc of FP32 models without a register-resident bond kernel (stored-t bond
 kernel): every lattice size, one and several RBMs, random configurations and
 ordered ones whose antiparallel bonds need more than one pass of bond slots
-(stripes: 40 of 64 / 108 of 144 / 192 of 256 / 300 of 400 bonds, against 40, 80,
-144 and 112 slots), one and many configurations per call; nqs_eloc_grad of the
+(stripes: 40 of 64 / 108 of 144 / 192 of 256 / 300 of 400 bonds, against 40, 88,
+144 and 224 slots), one and many configurations per call; nqs_eloc_grad of the
 same models against its two separate calls."""
 import numpy as np
 import pytest
