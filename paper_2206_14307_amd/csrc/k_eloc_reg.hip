@@ -196,12 +196,22 @@ hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t, 
 // and (s1 s2)^M = 1, so the second-hop product is prod_h (s2 A_h + T2_h B_h)
 // and the first-hop product prod_h A_h.
 //
-// One wavefront per (sample, first-hop slot, 32-image tile).  The two lanes
-// of an image split the hidden units by parity (lane half = lane / 32 takes
-// h = 2j + half), both walk every second-hop bond, and the two partial
+// One wavefront per (sample, first-hop slot, group of 32-image tiles).  The two
+// lanes of an image split the hidden units by parity (lane half = lane / 32
+// takes h = 2j + half), both walk every second-hop bond, and the two partial
 // products are joined with v_permlane32_swap, which serves the two bonds of a
 // pass at once (bond 0 complete in lanes 0..31, bond 1 in lanes 32..63).  The
-// +T table stays in LDS for the launch, each row ordered [even h | odd h].
+// +T table stays in LDS for the launch, each row ordered [even h | odd h] and
+// followed by F_+, F_-, the rows placed by bank groups as in the fused kernel;
+// the bond lists come from the spins as a mask, once for the tiles of an item.
+//
+// Bound: VALU issue of the second-hop factors (8 each), 576 of 637 instructions
+// of a pass at 6x6 M = 72, with 36 LDS reads of 16 bytes beside them.
+// nqs_lanczos_moments of 768 configurations 12.5 -> 12.1 ms (rows by bank groups
+// 0.7; the lists, which another wavefront's products hid, nothing); 4x4 M = 16,
+// 5000 configurations 10.5 -> 2.8 ms, where the lists and the slots' unequal
+// lengths had cost more than the products.  Twelve wavefronts (168 VGPRs,
+// spills) took 14.4 ms at 6x6.
 //
 // Ratio form: f = s2 A + T2 B = A (s2 + T2 Q) with Q = B / A.  Once per
 // (first hop, image) Q replaces t in registers and every second-hop product
@@ -227,51 +237,94 @@ template <typename R, int N, int M>
 __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
     const int8_t* __restrict__ spins, int64_t S, int G, int n_htiles,
     const int32_t* __restrict__ bonds, const double* __restrict__ bond_J,
-    const int32_t* __restrict__ bmap, const R* __restrict__ t, const R* __restrict__ w,
-    const R* __restrict__ Tpm, const R* __restrict__ F, double* __restrict__ partial2,
-    int allow_ratio) {
+    const int32_t* __restrict__ fmap, const int32_t* __restrict__ frow,
+    const R* __restrict__ t, const R* __restrict__ w, const R* __restrict__ Tpm,
+    const R* __restrict__ F, double* __restrict__ partial2,
+    int allow_ratio, int tpi) {
   using Cfg = RegCfg<R, N, 1, M>;
-  constexpr int NB = Cfg::NB, ST = Cfg::STRIDE, MH = M / 2;
-  __shared__ __align__(16) R Tl[NB * ST];
-  __shared__ int16_t lists[kRegWaves][2][NB];
-  __shared__ int8_t rows[kRegWaves][N];
+  constexpr int NB = Cfg::NB, MH = M / 2;
+  constexpr int CAP = fused_cap16(NB, fused_row16(1, M, sizeof(R))) * 16 / (int)sizeof(R);
+  constexpr int BPL = (NB + 63) / 64;                    // bonds of a lane
+  static_assert(N <= 64, "a configuration's spins are one mask");
+  __shared__ __align__(16) R Tl[CAP];
+  __shared__ uint16_t lists[kRegWaves][NB];
   for (int idx = threadIdx.x; idx < NB * M; idx += blockDim.x) {
     const int beta = idx / M, h = idx % M;
     const R* src = Tpm + ((size_t)beta * 2 * M + h) * 2;
     const int pos = (h & 1) * MH + (h >> 1);             // [even h | odd h]
-    Tl[beta * ST + 2 * pos] = src[0];
-    Tl[beta * ST + 2 * pos + 1] = src[1];
+    R* row = Tl + frow[beta];
+    row[2 * pos] = src[0];
+    row[2 * pos + 1] = src[1];
+    if (h < 4) row[2 * M + h] = F[(size_t)beta * 4 + h];   // F_+, F_-
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int ntiles = G / 32;
-  const int64_t n_items = S * NB * ntiles;
+  const int ntiles = G / 32, parts = ntiles / tpi;
+  const int64_t n_items = S * NB * parts;
   const int64_t stride = (int64_t)gridDim.x * kRegWaves;
-  int16_t* l1 = lists[wv][0];
-  int16_t* l2 = lists[wv][1];
-  int8_t* row2 = rows[wv];
+  uint16_t* l2 = lists[wv];
+  // this lane's bonds 64 u + lane (a pair of equal sites where there is none)
+  int bi[BPL], bj[BPL];
+#pragma unroll
+  for (int u = 0; u < BPL; ++u) {
+    const int b = 64 * u + lane;
+    bi[u] = b < NB ? bonds[2 * b] : 0;
+    bj[u] = b < NB ? bonds[2 * b + 1] : 0;
+  }
+  // a row from its offset, a multiple of 16 bytes (read in 16-byte pieces)
+  auto row_at = [&](int off) __attribute__((always_inline)) {
+    return reinterpret_cast<const f32x4*>(Tl) + (off >> 2);
+  };
   for (int64_t item = (int64_t)blockIdx.x * kRegWaves + wv; item < n_items; item += stride) {
-    const int64_t s = item / ((int64_t)NB * ntiles);
-    const int slot = (int)((item / ntiles) % NB);
-    const int tile = (int)(item % ntiles);
+    // items in blocks of 16 configurations, the slots slowest within a block and
+    // rotated from block to block: the block's t stays in L2, and a wavefront's
+    // items spread over the slots, whose lists shorten from the first to the last
+    const int64_t sp = item / parts;
+    const int part = (int)(item - sp * parts);
+    const int64_t s0 = sp / (16 * NB) * 16;
+    const int ns = (int)min((int64_t)16, S - s0), r = (int)(sp - s0 * NB);
+    const int rs = r / ns;
+    const int64_t s = s0 + (r - rs * ns);
+    const int slot = (int)((rs + 37 * (s0 / 16)) % NB);
     const int8_t* srow = spins + s * N;
-    const int nc = build_list(srow, bonds, NB, l1, lane);
-    if (slot >= nc) continue;                            // wave-uniform
-    const int b1 = l1[slot];
-    const int i1 = bonds[2 * b1], j1 = bonds[2 * b1 + 1];
-    for (int i = lane; i < N; i += 64) row2[i] = srow[i];
-    wave_sync_lds();
-    if (lane == 0) {
-      row2[i1] = srow[j1];
-      row2[j1] = srow[i1];
+    // up spins of s; its antiparallel bonds as masks; the slot-th of them is b1
+    const uint64_t up = __builtin_amdgcn_ballot_w64(lane < N && srow[lane < N ? lane : 0] > 0);
+    int b1 = 0, nc = 0;
+#pragma unroll
+    for (int u = 0; u < BPL; ++u) {
+      uint64_t m = __builtin_amdgcn_ballot_w64((((up >> bi[u]) ^ (up >> bj[u])) & 1u) != 0u);
+      const int n = __popcll(m);
+      if (slot >= nc && slot < nc + n) {
+        for (int skip = slot - nc; skip > 0; --skip) m &= m - 1;
+        b1 = 64 * u + __builtin_ctzll(m);
+      }
+      nc += n;
     }
-    wave_sync_lds();
-    const int nc2 = build_pair_list(row2, bonds, NB, l2, lane, b1, i1, j1);
+    if (slot >= nc) continue;                            // wave-uniform
+    const int i1 = bonds[2 * b1], j1 = bonds[2 * b1 + 1];
+    const uint64_t up2 = up ^ (1ull << i1) ^ (1ull << j1);   // s^{b1}
+    // its second hops (pair_list.h), with the flag 0x8000 where the sign of
+    // the exchange is -1, and its diagonal energy
+    int nc2 = 0;
     double diag2 = 0.0;
-    for (int b = lane; b < NB; b += 64)
-      diag2 += 0.25 * bond_J[b] * (double)(row2[bonds[2 * b]] * row2[bonds[2 * b + 1]]);
+#pragma unroll
+    for (int u = 0; u < BPL; ++u) {
+      const int b = 64 * u + lane, i = bi[u], j = bj[u];
+      const bool anti = (((up2 >> i) ^ (up2 >> j)) & 1u) != 0u;
+      const bool shared = i == i1 || i == j1 || j == i1 || j == j1;
+      const bool keep = anti && b != b1 && (shared || b > b1);
+      const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+      const int pos = nc2 + __popcll(m & ((1ull << lane) - 1ull));
+      if (keep)
+        l2[pos] = (uint16_t)(b | (shared ? 0 : kPairTwice) | (((up2 >> i) & 1u) ? 0x8000 : 0));
+      nc2 += __popcll(m);
+      const double jb = b < NB ? 0.25 * bond_J[b] : 0.0;
+      diag2 += anti ? -jb : jb;
+    }
     diag2 = wave_sum(diag2);
+    wave_sync_lds();
 
+    for (int tile = part * tpi; tile < (part + 1) * tpi; ++tile) {
     // lane-derived values are recomputed per item rather than hoisted out of
     // the item loop and kept live (or spilled) across it
     int lane_i = lane;
@@ -293,13 +346,12 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
     };
     load_t(g);
     const R wr = w[((size_t)s * G + g) * 2], wi = w[((size_t)s * G + g) * 2 + 1];
-    const int v1 = bmap[(size_t)g * NB + b1];
-    const int beta1 = v1 >> 1;
-    const int s1b = -(int)srow[i1];
+    const int v1 = fmap[(size_t)g * NB + b1];
+    const int s1b = ((up >> i1) & 1u) ? -1 : 1;
     const int s1i = (v1 & 1) ? -s1b : s1b;
     const R s1 = (R)s1i;
-    const R* T1 = Tl + beta1 * ST + half * M;           // this lane's half of the row
-    const R* f1 = F + ((size_t)beta1 * 2 + (s1i > 0 ? 0 : 1)) * 2;
+    const f32x4* T1 = row_at(v1 >> 1) + half * (M / 4);   // this lane's half of the row
+    const R* f1 = Tl + (v1 >> 1) + 2 * M + (s1i > 0 ? 0 : 2);
     const R g1r = f1[0] * wr - f1[1] * wi, g1i = f1[0] * wi + f1[1] * wr;   // w F1
     double accr = 0.0, acci = 0.0;
 
@@ -311,7 +363,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
 #pragma unroll
       for (int j = 0; j < MH; ++j) {
         if ((j & 3) == 0) __builtin_amdgcn_sched_barrier(0);
-        const R Tr = T1[2 * j], Ti = T1[2 * j + 1];
+        const R Tr = T1[j >> 1][2 * (j & 1)], Ti = T1[j >> 1][2 * (j & 1) + 1];
         const R ar = fmaf_t(tr[j], Tr, fmaf_t(-ti[j], Ti, s1));
         const R ai = fmaf_t(tr[j], Ti, ti[j] * Tr);
         const R br = fmaf_t(s1, tr[j], Tr), bi = fmaf_t(s1, ti[j], Ti);
@@ -347,7 +399,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
         pi = 0;
 #pragma unroll
         for (int j = 0; j < MH; ++j) {
-          const R Tr = T1[2 * j], Ti = T1[2 * j + 1];
+          const R Tr = T1[j >> 1][2 * (j & 1)], Ti = T1[j >> 1][2 * (j & 1) + 1];
           const R a = fmaf_t(tr[j], Tr, fmaf_t(-ti[j], Ti, s1));
           const R b = fmaf_t(tr[j], Ti, ti[j] * Tr);
           const R nr = fmaf_t(pr, a, -(pi * b));
@@ -365,25 +417,35 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
         acci += jj * (double)wi;
       }
     }
+    // list entries and image bonds of a pass, read one pass ahead
+    int en[2], vn[2];
+    auto entry = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const int ii = i0 + n;
+        en[n] = l2[ii < nc2 ? ii : i0 < nc2 ? i0 : 0];
+        vn[n] = fmap[(size_t)g * NB + (en[n] & kPairBond)];
+      }
+    };
+    if (nc2 > 0) entry(0);
     for (int i0 = 0; i0 < nc2; i0 += 2) {
-      int beta[2], sidx[2];
+      int off[2], sidx[2];
       R sgn[2];
       double mult[2];
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
-        const int ii = i0 + n;
-        const int e = l2[ii < nc2 ? ii : i0];
-        const int b = e & kPairBond;
+        const int e = en[n], v = vn[n];
         mult[n] = (e & kPairTwice) ? 2.0 : 1.0;
-        const int v = bmap[(size_t)g * NB + b];
-        beta[n] = v >> 1;
-        const int s_b = -(int)row2[bonds[2 * b]];
-        const int sp = (v & 1) ? -s_b : s_b;
-        sgn[n] = (R)sp;
-        sidx[n] = sp > 0 ? 0 : 1;
+        off[n] = v >> 1;
+        const bool neg = ((v ^ (e >> 15)) & 1) != 0;     // s_b = -1 for an up spin at site i
+        sgn[n] = neg ? R(-1) : R(1);
+        sidx[n] = neg ? 2 : 0;
       }
-      const R* U0 = Tl + beta[0] * ST + half * M;
-      const R* U1 = Tl + beta[1] * ST + half * M;
+      const R* f2 = Tl + (half ? off[1] + sidx[1] : off[0] + sidx[0]) + 2 * M;
+      const R f2r = f2[0], f2i = f2[1];
+      entry(i0 + 2);
+      const f32x4* U0 = row_at(off[0]) + half * (M / 4);
+      const f32x4* U1 = row_at(off[1]) + half * (M / 4);
       R p0r, p0i, p1r, p1i;
       if (ratio) {
         p0r = p1r = par;
@@ -393,7 +455,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
           if ((j & 3) == 0) __builtin_amdgcn_sched_barrier(0);
           const R Qr = tr[j], Qi = ti[j];
           {
-            const R Vr = U0[2 * j], Vi = U0[2 * j + 1];
+            const R Vr = U0[j >> 1][2 * (j & 1)], Vi = U0[j >> 1][2 * (j & 1) + 1];
             const R fr = fmaf_t(Vr, Qr, fmaf_t(-Vi, Qi, sgn[0]));
             const R fi = fmaf_t(Vr, Qi, Vi * Qr);
             const R nr = fmaf_t(p0r, fr, -(p0i * fi));
@@ -401,7 +463,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
             p0r = nr;
           }
           {
-            const R Vr = U1[2 * j], Vi = U1[2 * j + 1];
+            const R Vr = U1[j >> 1][2 * (j & 1)], Vi = U1[j >> 1][2 * (j & 1) + 1];
             const R fr = fmaf_t(Vr, Qr, fmaf_t(-Vi, Qi, sgn[1]));
             const R fi = fmaf_t(Vr, Qi, Vi * Qr);
             const R nr = fmaf_t(p1r, fr, -(p1i * fi));
@@ -415,12 +477,12 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
 #pragma unroll
         for (int j = 0; j < MH; ++j) {
           if ((j & 3) == 0) __builtin_amdgcn_sched_barrier(0);
-          const R Tr = T1[2 * j], Ti = T1[2 * j + 1];
+          const R Tr = T1[j >> 1][2 * (j & 1)], Ti = T1[j >> 1][2 * (j & 1) + 1];
           const R Ar = fmaf_t(tr[j], Tr, fmaf_t(-ti[j], Ti, s1));
           const R Ai = fmaf_t(tr[j], Ti, ti[j] * Tr);
           const R Br = fmaf_t(s1, tr[j], Tr), Bi = fmaf_t(s1, ti[j], Ti);
           {
-            const R Vr = U0[2 * j], Vi = U0[2 * j + 1];
+            const R Vr = U0[j >> 1][2 * (j & 1)], Vi = U0[j >> 1][2 * (j & 1) + 1];
             const R fr = fmaf_t(Vr, Br, fmaf_t(-Vi, Bi, sgn[0] * Ar));
             const R fi = fmaf_t(Vr, Bi, fmaf_t(Vi, Br, sgn[0] * Ai));
             const R nr = fmaf_t(p0r, fr, -(p0i * fi));
@@ -428,7 +490,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
             p0r = nr;
           }
           {
-            const R Vr = U1[2 * j], Vi = U1[2 * j + 1];
+            const R Vr = U1[j >> 1][2 * (j & 1)], Vi = U1[j >> 1][2 * (j & 1) + 1];
             const R fr = fmaf_t(Vr, Br, fmaf_t(-Vi, Bi, sgn[1] * Ar));
             const R fi = fmaf_t(Vr, Bi, fmaf_t(Vi, Br, sgn[1] * Ai));
             const R nr = fmaf_t(p1r, fr, -(p1i * fi));
@@ -442,8 +504,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
       swap32(p0i, p1i);
       const R pr = p0r * p1r - p0i * p1i, pi = p0r * p1i + p0i * p1r;
       const bool valid = i0 + half < nc2;
-      const R* f2 = F + ((size_t)beta[half] * 2 + sidx[half]) * 2;
-      const R hr = f2[0] * g1r - f2[1] * g1i, hi = f2[0] * g1i + f2[1] * g1r;
+      const R hr = f2r * g1r - f2i * g1i, hi = f2r * g1i + f2i * g1r;
       accr += valid ? mult[half] * (double)(hr * pr - hi * pi) : 0.0;
       acci += valid ? mult[half] * (double)(hr * pi + hi * pr) : 0.0;
     }
@@ -454,6 +515,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
       partial2[2 * o] = accr;
       partial2[2 * o + 1] = acci;
     }
+    }   // tiles
     wave_sync_lds();
   }
 }
@@ -461,12 +523,18 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
 template <typename R, int N, int M>
 hipError_t run_twohop(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                       const void* w, double* partial2, hipStream_t st) {
-  const int64_t items = S * c->NB * (c->G / 32);
+  // tiles of an item, which share its lists: three (two at 4x4) unless the call
+  // is too small to give every wavefront several items
+  const int64_t slots = (int64_t)kRegWaves * (c->n_cu > 0 ? c->n_cu : 256);
+  const int ntiles = c->G / 32, tmax = ntiles % 3 == 0 ? 3 : 2;
+  const int tpi = S * c->NB * (ntiles / tmax) >= 16 * slots ? tmax : 1;
+  const int64_t items = S * c->NB * (ntiles / tpi);
+  // two workgroups per compute unit at 4x4 (128 VGPRs, 18 KiB of LDS)
   int64_t blocks = (items + kRegWaves - 1) / kRegWaves;
-  blocks = std::min<int64_t>(blocks, c->n_cu > 0 ? c->n_cu : 256);
+  blocks = std::min<int64_t>(blocks, (c->n_cu > 0 ? c->n_cu : 256) * (N == 16 ? 2 : 1));
   twohop_reg_kernel<R, N, M><<<(unsigned)blocks, 64 * kRegWaves, 0, st>>>(
-      spins, S, c->G, c->n_htiles, c->dev.bonds, c->dev.bond_J, c->dev.bmap, (const R*)t,
-      (const R*)w, (const R*)c->par.Tpm, (const R*)c->par.F, partial2, c->direct_only ? 0 : 1);
+      spins, S, c->G, c->n_htiles, c->dev.bonds, c->dev.bond_J, c->dev.fmap, c->dev.frow,
+      (const R*)t, (const R*)w, (const R*)c->par.Tpm, (const R*)c->par.F, partial2, c->direct_only ? 0 : 1, tpi);
   return hipGetLastError();
 }
 
