@@ -567,14 +567,19 @@ nqs_status nqs_logpsi(nqs_ctx* c, const int8_t* spins, int64_t S, double* logpsi
 
 namespace {
 // log psi and E_loc of n configurations with the fused (K*M <= 128) or wide
-// kernel; part holds the per-(configuration, 16-image block) partials.
+// kernel; part holds the per-(configuration, 16-image block) partials.  The bond
+// lists are not split over wavefronts: a configuration's sums have one order,
+// whatever the call and the neighbour chunk that hold it.
 hipError_t eloc_fused_any(nqs_ctx* c, const int8_t* sp, int64_t n, double* part, double* lp,
                           double* eloc, int eloc_stride, hipStream_t st) {
   if (eloc_fused_supported(c))
-    return NQS_RUN(c, K_ELOC, st, launch_eloc_fused(c, sp, n, part, lp, eloc, eloc_stride, st));
-  hipError_t e = NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, part, st));
+    return NQS_RUN(c, K_ELOC, st,
+                   launch_eloc_fused(c, sp, n, part, lp, eloc, eloc_stride, st, false));
+  hipError_t e =
+      NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, part, st, nullptr, false));
   if (e == hipSuccess)
-    e = NQS_RUN(c, K_ELOC_FIN, st, launch_fused_finish(c, sp, n, part, lp, eloc, eloc_stride, st));
+    e = NQS_RUN(c, K_ELOC_FIN, st,
+                launch_fused_finish(c, sp, n, part, lp, eloc, eloc_stride, st, false));
   return e;
 }
 

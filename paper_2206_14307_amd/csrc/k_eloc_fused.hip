@@ -409,10 +409,10 @@ namespace {
 
 template <int N, int PREC, int K, int M, bool RECIP>
 hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, double* logpsi,
-               double* eloc, int eloc_stride, hipStream_t st) {
+               double* eloc, int eloc_stride, int nsplit, hipStream_t st) {
   using T = ThetaTraits<PREC>;
   using R = typename T::R;
-  const int nsplit = fused_nsplit(c, S), cbs = c->G / 16 * nsplit;
+  const int cbs = c->G / 16 * nsplit;
   const int64_t blocks = std::min<int64_t>(S * cbs, c->n_cu > 0 ? c->n_cu : 256);
   auto kernel = nsplit > 1 ? eloc_fused_kernel<N, PREC, K, M, RECIP, true>
                            : eloc_fused_kernel<N, PREC, K, M, RECIP, false>;
@@ -438,32 +438,32 @@ constexpr size_t kLdsLimit = 160 * 1024;
 // range check passed for the current parameters and its table fits in LDS.
 template <int N, int PREC, int K, int M>
 hipError_t run_if_fits(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                       double* logpsi, double* eloc, int es, hipStream_t st) {
+                       double* logpsi, double* eloc, int es, int nsplit, hipStream_t st) {
   if constexpr (FusedCfg<N, PREC, K, M, false>::LDS > kLdsLimit) {
     return hipErrorNotSupported;
   } else {
     if constexpr (FusedCfg<N, PREC, K, M, true>::LDS <= kLdsLimit)
       if (c->par.recip_ok && !c->direct_only)
-        return run<N, PREC, K, M, true>(c, spins, S, part, logpsi, eloc, es, st);
-    return run<N, PREC, K, M, false>(c, spins, S, part, logpsi, eloc, es, st);
+        return run<N, PREC, K, M, true>(c, spins, S, part, logpsi, eloc, es, nsplit, st);
+    return run<N, PREC, K, M, false>(c, spins, S, part, logpsi, eloc, es, nsplit, st);
   }
 }
 
 template <int N, int K, int M>
 hipError_t run_prec(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                    double* logpsi, double* eloc, int es, hipStream_t st) {
+                    double* logpsi, double* eloc, int es, int nsplit, hipStream_t st) {
   switch (c->prec) {
-    case NQS_FP64: return run_if_fits<N, NQS_FP64, K, M>(c, spins, S, part, logpsi, eloc, es, st);
+    case NQS_FP64: return run_if_fits<N, NQS_FP64, K, M>(c, spins, S, part, logpsi, eloc, es, nsplit, st);
     case NQS_FP32:
       // theta from the three-term BF16 split of W (site-grouped) where its
       // fragments fit in LDS
       if constexpr (N % 4 == 0 && FusedCfg<N, kPrecF32S3, K, M, false>::LDS <= kLdsLimit)
-        return run_if_fits<N, kPrecF32S3, K, M>(c, spins, S, part, logpsi, eloc, es, st);
+        return run_if_fits<N, kPrecF32S3, K, M>(c, spins, S, part, logpsi, eloc, es, nsplit, st);
       else if constexpr (FusedCfg<N, kPrecF32X3, K, M, false>::LDS <= kLdsLimit)
-        return run_if_fits<N, kPrecF32X3, K, M>(c, spins, S, part, logpsi, eloc, es, st);
+        return run_if_fits<N, kPrecF32X3, K, M>(c, spins, S, part, logpsi, eloc, es, nsplit, st);
       else
-        return run_if_fits<N, NQS_FP32, K, M>(c, spins, S, part, logpsi, eloc, es, st);
-    default: return run_if_fits<N, NQS_BF16X2, K, M>(c, spins, S, part, logpsi, eloc, es, st);
+        return run_if_fits<N, NQS_FP32, K, M>(c, spins, S, part, logpsi, eloc, es, nsplit, st);
+    default: return run_if_fits<N, NQS_BF16X2, K, M>(c, spins, S, part, logpsi, eloc, es, nsplit, st);
   }
 }
 
@@ -480,10 +480,10 @@ bool fits(int prec) {
 
 hipError_t launch_fused_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                const double* part, double* logpsi, double* eloc, int eloc_stride,
-                               hipStream_t st) {
+                               hipStream_t st, bool split) {
   if (S <= 0) return hipSuccess;
   fused_finish_kernel<<<(unsigned)S, 64, 0, st>>>(
-      spins, c->N, c->NB, c->G / 16 * wide_nsplit(c, S), c->dev.bonds, c->dev.bond_J, part, logpsi,
+      spins, c->N, c->NB, c->G / 16 * (split ? wide_nsplit(c, S) : 1), c->dev.bonds, c->dev.bond_J, part, logpsi,
       eloc, eloc_stride);
   return hipGetLastError();
 }
@@ -499,14 +499,20 @@ bool eloc_fused_supported(const nqs_ctx* c) {
 }
 
 hipError_t launch_eloc_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                             double* logpsi, double* eloc, int eloc_stride, hipStream_t st) {
+                             double* logpsi, double* eloc, int eloc_stride, hipStream_t st,
+                             bool split) {
   if (S <= 0) return hipSuccess;
-  const int N = c->N, K = c->K, M = c->M;
-  if (N == 16 && K == 1 && M == 16) return run_prec<16, 1, 16>(c, spins, S, part, logpsi, eloc, eloc_stride, st);
-  if (N == 16 && K == 2 && M == 8) return run_prec<16, 2, 8>(c, spins, S, part, logpsi, eloc, eloc_stride, st);
-  if (N == 36 && K == 1 && M == 72) return run_prec<36, 1, 72>(c, spins, S, part, logpsi, eloc, eloc_stride, st);
-  if (N == 36 && K == 2 && M == 16) return run_prec<36, 2, 16>(c, spins, S, part, logpsi, eloc, eloc_stride, st);
-  if (N == 36 && K == 1 && M == 16) return run_prec<36, 1, 16>(c, spins, S, part, logpsi, eloc, eloc_stride, st);
+  const int N = c->N, K = c->K, M = c->M, nsplit = split ? fused_nsplit(c, S) : 1;
+  if (N == 16 && K == 1 && M == 16)
+    return run_prec<16, 1, 16>(c, spins, S, part, logpsi, eloc, eloc_stride, nsplit, st);
+  if (N == 16 && K == 2 && M == 8)
+    return run_prec<16, 2, 8>(c, spins, S, part, logpsi, eloc, eloc_stride, nsplit, st);
+  if (N == 36 && K == 1 && M == 72)
+    return run_prec<36, 1, 72>(c, spins, S, part, logpsi, eloc, eloc_stride, nsplit, st);
+  if (N == 36 && K == 2 && M == 16)
+    return run_prec<36, 2, 16>(c, spins, S, part, logpsi, eloc, eloc_stride, nsplit, st);
+  if (N == 36 && K == 1 && M == 16)
+    return run_prec<36, 1, 16>(c, spins, S, part, logpsi, eloc, eloc_stride, nsplit, st);
   return hipErrorNotSupported;
 }
 

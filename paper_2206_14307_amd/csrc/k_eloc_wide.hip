@@ -490,8 +490,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
 
 template <int N, int PREC>
 hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, hipStream_t st,
-               const int16_t* parent, double* Lout) {
-  const int nsplit = parent ? 1 : wide_nsplit(c, S);
+               const int16_t* parent, double* Lout, bool split) {
+  const int nsplit = split ? wide_nsplit(c, S) : 1;
   const int64_t n_cu = c->n_cu > 0 ? c->n_cu : 256, items = S * (c->G / 16) * nsplit;
   // fewer items than wavefront slots: the same number in every workgroup
   const int per = (int)std::min<int64_t>(kWideWaves, (items + n_cu - 1) / n_cu);
@@ -531,29 +531,29 @@ int wide_nsplit(const nqs_ctx* c, int64_t S) {
 
 namespace {
 hipError_t dispatch(const nqs_ctx* c, const int8_t* spins, int64_t S, const int16_t* parent,
-                    double* part, double* Lout, hipStream_t st) {
+                    double* part, double* Lout, bool split, hipStream_t st) {
   if (S <= 0) return hipSuccess;
   const bool bf = c->prec == NQS_BF16X2;
   switch (c->N) {
-    case 36: return bf ? run<36, NQS_BF16X2>(c, spins, S, part, st, parent, Lout)
-                       : run<36, kPrecF32X3>(c, spins, S, part, st, parent, Lout);
-    case 64: return bf ? run<64, NQS_BF16X2>(c, spins, S, part, st, parent, Lout)
-                       : run<64, kPrecF32X3>(c, spins, S, part, st, parent, Lout);
-    case 100: return bf ? run<100, NQS_BF16X2>(c, spins, S, part, st, parent, Lout)
-                        : run<100, kPrecF32X3>(c, spins, S, part, st, parent, Lout);
+    case 36: return bf ? run<36, NQS_BF16X2>(c, spins, S, part, st, parent, Lout, split)
+                       : run<36, kPrecF32X3>(c, spins, S, part, st, parent, Lout, split);
+    case 64: return bf ? run<64, NQS_BF16X2>(c, spins, S, part, st, parent, Lout, split)
+                       : run<64, kPrecF32X3>(c, spins, S, part, st, parent, Lout, split);
+    case 100: return bf ? run<100, NQS_BF16X2>(c, spins, S, part, st, parent, Lout, split)
+                        : run<100, kPrecF32X3>(c, spins, S, part, st, parent, Lout, split);
     default: return hipErrorNotSupported;
   }
 }
 }  // namespace
 
 hipError_t launch_eloc_wide(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                            hipStream_t st, double* Lout) {
-  return dispatch(c, spins, S, nullptr, part, Lout, st);
+                            hipStream_t st, double* Lout, bool split) {
+  return dispatch(c, spins, S, nullptr, part, Lout, split, st);
 }
 
 hipError_t launch_eloc_wide_pairs(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                   const int16_t* parent, double* part, hipStream_t st) {
-  return dispatch(c, spins, S, parent, part, nullptr, st);
+  return dispatch(c, spins, S, parent, part, nullptr, false, st);
 }
 
 }  // namespace nqs

@@ -159,7 +159,8 @@ hipError_t launch_eloc_rows(const nqs_ctx* c, const int8_t* spins, int64_t S, co
 hipError_t launch_eloc_bonds_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                                  const void* w, double* partial, hipStream_t st);
 // Fused theta + epilogue + bond exchanges (K*M <= 128 register-resident
-// variants); part holds S * (G/16) * fused_nsplit * 6 doubles.
+// variants); part holds S * (G/16) * fused_nsplit * 6 doubles.  Here and below,
+// split = false keeps one share: sums in an order that does not depend on S.
 int fused_nsplit(const nqs_ctx* c, int64_t S);
 size_t fused_max_split_items(const nqs_ctx* c);   // most work items of a split launch
 bool eloc_fused_supported(const nqs_ctx* c);
@@ -169,17 +170,18 @@ bool eloc_wide_supported(const nqs_ctx* c);
 // Lout (optional): the per-image log amplitudes [S][K][G], unreduced (four
 // reals each, see launch_lse), for a gradient pass on the same configurations
 hipError_t launch_eloc_wide(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                            hipStream_t st, double* Lout = nullptr);
+                            hipStream_t st, double* Lout = nullptr, bool split = true);
 // shares of the bond list per (configuration, column block) in a launch of S configurations
 int wide_nsplit(const nqs_ctx* c, int64_t S);
 // combines the partials of launch_eloc_wide
 hipError_t launch_fused_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                const double* part, double* logpsi, double* eloc, int eloc_stride,
-                               hipStream_t st);
+                               hipStream_t st, bool split = true);
 hipError_t launch_grad_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, void* O,
                              double* logpsi, hipStream_t st);
 hipError_t launch_eloc_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                             double* logpsi, double* eloc, int eloc_stride, hipStream_t st);
+                             double* logpsi, double* eloc, int eloc_stride, hipStream_t st,
+                             bool split = true);
 hipError_t launch_eloc_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                               const double* partial, double* eloc_out, int eloc_stride,
                               hipStream_t st);
