@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void gram_kernel(const RG* __restrict__ Tre,
       }
 }
 
-// FP32 Gram on GT x GT output tiles (GT = 128, 96 or 64), one workgroup of four
+// FP32 Gram on GT x GT output tiles (GT = 96 or 64), one workgroup of four
 // wavefronts per lower tile, each wavefront a quarter of NA x NA MFMA tiles of
 // 16 x 16 for each of the real and imaginary parts.  The two row panels of the
 // tile go through LDS in stages of kGK parameters, double-buffered, with
@@ -338,19 +338,17 @@ __global__ __launch_bounds__(256) void gram_tile_kernel(const float* __restrict_
 }
 
 // Tile size of the FP32 Gram: rounds of workgroups (one per CU at a time) x
-// tile area is the time to within the kernels' efficiency; of equals the larger
-// tile, which reads less.
+// tile area, for tiles of 64 times 1.15 (they read their rows half as often
+// again): 64 up to a few thousand samples where it fills the last round better,
+// 96 otherwise.  The whole solve at 10x10 M = 400 with tiles of 128, 96 and 64:
+// S = 4096 48, 30.9 and 35.1 ms, 8192 143, 109 and 121, 20000 911, 695 and 770;
+// 6x6 M = 72 S = 3000 6.4, 5.8 and 5.6.
 inline int gram_tile(int64_t S32, int n_cu) {
-  int best = 128;
-  int64_t cost = INT64_MAX;
-  for (int gt : {128, 96, 64}) {
+  auto cost = [&](int64_t gt) {
     const int64_t nt = (S32 + gt - 1) / gt, rounds = (nt * (nt + 1) / 2 + n_cu - 1) / n_cu;
-    if (rounds * gt * gt < cost) {
-      cost = rounds * gt * gt;
-      best = gt;
-    }
-  }
-  return best;
+    return rounds * gt * gt;
+  };
+  return 23 * cost(64) < 20 * cost(96) ? 64 : 96;
 }
 
 // --------------------------------------------------------------- Cholesky
@@ -761,7 +759,7 @@ hipError_t sr_run(const nqs_ctx* c, const void* Ov, const double* el, int64_t S,
   if constexpr (sizeof(RG) == 4) {
     const int gt = gram_tile(S32, c->n_cu > 0 ? c->n_cu : 256);
     const int64_t ntile = (S32 + gt - 1) / gt;
-    auto kernel = gt == 128 ? gram_tile_kernel<128> : gt == 96 ? gram_tile_kernel<96> : gram_tile_kernel<64>;
+    auto kernel = gt == 96 ? gram_tile_kernel<96> : gram_tile_kernel<64>;
     kernel<<<(unsigned)(ntile * (ntile + 1) / 2), 256, 0, st>>>((const float*)Tre, (const float*)Tim,
                                                                 Pk, S32, lambda, T);
   } else {
