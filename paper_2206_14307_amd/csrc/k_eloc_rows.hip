@@ -12,7 +12,7 @@
 //
 // Bound: VALU issue of the factors F prod_h (s + t_h T_h), 8 instructions each,
 // 132 per pair of bonds and chunk with the two addresses and signs.  At 8x8
-// M = 128, 2003 configurations: 4.3 ms (0.81 of the issue bound) where a kernel
+// M = 128, 2003 configurations: 4.3 ms (a VALU instruction in 3.9 cycles) where a kernel
 // that reads every T row from L2 per (image, bond) took 18.6 ms, and one whose
 // eight wavefronts share a configuration 4.7 ms; nqs_eloc at 10x10 M = 104, 500
 // configurations 8.4, 2.9 and 2.7 ms; 6x6 K = 3 M = 24, 3000 configurations 4.2,

@@ -22,15 +22,16 @@
 // the fused kernel, combined by its finish kernel.
 //
 // Bound: VALU issue of the factors, 8 instructions per (image, bond, unit) and
-// 4 or 5 per pair of bonds and chunk for the row addresses and signs.  10x10
-// M = 400, 1500 configurations: 20.5 ms, 0.97 of the issue rate, where eight
-// wavefronts on the blocks of one configuration (7 rounds for 50 blocks) and 18
-// bonds a lane, so theta three times per image, took 28.3 ms; 8x8 K = 4 M = 256,
-// 1000 configurations 17.3 -> 14.9 ms; one 10x10 configuration, its lists in
-// eight shares, 4.4 -> 0.27 ms.  Every product has the same factors in the same
-// order.  theta of the next chunk in half of the wavefronts before the bond
-// products, in the others after them, gave 2-4 % at 6x6 and 8x8 and lost 1 % at
-// 10x10 in split BF16 and 3-8 % in calls of a few configurations: not used.
+// 4 or 5 per pair of bonds and chunk for the row addresses and signs; counters
+// put a SIMD at one VALU instruction in 3.5 cycles.  10x10 M = 400, 1500
+// configurations: 20.5 ms, where eight wavefronts on the blocks of one
+// configuration (7 rounds for 50 blocks) and 18 bonds a lane, so theta three
+// times per image, took 28.3 ms; 8x8 K = 4 M = 256, 1000 configurations 17.3 ->
+// 14.9 ms; one 10x10 configuration, its lists in eight shares, 4.4 -> 0.27 ms.
+// Every product has the same factors in the same order.  theta of the next
+// chunk in half of the wavefronts before the bond products, in the others after
+// them, gave 2-4 % at 6x6 and 8x8 and lost 1 % at 10x10 in split BF16 and 3-8 %
+// in calls of a few configurations: not used.
 #include "theta_common.h"
 #include "hops.h"
 
