@@ -564,7 +564,8 @@ hipError_t launch_eloc_bonds_reg(const nqs_ctx* c, const int8_t* spins, int64_t 
 bool twohop_reg_supported(const nqs_ctx* c) {
   if (c->K != 1) return false;
   if (c->prec == NQS_FP64) return twohop16_supported(c);
-  return (c->N == 16 && c->M == 16) || (c->N == 36 && c->M == 72);
+  // its rows are placed by the fused kernel's maps
+  return ((c->N == 16 && c->M == 16) || (c->N == 36 && c->M == 72)) && eloc_fused_supported(c);
 }
 
 hipError_t launch_twohop_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,

@@ -2,7 +2,7 @@
 chains' caches, as many as the acceptance rate and the LDS for their ratios
 allow.  Chains with high, middle and low acceptance (passes that follow
 acceptances or rejections, with exchanges left pending), with room for four,
-three, two and one proposals (by K, FP32 and FP64), across the cache refresh
+three, two and one proposals (by K; FP64 decides one in a pass), across the cache refresh
 after 256 proposals and up to a proposal count that leaves a partial pass,
 replay the oracle's trajectories; a decision may differ only after a near-tie."""
 import numpy as np
