@@ -309,14 +309,13 @@ __global__ __launch_bounds__(256) void twohop_kernel(
   }
 }
 
-// e2 = diag e1 + sum over (first-hop slot, tile) partials, or over n_part
-// partials per configuration if n_part > 0; e1e2 holds e1 on entry.
+// e2 = diag e1 + sum over (first-hop slot, tile) partials; e1e2 holds e1 on entry.
 __global__ __launch_bounds__(64) void twohop_finish_kernel(const int8_t* __restrict__ spins, int N,
                                                            int NB, int ntiles,
                                                            const int32_t* __restrict__ bonds,
                                                            const double* __restrict__ bond_J,
                                                            const double* __restrict__ partial2,
-                                                           int n_part, double* __restrict__ e1e2) {
+                                                           double* __restrict__ e1e2) {
   __shared__ int16_t list[kMaxBonds];
   const int64_t s = blockIdx.x;
   const int lane = threadIdx.x;
@@ -324,10 +323,9 @@ __global__ __launch_bounds__(64) void twohop_finish_kernel(const int8_t* __restr
   const int nc = build_anti_list(srow, bonds, NB, list, lane);
   const double d = diag_of(srow, bonds, bond_J, NB, lane);
   double pr = 0.0, pi = 0.0;
-  const int n = n_part > 0 ? n_part : nc * ntiles;
+  const int n = nc * ntiles;
   for (int i = lane; i < n; i += 64) {
-    const size_t o = n_part > 0 ? (size_t)s * n_part + i
-                                : ((size_t)s * NB + i / ntiles) * ntiles + (i % ntiles);
+    const size_t o = ((size_t)s * NB + i / ntiles) * ntiles + (i % ntiles);
     pr += partial2[2 * o];
     pi += partial2[2 * o + 1];
   }
@@ -476,9 +474,7 @@ hipError_t launch_twohop_finish(const nqs_ctx* c, const int8_t* spins, int64_t S
                                 const double* partial2, double* e1e2, hipStream_t st) {
   if (S <= 0) return hipSuccess;
   twohop_finish_kernel<<<(unsigned)S, 64, 0, st>>>(spins, c->N, c->NB, c->G / 32, c->dev.bonds,
-                                                   c->dev.bond_J, partial2,
-                                                   twohop16_supported(c) ? twohop16_parts(c, S) : 0,
-                                                   e1e2);
+                                                   c->dev.bond_J, partial2, e1e2);
   return hipGetLastError();
 }
 

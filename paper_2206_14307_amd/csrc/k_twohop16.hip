@@ -5,7 +5,9 @@
 // the image's ratio is F1 F2 prod_h A_h (s2 + T2_h Q_h), A = s1 + t T1,
 // Q = (s1 t + T1) / A.  A wavefront takes 32 images of one configuration, two
 // lanes each (halves of the hidden units) with t in registers, and walks a
-// share of the first hops; Q and prod A are formed once per first hop.  With 64
+// share of the first hops; Q and prod A are formed once per first hop.  Each
+// first hop leaves a partial of its own, so that e2 is summed in one order
+// whatever the shares.  With 64
 // bonds the antiparallel bonds and the unordered-pair list are bit masks in
 // scalar registers (one vote each), so a pair of second hops costs the lane its
 // M factors of 8 instructions and about 30 more.
@@ -86,7 +88,6 @@ __global__ __launch_bounds__(64 * kWaves16, 3) void twohop16_kernel(
       tr[h] = v.x;
       ti[h] = v.y;
     }
-    double accr = 0.0, acci = 0.0;
     for (int n = 0; l1 != 0; l1 &= l1 - 1, ++n) {
       if ((n & (parts - 1)) != share) continue;
       const int b1 = __builtin_ctzll(l1);
@@ -191,14 +192,14 @@ __global__ __launch_bounds__(64 * kWaves16, 3) void twohop16_kernel(
       const double jj = half ? 0.0 : 0.25 * J1 * J1, dg = half ? 0.0 : diag2;
       sr = fma(dg, pa.x, sr);
       si = fma(dg, pa.y, si);
-      accr += fma(g1.x, sr, fma(-g1.y, si, jj * wg.x));
-      acci += fma(g1.x, si, fma(g1.y, sr, jj * wg.y));
-    }
-    accr = wave_sum(accr);
-    acci = wave_sum(acci);
-    if (lane == 0) {
-      part[2 * item] = accr;
-      part[2 * item + 1] = acci;
+      double er = fma(g1.x, sr, fma(-g1.y, si, jj * wg.x));
+      double ei = fma(g1.x, si, fma(g1.y, sr, jj * wg.y));
+      // the sum over the lanes, real part in lanes 0..31 and imaginary in 32..63
+      swap32(er, ei);
+      er += ei;
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) er += __shfl_xor(er, o, 64);
+      if ((lane & 31) == 0) part[2 * ((s * kNB16 + n) * 4 + (sub & 3)) + half] = er;
     }
   }
 }
@@ -206,10 +207,13 @@ __global__ __launch_bounds__(64 * kWaves16, 3) void twohop16_kernel(
 template <int M>
 hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t, const void* w,
                double* part, hipStream_t st) {
-  const int parts = twohop16_parts(c, S) / 4;
+  // shares of the first hops, a power of two: enough to give every SIMD four
+  // wavefronts, at most one for each bond
+  const int64_t n_cu = c->n_cu > 0 ? c->n_cu : 256;
+  int parts = 1;
+  while (parts < kNB16 && S * 4 * parts < 32 * n_cu) parts *= 2;
   const int64_t items = S * 4 * parts;
-  const int64_t blocks = std::min<int64_t>((items + kWaves16 - 1) / kWaves16,
-                                           3 * (int64_t)(c->n_cu > 0 ? c->n_cu : 256));
+  const int64_t blocks = std::min<int64_t>((items + kWaves16 - 1) / kWaves16, 3 * n_cu);
   twohop16_kernel<M><<<(unsigned)blocks, 64 * kWaves16, 0, st>>>(
       spins, S, c->dev.bonds, c->dev.bond_J, c->dev.bmap, (const double2*)t, (const double2*)w,
       (const double2*)c->par.Tpm, (const double2*)c->par.F, part, __builtin_ctz(parts), c->direct_only ? 0 : 1);
@@ -220,14 +224,6 @@ hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t, 
 
 bool twohop16_supported(const nqs_ctx* c) {
   return c->prec == NQS_FP64 && c->N == 16 && c->K == 1 && (c->M == 8 || c->M == 16);
-}
-
-// Four image tiles x shares of the first hops: enough shares (a power of two)
-// to give every SIMD four wavefronts.
-int twohop16_parts(const nqs_ctx* c, int64_t S) {
-  int parts = 1;
-  while (parts < 32 && S * 4 * parts < 32 * (int64_t)(c->n_cu > 0 ? c->n_cu : 256)) parts *= 2;
-  return 4 * parts;
 }
 
 hipError_t launch_twohop16(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,

@@ -190,11 +190,10 @@ hipError_t launch_twohop(const nqs_ctx* c, const int8_t* spins, int64_t S, const
                          const void* w, double* partial2, hipStream_t st);
 hipError_t launch_twohop_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                              const void* w, double* partial2, hipStream_t st);
-// The 4x4 FP64 two-hop kernel: twohop16_parts partials per configuration.
+// The 4x4 FP64 two-hop kernel (partials as above; its tiles are other images).
 bool twohop16_supported(const nqs_ctx* c);
-int twohop16_parts(const nqs_ctx* c, int64_t S);
 hipError_t launch_twohop16(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
-                           const void* w, double* part, hipStream_t st);
+                           const void* w, double* partial2, hipStream_t st);
 hipError_t launch_twohop_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                 const double* partial2, double* e1e2, hipStream_t st);
 hipError_t launch_moments(const double* e1e2, const double* logpsi, int64_t S, int exact,
