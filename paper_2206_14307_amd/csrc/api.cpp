@@ -64,10 +64,12 @@ bool composed_moments(const nqs_ctx* c, int op) {
          (eloc_fused_supported(c) || eloc_wide_supported(c));
 }
 size_t fused_part_bytes(const nqs_ctx* c) { return (size_t)(c->G / 16) * 6 * 8; }
-// of ch configurations, at most ch of them in one launch: a small launch of the
-// fused kernel splits its bond lists over at most its wavefront slots
+// of ch configurations, at most ch of them in one launch: a small launch shares
+// out its bond lists
 size_t part_bytes(const nqs_ctx* c, int64_t ch) {
-  return std::max(fused_part_bytes(c) * (size_t)ch, fused_max_split_items(c) * 6 * 8);
+  return std::max(fused_part_bytes(c) * (size_t)ch,
+                  eloc_fused_supported(c) ? fused_split_part_bytes(c, ch)
+                                          : fused_max_split_items(c) * 6 * 8);
 }
 // nqs_eloc_grad shares the per-image log amplitudes of the wide E_loc kernel
 // with the wide gradient kernel (no theta pass of its own)
@@ -122,6 +124,7 @@ struct Work {
   void* w = nullptr;
   void* t = nullptr;
   double* partial = nullptr;
+  size_t partial_cap = 0;          // bytes of partial (fused and wide E_loc)
   double* partial2 = nullptr;
   double* e1e2 = nullptr;
   double* logpsi = nullptr;
@@ -158,7 +161,8 @@ Work plan(const nqs_ctx* c, int op, int64_t S, void* ws) {
     ch = std::max<int64_t>(std::min<int64_t>(ch, std::max<int64_t>(S, 1) * c->NB), c->NB);
     wk.chunk = ch;
     wk.n_out = std::max<int64_t>(1, ch / c->NB);
-    wk.partial = (double*)cv.take(part_bytes(c, ch));
+    wk.partial_cap = part_bytes(c, ch);
+    wk.partial = (double*)cv.take(wk.partial_cap);
     wk.nb_spins = (int8_t*)cv.take((size_t)ch * c->N);
     wk.nb_lp = (double*)cv.take((size_t)ch * 16);
     wk.nb_e1e2 = (double*)cv.take((size_t)ch * 32);
@@ -177,7 +181,8 @@ Work plan(const nqs_ctx* c, int op, int64_t S, void* ws) {
   const int64_t ch = chunk_of(c, op, S);
   wk.chunk = ch;
   if (op == NQS_OP_ELOC_GRAD) {
-    wk.partial = (double*)cv.take(part_bytes(c, ch));
+    wk.partial_cap = part_bytes(c, ch);
+    wk.partial = (double*)cv.take(wk.partial_cap);
     wk.L = (double*)cv.take(2 * z.L * ch);
     wk.w = cv.take(z.w * ch);
     wk.lp = (double*)cv.take((size_t)16 * ch);
@@ -187,7 +192,8 @@ Work plan(const nqs_ctx* c, int op, int64_t S, void* ws) {
   }
   if (fused_grad(c, op)) return wk;
   if (fused_eloc(c, op)) {
-    wk.partial = (double*)cv.take(part_bytes(c, ch));
+    wk.partial_cap = part_bytes(c, ch);
+    wk.partial = (double*)cv.take(wk.partial_cap);
     wk.lp = (double*)cv.take((size_t)16 * ch);
     wk.bytes = cv.off;
     return wk;
@@ -567,19 +573,19 @@ nqs_status nqs_logpsi(nqs_ctx* c, const int8_t* spins, int64_t S, double* logpsi
 
 namespace {
 // log psi and E_loc of n configurations with the fused (K*M <= 128) or wide
-// kernel; part holds the per-(configuration, 16-image block) partials.  The bond
-// lists are not split over wavefronts: a configuration's sums have one order,
-// whatever the call and the neighbour chunk that hold it.
-hipError_t eloc_fused_any(nqs_ctx* c, const int8_t* sp, int64_t n, double* part, double* lp,
+// kernel.  The wide kernel's bond lists are not split over wavefronts here: a
+// configuration's sums have one order, whatever the call and the neighbour chunk
+// that hold it.
+hipError_t eloc_fused_any(nqs_ctx* c, const Work& wk, const int8_t* sp, int64_t n, double* lp,
                           double* eloc, int eloc_stride, hipStream_t st) {
   if (eloc_fused_supported(c))
-    return NQS_RUN(c, K_ELOC, st,
-                   launch_eloc_fused(c, sp, n, part, lp, eloc, eloc_stride, st, false));
+    return NQS_RUN(c, K_ELOC, st, launch_eloc_fused(c, sp, n, wk.partial, wk.partial_cap, lp, eloc,
+                                                    eloc_stride, st));
   hipError_t e =
-      NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, part, st, nullptr, false));
+      NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, wk.partial, st, nullptr, false));
   if (e == hipSuccess)
     e = NQS_RUN(c, K_ELOC_FIN, st,
-                launch_fused_finish(c, sp, n, part, lp, eloc, eloc_stride, st, false));
+                launch_fused_finish(c, sp, n, wk.partial, lp, eloc, eloc_stride, st, false));
   return e;
 }
 
@@ -629,7 +635,8 @@ nqs_status nqs_eloc(nqs_ctx* c, const int8_t* spins, int64_t S, double* logpsi_o
     hipError_t e;
     if (fused && eloc_fused_supported(c)) {
       e = NQS_RUN(c, K_ELOC, st,
-                  launch_eloc_fused(c, sp, n, wk.partial, lp, eloc_out + 2 * s0, 2, st));
+                  launch_eloc_fused(c, sp, n, wk.partial, wk.partial_cap, lp, eloc_out + 2 * s0, 2,
+                                    st));
     } else if (fused) {
       e = NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, wk.partial, st));
       if (e == hipSuccess)
@@ -663,7 +670,7 @@ nqs_status nqs_lanczos_moments(nqs_ctx* c, const int8_t* spins, int64_t S, int e
     // wide models: each neighbour's bond list is its parent's unordered-pair
     // list and the neighbours contribute path sums (no division by their psi)
     const bool pairs = !eloc_fused_supported(c);
-    e = eloc_fused_any(c, sp, n, wk.partial, lp, e12, 4, st);
+    e = eloc_fused_any(c, wk, sp, n, lp, e12, 4, st);
     int32_t total = 0;
     if (e == hipSuccess) e = expand_neighbours(c, wk, sp, n, &total, st, pairs ? wk.nb_parent : nullptr);
     if (e == hipErrorInvalidValue)
@@ -682,7 +689,7 @@ nqs_status nqs_lanczos_moments(nqs_ctx* c, const int8_t* spins, int64_t S, int e
                                        e12 + 2, 4, st, 1));
     } else {
       if (e == hipSuccess && total > 0)
-        e = eloc_fused_any(c, wk.nb_spins, total, wk.partial, wk.nb_lp, wk.nb_e1e2, 4, st);
+        e = eloc_fused_any(c, wk, wk.nb_spins, total, wk.nb_lp, wk.nb_e1e2, 4, st);
       if (e == hipSuccess)
         e = NQS_RUN(c, K_HOP3, st,
                     launch_hop_combine(c, sp, n, wk.nb_off, lp, e12, 4, wk.nb_lp, wk.nb_e1e2, 4,

@@ -21,9 +21,12 @@
 // the column blocks: log psi = M + log sum e^{m-M} den,
 // E_loc = diag + sum e^{m-M} Q / sum e^{m-M} den.
 //
-// Few work items (small calls) are split further, into shares of the bond list
-// (SPLIT), so that the launch fills the device; each share emits its own
-// partial.
+// The passes of a bond list fall into fused_units units, each summed on its own, the
+// units' sums added in order.  Few work items (small calls) are split further,
+// into shares of one or more units (SPLIT), so that the launch fills the device:
+// the shares store the units' sums and the finish kernel adds and weights them
+// as an unsplit wavefront does, so a configuration's results are the same bits
+// whatever the call that holds it.
 //
 // Persistent workgroups keep the bond rows and the W fragments in LDS for the
 // whole launch; the rows are placed (host side) so that the 16 images of a q
@@ -110,6 +113,33 @@ __device__ __forceinline__ void qprod_pair(R& pr, R& pi, R orr, R oi) {
   pi = vr * wi + vi * wr;
 }
 
+// q += u Q (weight of an image, its sum over the bonds); explicit FMAs, so that
+// both users round alike
+__device__ __forceinline__ void weigh(double ur, double ui, double Qr, double Qi, double& qr,
+                                      double& qi) {
+  qr = fma(ur, Qr, fma(-ui, Qi, qr));
+  qi = fma(ur, Qi, fma(ui, Qr, qi));
+}
+
+// Units of a bond list: six passes each at 6x6 (37 in the mean), five at 4x4
+// (17).  More of them cost the unsplit loop (14 at 6x6 1 %), fewer leave a small
+// call's wavefronts with longer shares.
+__host__ __device__ constexpr int fused_units(int N) { return N == 16 ? 4 : 7; }
+
+// Partials of a split launch of n blocks (configuration, 16 images): heads as in
+// an unsplit one, [n][6] doubles, without the bond sums; the units' sums
+// [n][units][K][32] (lanes 0..31; the others hold the same values); the image
+// weights u [n][K][16].
+template <typename R>
+struct SplitPart {
+  double* head;
+  double2* sum;
+  c2_t<R>* u;
+  __device__ SplitPart(double* p, int64_t n, int units, int K)
+      : head(p), sum(reinterpret_cast<double2*>(p + 6 * n)),
+        u(reinterpret_cast<c2_t<R>*>(sum + n * units * K * 32)) {}
+};
+
 template <int N, int PREC, int K, int M, bool RECIP, bool SPLIT>
 __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
     const int8_t* __restrict__ spins, int64_t S, int nsplit, const uint8_t* __restrict__ perm,
@@ -124,7 +154,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
   using R = typename T::R;
   using AF = typename T::AFrag;
   constexpr int NB = Cfg::NB, KM = Cfg::KM, NHT = Cfg::NHT, NK = Cfg::NK;
-  constexpr int ROW = Cfg::ROW;
+  constexpr int ROW = Cfg::ROW, kUnits = fused_units(N);
   constexpr int TPR = M / 8;
   __shared__ __align__(16) R Tl[Cfg::CAP];
   __shared__ __align__(16) AF Wl[NHT * NK * 64];
@@ -158,6 +188,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
   // over the CUs; (s, cb) advance by the stride without a division
   const int cbs = G / 16;
   const int64_t n_items = S * cbs * (SPLIT ? nsplit : 1);
+  const SplitPart<R> sp(part, S * cbs, kUnits, K);
   const int64_t stride = (int64_t)gridDim.x * kFusedWaves;
   uint16_t* list = lists[wv];
   int64_t item = (int64_t)wv * gridDim.x + blockIdx.x;
@@ -185,6 +216,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
       cb -= cbs;
       ++s;
     }
+    const int64_t ib = s * cbs + cb;
     const int g = cb * 16 + c;
     const int8_t* srow = spins + s * N;
     const uint8_t* prow = perm + (size_t)g * N;
@@ -239,13 +271,17 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
 
     // ---- bond exchanges, two bonds per pass; the next pass's map entries
     // are loaded one pass ahead
-    double Qr[K], Qi[K];
+    double Qr[K], Qi[K], Tr[K], Ti[K];     // sums of the unit and of the units before it
 #pragma unroll
-    for (int k = 0; k < K; ++k) Qr[k] = Qi[k] = 0.0;
+    for (int k = 0; k < K; ++k) Qr[k] = Qi[k] = Tr[k] = Ti[k] = 0.0;
     const int32_t* bm = fmap + (size_t)g * NB;
-    // this share's bonds [i_lo, i_hi): whole passes of the list
-    const int per = SPLIT ? 2 * (((nc + 1) / 2 + nsplit - 1) / nsplit) : nc;
-    const int i_lo = SPLIT ? share * per : 0, i_hi = SPLIT ? min(nc, i_lo + per) : nc;
+    // units of `per` list entries; this share's units [unit, unit_hi) and entries
+    const int per = 2 * max(1, ((nc + 1) / 2 + kUnits - 1) / kUnits);
+    const int upw = SPLIT ? (kUnits + nsplit - 1) / nsplit : kUnits;
+    int unit = SPLIT ? share * upw : 0;
+    const int unit_hi = min(kUnits, unit + upw);
+    const int i_lo = SPLIT ? min(nc, unit * per) : 0, i_hi = SPLIT ? min(nc, unit_hi * per) : nc;
+    int next = min(i_lo + per, i_hi);      // end of the unit
     int en[2] = {0, 0}, vn[2] = {0, 0};
     if (i_lo < i_hi) {
 #pragma unroll
@@ -259,7 +295,11 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
       if (i0 + 2 < i_hi) {
 #pragma unroll
         for (int n = 0; n < 2; ++n) {
-          en[n] = list[min(i0 + 2 + n, i_hi - 1)];
+          // (either form of the clamp reads a valid entry: min is 0.4 % faster at
+          // 6x6 M = 72 in FP32, the select 1-4 % elsewhere)
+          en[n] = list[sizeof(R) == 4 && KM >= 64 ? min(i0 + 2 + n, i_hi - 1)
+                       : i0 + 2 + n < i_hi        ? i0 + 2 + n
+                                                  : i0 + 2];
           vn[n] = bm[en[n] & 0x7fff];
         }
       }
@@ -318,17 +358,55 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
         Qr[k] += use ? (double)p0r : 0.0;
         Qi[k] += use ? (double)p0i : 0.0;
       }
+      if (i0 + 2 >= next) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          if constexpr (SPLIT) {
+            if (lane < 32)
+              sp.sum[((ib * kUnits + unit) * K + k) * 32 + lane] = make_double2(Qr[k], Qi[k]);
+          } else {
+            Tr[k] += Qr[k];
+            Ti[k] += Qi[k];
+          }
+          Qr[k] = Qi[k] = 0.0;
+        }
+        next = min(next + per, i_hi);
+        ++unit;
+      }
+    }
+    if constexpr (SPLIT) {
+      for (; unit < unit_hi; ++unit)       // units past the end of the list
+        for (int k = 0; k < K; ++k)
+          if (lane < 32)
+            sp.sum[((ib * kUnits + unit) * K + k) * 32 + lane] = make_double2(0.0, 0.0);
+      if (share == 0) {
+        denr = wave_sum(q == 0 ? denr : 0.0);
+        deni = wave_sum(q == 0 ? deni : 0.0);
+        if (q == 0) {
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            c2_t<R> v;
+            v.x = ur[k];
+            v.y = ui[k];
+            sp.u[(ib * K + k) * 16 + c] = v;
+          }
+        }
+        if (lane == 0) {
+          sp.head[6 * ib] = m;
+          sp.head[6 * ib + 1] = denr;
+          sp.head[6 * ib + 2] = deni;
+        }
+      }
+      wave_sync_lds();
+      continue;
     }
     // every bond was summed twice (rows 0 and 2, or 1 and 3)
     double qr = 0.0, qi = 0.0;
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      qr += (double)ur[k] * Qr[k] - (double)ui[k] * Qi[k];
-      qi += (double)ur[k] * Qi[k] + (double)ui[k] * Qr[k];
-    }
+    for (int k = 0; k < K; ++k) weigh((double)ur[k], (double)ui[k], Tr[k], Ti[k], qr, qi);
     qr *= 0.5;
     qi *= 0.5;
-    if (q != 0 || (SPLIT && share != 0)) {
+    if (q != 0) {
       denr = 0.0;
       deni = 0.0;
     }
@@ -349,60 +427,131 @@ __global__ __launch_bounds__(64 * kFusedWaves) void eloc_fused_kernel(
   }
 }
 
-// Per sample: combine the column blocks into log psi and E_loc.
-__global__ __launch_bounds__(64) void fused_finish_kernel(
-    const int8_t* __restrict__ spins, int N, int NB, int cbs, const int32_t* __restrict__ bonds,
-    const double* __restrict__ bond_J, const double* __restrict__ part, double* __restrict__ logpsi,
-    double* __restrict__ eloc, int eloc_stride) {
-  const int64_t s = blockIdx.x;
-  const int lane = threadIdx.x;
-  const int8_t* srow = spins + s * N;
+// Per sample (one wavefront): combine the column blocks' partials ps [cbs][6]
+// into log psi and E_loc.
+__device__ __forceinline__ void finish_sample(const int8_t* srow, int64_t s, int NB, int cbs,
+                                              const int32_t* bonds, const double* bond_J,
+                                              const double* ps, double* logpsi, double* eloc,
+                                              int eloc_stride, int lane) {
   double d = 0.0;
   for (int b = lane; b < NB; b += 64)
     d += 0.25 * bond_J[b] * (double)(srow[bonds[2 * b]] * srow[bonds[2 * b + 1]]);
   d = wave_sum(d);
-  const double* ps = part + (size_t)s * cbs * 6;
   double mx = -INFINITY;
   for (int i = lane; i < cbs; i += 64) mx = fmax(mx, ps[6 * i]);
   mx = wave_max(mx);
   double dr = 0, di = 0, qr = 0, qi = 0;
   for (int i = lane; i < cbs; i += 64) {
     const double e = exp(ps[6 * i] - mx);
-    dr += e * ps[6 * i + 1];
-    di += e * ps[6 * i + 2];
-    qr += e * ps[6 * i + 3];
-    qi += e * ps[6 * i + 4];
+    dr = fma(e, ps[6 * i + 1], dr);
+    di = fma(e, ps[6 * i + 2], di);
+    qr = fma(e, ps[6 * i + 3], qr);
+    qi = fma(e, ps[6 * i + 4], qi);
   }
   dr = wave_sum(dr);
   di = wave_sum(di);
   qr = wave_sum(qr);
   qi = wave_sum(qi);
   if (lane == 0) {
-    const double den2 = dr * dr + di * di;
+    const double den2 = fma(dr, dr, di * di);
     if (logpsi) {
       logpsi[2 * s] = mx + 0.5 * log(den2);
       logpsi[2 * s + 1] = atan2(di, dr);
     }
-    eloc[(size_t)s * eloc_stride] = d + (qr * dr + qi * di) / den2;
-    eloc[(size_t)s * eloc_stride + 1] = (qi * dr - qr * di) / den2;
+    eloc[(size_t)s * eloc_stride] = d + fma(qr, dr, qi * di) / den2;
+    eloc[(size_t)s * eloc_stride + 1] = fma(qi, dr, -(qr * di)) / den2;
   }
+}
+
+__global__ __launch_bounds__(64) void fused_finish_kernel(
+    const int8_t* __restrict__ spins, int N, int NB, int cbs, const int32_t* __restrict__ bonds,
+    const double* __restrict__ bond_J, const double* __restrict__ part, double* __restrict__ logpsi,
+    double* __restrict__ eloc, int eloc_stride) {
+  const int64_t s = blockIdx.x;
+  finish_sample(spins + s * N, s, NB, cbs, bonds, bond_J, part + (size_t)s * cbs * 6, logpsi, eloc,
+                eloc_stride, threadIdx.x);
+}
+
+// The same after a split launch: half a wavefront first adds up a column block's
+// units (rows 0, 1 of a wavefront; rows 2, 3 hold the same values, so twice the
+// half sum, halved, is the unsplit sum).
+template <typename R, int N, int K>
+__global__ __launch_bounds__(16 * N) void fused_finish_split_kernel(
+    const int8_t* __restrict__ spins, const int32_t* __restrict__ bonds,
+    const double* __restrict__ bond_J, double* __restrict__ part, double* __restrict__ logpsi,
+    double* __restrict__ eloc, int eloc_stride) {
+  constexpr int NB = 4 * N, cbs = N / 2, kUnits = fused_units(N);
+  __shared__ double ps[cbs * 6];
+  const int64_t s = blockIdx.x;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int cb = threadIdx.x >> 5;                 // a block per half wavefront
+  const SplitPart<R> sp(part, (int64_t)gridDim.x * cbs, kUnits, K);
+  const int64_t ib = s * cbs + cb;
+  double2 v[kUnits][K];
+  c2_t<R> u[K];
+#pragma unroll
+  for (int j = 0; j < kUnits; ++j)
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[j][k] = sp.sum[((ib * kUnits + j) * K + k) * 32 + (lane & 31)];
+#pragma unroll
+  for (int k = 0; k < K; ++k) u[k] = sp.u[(ib * K + k) * 16 + (lane & 15)];
+  double qr = 0.0, qi = 0.0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    double Tr = 0.0, Ti = 0.0;
+#pragma unroll
+    for (int j = 0; j < kUnits; ++j) {
+      Tr += v[j][k].x;
+      Ti += v[j][k].y;
+    }
+    weigh((double)u[k].x, (double)u[k].y, Tr, Ti, qr, qi);
+  }
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) {
+    qr += __shfl_xor(qr, o, 64);
+    qi += __shfl_xor(qi, o, 64);
+  }
+  if ((lane & 31) == 0) {
+    ps[6 * cb + 3] = qr;
+    ps[6 * cb + 4] = qi;
+  }
+  if ((lane & 31) < 3) ps[6 * cb + (lane & 31)] = sp.head[6 * ib + (lane & 31)];
+  __syncthreads();
+  if (wv == 0)
+    finish_sample(spins + s * N, s, NB, cbs, bonds, bond_J, ps, logpsi, eloc, eloc_stride, lane);
 }
 
 }  // namespace
 
 // Shares of the bond list per (configuration, column block): where one
-// wavefront each leaves wavefront slots of the persistent grid empty, the
-// bonds are split as far as the slots go (at most eight: every share computes
-// theta again, about five bond passes' worth).  A call of nqs_eloc at 6x6
-// M = 72, with the rows staged eight loads at a time: 16 configurations
-// 56.6 -> 22.0 us (seven shares), one 57 -> 20 us.
+// wavefront each leaves wavefront slots of the persistent grid empty, the units
+// are shared out as far as the slots go (every share computes theta again, about
+// five bond passes' worth), if the partials then fit in cap bytes.  Two shares pay
+// only for the longer products: 56 configurations 39.8 us against 44.3 in one
+// share at 6x6 M = 72, but 55.3 against 47.4 at 6x6 K = 2 M = 16 FP64 and 21.9
+// against 18.4 (128 configurations) at 4x4.  A call of nqs_eloc at 6x6 M = 72
+// with the rows staged eight loads at a time: 16 configurations 54.8 -> 22.4 us
+// (seven shares), one 52 -> 18 us.
 size_t fused_max_split_items(const nqs_ctx* c) {
   return (size_t)kFusedWaves * (c->n_cu > 0 ? c->n_cu : 256);
 }
-int fused_nsplit(const nqs_ctx* c, int64_t S) {
-  const int64_t items = std::max<int64_t>(S, 1) * (c->G / 16);
+static size_t split_bytes(const nqs_ctx* c, int64_t blocks) {
+  const size_t cr = c->prec == NQS_FP64 ? 16 : 8;
+  return (size_t)blocks * (48 + (size_t)c->K * (fused_units(c->N) * 32 * 16 + 16 * cr));
+}
+static int fused_nsplit(const nqs_ctx* c, int64_t S, size_t cap) {
+  const int64_t blocks = std::max<int64_t>(S, 1) * (c->G / 16);
+  if (split_bytes(c, blocks) > cap) return 1;
   const int64_t slots = (int64_t)fused_max_split_items(c);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(8, slots / items));
+  const int units = fused_units(c->N);
+  const int most = (int)std::min<int64_t>(units, slots / blocks);
+  if (most < (c->KM >= 64 ? 2 : 3)) return 1;
+  const int upw = (units + most - 1) / most;      // units of a share
+  return (units + upw - 1) / upw;
+}
+size_t fused_split_part_bytes(const nqs_ctx* c, int64_t S) {
+  const int64_t cbs = c->G / 16, most = (int64_t)fused_max_split_items(c) / 2 / cbs;
+  return split_bytes(c, std::min<int64_t>(S, most) * cbs);
 }
 
 namespace {
@@ -412,8 +561,8 @@ hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, d
                double* eloc, int eloc_stride, int nsplit, hipStream_t st) {
   using T = ThetaTraits<PREC>;
   using R = typename T::R;
-  const int cbs = c->G / 16 * nsplit;
-  const int64_t blocks = std::min<int64_t>(S * cbs, c->n_cu > 0 ? c->n_cu : 256);
+  const int cbs = c->G / 16;
+  const int64_t blocks = std::min<int64_t>(S * cbs * nsplit, c->n_cu > 0 ? c->n_cu : 256);
   auto kernel = nsplit > 1 ? eloc_fused_kernel<N, PREC, K, M, RECIP, true>
                            : eloc_fused_kernel<N, PREC, K, M, RECIP, false>;
   kernel<<<(unsigned)blocks, 64 * kFusedWaves, 0, st>>>(
@@ -426,8 +575,12 @@ hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, d
       (const R*)(RECIP ? c->par.Urec : c->par.Tdir), part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  fused_finish_kernel<<<(unsigned)S, 64, 0, st>>>(spins, c->N, c->NB, cbs, c->dev.bonds,
-                                                  c->dev.bond_J, part, logpsi, eloc, eloc_stride);
+  if (nsplit > 1)
+    fused_finish_split_kernel<R, N, K><<<(unsigned)S, 16 * N, 0, st>>>(
+        spins, c->dev.bonds, c->dev.bond_J, part, logpsi, eloc, eloc_stride);
+  else
+    fused_finish_kernel<<<(unsigned)S, 64, 0, st>>>(spins, c->N, c->NB, cbs, c->dev.bonds,
+                                                    c->dev.bond_J, part, logpsi, eloc, eloc_stride);
   return hipGetLastError();
 }
 
@@ -499,10 +652,10 @@ bool eloc_fused_supported(const nqs_ctx* c) {
 }
 
 hipError_t launch_eloc_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                             double* logpsi, double* eloc, int eloc_stride, hipStream_t st,
-                             bool split) {
+                             size_t part_cap, double* logpsi, double* eloc, int eloc_stride,
+                             hipStream_t st) {
   if (S <= 0) return hipSuccess;
-  const int N = c->N, K = c->K, M = c->M, nsplit = split ? fused_nsplit(c, S) : 1;
+  const int N = c->N, K = c->K, M = c->M, nsplit = fused_nsplit(c, S, part_cap);
   if (N == 16 && K == 1 && M == 16)
     return run_prec<16, 1, 16>(c, spins, S, part, logpsi, eloc, eloc_stride, nsplit, st);
   if (N == 16 && K == 2 && M == 8)

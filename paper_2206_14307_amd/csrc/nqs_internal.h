@@ -159,14 +159,16 @@ hipError_t launch_eloc_rows(const nqs_ctx* c, const int8_t* spins, int64_t S, co
 hipError_t launch_eloc_bonds_reg(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                                  const void* w, double* partial, hipStream_t st);
 // Fused theta + epilogue + bond exchanges (K*M <= 128 register-resident
-// variants); part holds S * (G/16) * fused_nsplit * 6 doubles.  Here and below,
-// split = false keeps one share: sums in an order that does not depend on S.
-int fused_nsplit(const nqs_ctx* c, int64_t S);
+// variants); part holds S * (G/16) * 6 doubles, or part_cap bytes: a launch too
+// small for the device shares out its bond lists if fused_split_part_bytes of it
+// fit.  The sums have one order, whatever S.
+size_t fused_split_part_bytes(const nqs_ctx* c, int64_t S);   // of any launch of at most S
 size_t fused_max_split_items(const nqs_ctx* c);   // most work items of a split launch
 bool eloc_fused_supported(const nqs_ctx* c);
 bool grad_fused_supported(const nqs_ctx* c);
 hipError_t launch_enum_sz0(const nqs_ctx* c, int64_t count, int8_t* out, hipStream_t st);
 bool eloc_wide_supported(const nqs_ctx* c);
+// split = false keeps one share: sums in an order that does not depend on S.
 // Lout (optional): the per-image log amplitudes [S][K][G], unreduced (four
 // reals each, see launch_lse), for a gradient pass on the same configurations
 hipError_t launch_eloc_wide(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
@@ -180,8 +182,8 @@ hipError_t launch_fused_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
 hipError_t launch_grad_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, void* O,
                              double* logpsi, hipStream_t st);
 hipError_t launch_eloc_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                             double* logpsi, double* eloc, int eloc_stride, hipStream_t st,
-                             bool split = true);
+                             size_t part_cap, double* logpsi, double* eloc, int eloc_stride,
+                             hipStream_t st);
 hipError_t launch_eloc_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                               const double* partial, double* eloc_out, int eloc_stride,
                               hipStream_t st);

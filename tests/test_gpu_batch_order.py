@@ -33,3 +33,25 @@ def test_e2_4x4_fp64(M):
     for S in (1, 2, 5, 33, 130, 260, 1030, 2100):
         _, e12 = m.lanczos_moments(sp[:S])
         assert torch.equal(e12, ref[:S]), S
+
+
+@pytest.mark.parametrize("L,K,M,prec", [(6, 1, 72, "fp32"), (6, 1, 72, "bf16x2"),
+                                        (6, 2, 16, "fp32"), (6, 2, 16, "fp64"),
+                                        (6, 1, 16, "bf16x2"), (4, 1, 16, "fp64"),
+                                        (4, 2, 8, "fp32")])
+def test_eloc_fused(L, K, M, prec):
+    """The chunk of 2200 is above every size at which bond lists are shared out."""
+    from paper_2206_14307_amd.nqs import _ptr, _stream
+    m = _model(L, K, M, prec)
+    sp = _rows(L, 2200)
+    lp, el = m.eloc(sp)
+    for S in (1, 2, 3, 7, 16, 37, 56, 57, 113, 128, 129, 300):
+        x = sp[:S].contiguous()
+        l1, e1 = m.eloc(x)
+        assert torch.equal(e1, el[:S]) and torch.equal(l1, lp[:S]), S
+        e2 = torch.empty_like(e1)
+        assert m.lib.nqs_eloc_noalloc(m._ctx, _ptr(x), S, None, _ptr(e2), _stream()) == 0
+        assert torch.equal(e2, e1), S
+        assert torch.equal(m.eloc_grad(x)[1], e1), S
+        if K > 1:
+            assert torch.equal(m.lanczos_moments(x)[1][:, 0], e1), S
