@@ -69,7 +69,7 @@ size_t fused_part_bytes(const nqs_ctx* c) { return (size_t)(c->G / 16) * 6 * 8; 
 size_t part_bytes(const nqs_ctx* c, int64_t ch) {
   return std::max(fused_part_bytes(c) * (size_t)ch,
                   eloc_fused_supported(c) ? fused_split_part_bytes(c, ch)
-                                          : fused_max_split_items(c) * 6 * 8);
+                                          : wide_split_part_bytes(c, ch));
 }
 // nqs_eloc_grad shares the per-image log amplitudes of the wide E_loc kernel
 // with the wide gradient kernel (no theta pass of its own)
@@ -573,19 +573,17 @@ nqs_status nqs_logpsi(nqs_ctx* c, const int8_t* spins, int64_t S, double* logpsi
 
 namespace {
 // log psi and E_loc of n configurations with the fused (K*M <= 128) or wide
-// kernel.  The wide kernel's bond lists are not split over wavefronts here: a
-// configuration's sums have one order, whatever the call and the neighbour chunk
-// that hold it.
+// kernel.
 hipError_t eloc_fused_any(nqs_ctx* c, const Work& wk, const int8_t* sp, int64_t n, double* lp,
                           double* eloc, int eloc_stride, hipStream_t st) {
   if (eloc_fused_supported(c))
     return NQS_RUN(c, K_ELOC, st, launch_eloc_fused(c, sp, n, wk.partial, wk.partial_cap, lp, eloc,
                                                     eloc_stride, st));
   hipError_t e =
-      NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, wk.partial, st, nullptr, false));
+      NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, wk.partial, wk.partial_cap, st));
   if (e == hipSuccess)
     e = NQS_RUN(c, K_ELOC_FIN, st,
-                launch_fused_finish(c, sp, n, wk.partial, lp, eloc, eloc_stride, st, false));
+                launch_fused_finish(c, sp, n, wk.partial, lp, eloc, eloc_stride, st));
   return e;
 }
 
@@ -638,7 +636,7 @@ nqs_status nqs_eloc(nqs_ctx* c, const int8_t* spins, int64_t S, double* logpsi_o
                   launch_eloc_fused(c, sp, n, wk.partial, wk.partial_cap, lp, eloc_out + 2 * s0, 2,
                                     st));
     } else if (fused) {
-      e = NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, wk.partial, st));
+      e = NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, wk.partial, wk.partial_cap, st));
       if (e == hipSuccess)
         e = NQS_RUN(c, K_ELOC_FIN, st,
                     launch_fused_finish(c, sp, n, wk.partial, lp, eloc_out + 2 * s0, 2, st));
@@ -890,7 +888,8 @@ nqs_status nqs_eloc_grad(nqs_ctx* c, const int8_t* spins, int64_t S, double* log
     double* lp = logpsi_out ? logpsi_out + 2 * s0 : wk.lp;
     // E_loc and log psi, the image log amplitudes kept; then the weights and
     // O_k from them
-    hipError_t e = NQS_RUN(c, K_ELOC, st, launch_eloc_wide(c, sp, n, wk.partial, st, wk.L));
+    hipError_t e = NQS_RUN(c, K_ELOC, st,
+                           launch_eloc_wide(c, sp, n, wk.partial, wk.partial_cap, st, wk.L));
     if (e == hipSuccess)
       e = NQS_RUN(c, K_ELOC_FIN, st,
                   launch_fused_finish(c, sp, n, wk.partial, lp, eloc_out + 2 * s0, 2, st));

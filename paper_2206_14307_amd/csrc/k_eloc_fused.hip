@@ -633,11 +633,10 @@ bool fits(int prec) {
 
 hipError_t launch_fused_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                const double* part, double* logpsi, double* eloc, int eloc_stride,
-                               hipStream_t st, bool split) {
+                               hipStream_t st) {
   if (S <= 0) return hipSuccess;
-  fused_finish_kernel<<<(unsigned)S, 64, 0, st>>>(
-      spins, c->N, c->NB, c->G / 16 * (split ? wide_nsplit(c, S) : 1), c->dev.bonds, c->dev.bond_J, part, logpsi,
-      eloc, eloc_stride);
+  fused_finish_kernel<<<(unsigned)S, 64, 0, st>>>(spins, c->N, c->NB, c->G / 16, c->dev.bonds,
+                                                  c->dev.bond_J, part, logpsi, eloc, eloc_stride);
   return hipGetLastError();
 }
 

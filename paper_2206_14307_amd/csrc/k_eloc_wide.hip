@@ -19,7 +19,10 @@
 // At the end of each RBM the products are weighted with the image weights
 // u = chi e^{L - m} (m a running maximum over the RBMs of the wave's images)
 // and summed; the wave emits (m, sum u, sum u R) per item in the same format as
-// the fused kernel, combined by its finish kernel.
+// the fused kernel, combined by its finish kernel.  The shares of a small call
+// store their products instead, and wide_join_kernel sums and weights a block's
+// whole list as an unsplit wavefront does: a configuration's results are the same
+// bits whatever the call that holds it.
 //
 // Bound: VALU issue of the factors, 8 instructions per (image, bond, unit) and
 // 4 or 5 per pair of bonds and chunk for the row addresses and signs; counters
@@ -63,6 +66,56 @@ typedef __attribute__((address_space(3))) const f32x2* lds_f32x2_ptr;
 struct WideRec {
   double Er[16], axi[16], dr[64], di[64];
   float pr[64], pi[64];
+};
+
+// Partials of a split launch of n blocks (configuration, 16 images): the blocks'
+// partials [n][6] (written by the join), the RBMs' results [n][K], the products
+// [n][K][list entry][image].
+struct WideRaw {
+  double Er[16], axi[16];
+  float pr[64], pi[64];
+};
+struct WideSplit {
+  double* part;
+  WideRaw* raw;
+  float2* prod;
+  __device__ WideSplit(double* p, int64_t n, int K)
+      : part(p), raw(reinterpret_cast<WideRaw*>(p + 6 * n)),
+        prod(reinterpret_cast<float2*>(raw + n * K)) {}
+};
+
+// The weighting of an RBM's sums, in explicit operations: the kernel and the join
+// round alike.  m: the running maximum of Re L over the RBMs of the wave's images.
+struct WideSums {
+  double m, Qr, Qi, denr, deni;
+  __device__ __forceinline__ void init() {
+    m = -INFINITY;
+    Qr = Qi = denr = deni = 0.0;
+  }
+  __device__ __forceinline__ void raise(double Er) {
+    const double mk = wave_max(Er);
+    if (mk > m) {
+      const double sc = (double)exp_t((float)(m - mk));   // 0 at the first RBM
+      Qr *= sc; Qi *= sc; denr *= sc; deni *= sc;
+      m = mk;
+    }
+  }
+  // u = chi e^{Er - m} P e^{i axi}
+  __device__ __forceinline__ float2 weight(double Er, double axi, float pr, float pi, float ch) const {
+    const float e = ch * exp_t((float)(Er - m));
+    float sn, cs;
+    sincos_t((float)axi, &sn, &cs);
+    return make_float2(e * fmaf(pr, cs, -(pi * sn)), e * fmaf(pr, sn, pi * cs));
+  }
+  // Q += u (sr + i si)
+  __device__ __forceinline__ void add(float2 u, double sr, double si) {
+    Qr = fma((double)u.x, sr, fma(-(double)u.y, si, Qr));
+    Qi = fma((double)u.x, si, fma((double)u.y, sr, Qi));
+  }
+  __device__ __forceinline__ void count(float2 u) {
+    denr += (double)u.x;
+    deni += (double)u.y;
+  }
 };
 
 // LDS, in bytes: the two staged chunks lie 64 KiB apart, so that a row's
@@ -112,11 +165,27 @@ struct XBits {
   }
 };
 
-// PAIRS: the rows are exchange neighbours with parent bonds (parent[s]); the
+// Pairs: the rows are exchange neighbours with parent bonds (parent[s]); the
 // bond list is the parent's unordered-pair list and pairs counted twice weigh 2.
+// Split: shares of the bond lists, part as WideSplit.
 // Lout: also write the images' log amplitudes, unreduced (see below).
 // per: items of a workgroup in a round (its first `per` wavefronts take them).
-template <int N, int PREC, bool PAIRS>
+// the wavefront's sums to a block's partial
+__device__ __forceinline__ void store_partial(const WideSums& w, double* o, int lane) {
+  const double Qr = wave_sum(w.Qr), Qi = wave_sum(w.Qi);
+  const double denr = wave_sum(w.denr), deni = wave_sum(w.deni);
+  if (lane == 0) {
+    o[0] = w.m;
+    o[1] = denr;
+    o[2] = deni;
+    o[3] = Qr;
+    o[4] = Qi;
+    o[5] = 0.0;
+  }
+}
+
+enum class Wide { Plain, Pairs, Split };
+template <int N, int PREC, Wide MODE>
 __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
     const int8_t* __restrict__ spins, int64_t S, int nsplit, int per,
     const uint8_t* __restrict__ perm, int K, int M,
@@ -129,6 +198,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
   using T = ThetaTraits<PREC>;
   using Cfg = WideCfg<N>;
   constexpr int NB = Cfg::NB, G = 8 * N, nblk = G / 16, NK = nk_of<N, PREC>();
+  constexpr bool PAIRS = MODE == Wide::Pairs, SPLIT = MODE == Wide::Split;
   constexpr int THREADS = 64 * kWideWaves, E4 = NB * 4, NSTG = (E4 + THREADS - 1) / THREADS;
   constexpr int kWB = wide_bonds<N>(), kHead = wide_head<N, PAIRS>();
   constexpr bool PACK = N == 100;            // two bond slots' offsets in a register
@@ -174,7 +244,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
   stage_store(0);
   uint32_t buf = 0;                            // byte offset of the chunk in use
 
-  const int64_t n_items = S * nblk * nsplit;
+  const int64_t n_items = S * nblk * (SPLIT ? nsplit : 1);
   int64_t item = (int64_t)blockIdx.x * per + wv;
   bool act = wv < per && item < n_items;
 
@@ -183,7 +253,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
   int blk = 0, share = 0, e0 = 0, e1 = 0;      // list entries [e0, e1) of this and later walks
   bool first = true;                           // first walk of the item
   float ch_g = 0.f;
-  double m_item = -INFINITY, Qr = 0.0, Qi = 0.0, denr = 0.0, deni = 0.0;
+  WideSums sum;
+  sum.init();
   typename T::BFrag bx[BITS ? 1 : NK];
   XBits<N, PREC> xb;
 
@@ -197,8 +268,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
     int head = 0;                              // slots of the list's first kHead entries
     if (act) {
       if (first) {
-        const int64_t cb = nsplit > 1 ? item / nsplit : item;
-        share = (int)(item - cb * nsplit);
+        const int64_t cb = SPLIT ? item / nsplit : item;
+        share = SPLIT ? (int)(item - cb * nsplit) : 0;
         s = cb / nblk;
         blk = (int)(cb - s * nblk);
         const int8_t* srow = spins + s * N;
@@ -228,15 +299,21 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
           n += __popcll(msk);
         }
         wave_sync_lds();
-        const int len = ((n + nsplit - 1) / nsplit + 7) & ~7;
-        e0 = min(n, share * len);
-        e1 = min(n, e0 + len);
+        if constexpr (SPLIT) {
+          const int len = ((n + nsplit - 1) / nsplit + 7) & ~7;
+          e0 = min(n, share * len);
+          e1 = min(n, e0 + len);
+        } else {
+          e0 = 0;
+          e1 = n;
+        }
         const uint8_t* prow = perm + (size_t)(blk * 16 + c) * N;
         if constexpr (BITS) xb.load(srow, prow, q);
         else load_bfrag_gather<N, PREC>(srow, prow, q, bx);
-        ch_g = (float)chi[blk * 16 + c];
-        m_item = -INFINITY;
-        Qr = Qi = denr = deni = 0.0;
+        if constexpr (!SPLIT) {
+          ch_g = (float)chi[blk * 16 + c];
+          sum.init();
+        }
       }
       const int g = blk * 16 + c;
       // more RBMs than the record holds: the first kHead entries take a walk of their own
@@ -383,41 +460,47 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
         axr += __shfl_xor(axr, 32, 64);
         axi += __shfl_xor(axi, 32, 64);
         const double Er = axr + sx + (double)E * 0.69314718055994530942;
-        const double mk = wave_max(Er);
-        if (mk > m_item) {
-          const double sc = (double)exp_t((float)(m_item - mk));   // 0 at the first RBM
-          Qr *= sc; Qi *= sc; denr *= sc; deni *= sc;
-          m_item = mk;
-        }
-        const float e = ch_g * exp_t((float)(Er - m_item));
-        float sn, cs;
-        sincos_t((float)axi, &sn, &cs);
-        const float ur = e * (pr * cs - pi * sn), ui = e * (pr * sn + pi * cs);
-        double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
+        if constexpr (SPLIT) {
+          // the share's one walk began at entry e0 - 4 kWB
+          const WideSplit out(part, S * nblk, K);
+          const size_t ik = (size_t)(s * nblk + blk) * K + k;
+          float2* pk = out.prod + (ik * NB + (e0 - 4 * kWB)) * 16;   // 16 (entry + q) + c
 #pragma unroll
-        for (int jb = 0; jb < kWB; ++jb) {
-          if (jb < nvu) {
-            double wj = 1.0;
-            if constexpr (PAIRS) {
-              const uint32_t o = PACK ? (jb & 1 ? offs[jb / 2] >> 16 : offs[jb / 2]) : offs[jb];
-              wj = o & 2u ? 2.0 : 1.0;
-            }
-            const double vr = jb < nv ? wj * (double)Pr[jb] : 0.0;
-            const double vi = jb < nv ? wj * (double)Pi[jb] : 0.0;
-            if (jb < head) {
-              sr += vr;
-              si += vi;
-            } else {
-              dr += vr;
-              di += vi;
-            }
+          for (int jb = 0; jb < kWB; ++jb)
+            if (jb < nv) (pk + 64 * jb)[lane] = make_float2(Pr[jb], Pi[jb]);
+          if (share == 0) {
+            WideRaw& o = out.raw[ik];
+            o.Er[c] = Er;
+            o.axi[c] = axi;
+            o.pr[lane] = pr;
+            o.pi[lane] = pi;
           }
         }
-        Qr += (double)ur * sr - (double)ui * si;
-        Qi += (double)ur * si + (double)ui * sr;
-        if (first && q == 0) {
-          denr += (double)ur;
-          deni += (double)ui;
+        double sr = 0.0, si = 0.0, dr = 0.0, di = 0.0;
+        if constexpr (!SPLIT) {
+          sum.raise(Er);
+          const float2 u = sum.weight(Er, axi, pr, pi, ch_g);
+#pragma unroll
+          for (int jb = 0; jb < kWB; ++jb) {
+            if (jb < nvu) {
+              double wj = 1.0;
+              if constexpr (PAIRS) {
+                const uint32_t o = PACK ? (jb & 1 ? offs[jb / 2] >> 16 : offs[jb / 2]) : offs[jb];
+                wj = o & 2u ? 2.0 : 1.0;
+              }
+              const double vr = jb < nv ? wj * (double)Pr[jb] : 0.0;
+              const double vi = jb < nv ? wj * (double)Pi[jb] : 0.0;
+              if (jb < head) {
+                sr += vr;
+                si += vi;
+              } else {
+                dr += vr;
+                di += vi;
+              }
+            }
+          }
+          sum.add(u, sr, si);
+          if (first && q == 0) sum.count(u);
         }
         if (first && K <= kRecK) {
           WideRec& o = rec[k];
@@ -440,18 +523,13 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
     }
 
     if (act) {
-      if (first && K > 1 && K <= kRecK) {
+      if (!SPLIT && first && K > 1 && K <= kRecK) {
         // the later entries' sums, weighted with the final m
         wave_sync_lds();
         for (int kk = 0; kk < K; ++kk) {
           const WideRec& o = rec[kk];
-          const float pr = o.pr[lane], pi = o.pi[lane];
-          const float e = ch_g * exp_t((float)(o.Er[c] - m_item));
-          float sn, cs;
-          sincos_t((float)o.axi[c], &sn, &cs);
-          const float ur = e * (pr * cs - pi * sn), ui = e * (pr * sn + pi * cs);
-          Qr += (double)ur * o.dr[lane] - (double)ui * o.di[lane];
-          Qi += (double)ur * o.di[lane] + (double)ui * o.dr[lane];
+          sum.add(sum.weight(o.Er[c], o.axi[c], o.pr[lane], o.pi[lane], ch_g), o.dr[lane],
+                  o.di[lane]);
         }
       }
       if (first && Lout != nullptr && share == 0) {
@@ -467,20 +545,8 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
         }
       }
       first = false;
-      if (e0 >= e1) {                          // the item's last walk
-        Qr = wave_sum(Qr);
-        Qi = wave_sum(Qi);
-        denr = wave_sum(share == 0 ? denr : 0.0);
-        deni = wave_sum(share == 0 ? deni : 0.0);
-        if (lane == 0) {
-          double* o = part + item * 6;
-          o[0] = m_item;
-          o[1] = denr;
-          o[2] = deni;
-          o[3] = Qr;
-          o[4] = Qi;
-          o[5] = 0.0;
-        }
+      if (SPLIT || e0 >= e1) {                 // the item's last walk
+        if constexpr (!SPLIT) store_partial(sum, part + item * 6, lane);
         item += (int64_t)gridDim.x * per;
         act = item < n_items;
         first = true;
@@ -489,27 +555,118 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
   }
 }
 
+// One workgroup of K wavefronts per (configuration, 16-image block) of a split
+// launch: the walks of an unsplit wavefront over the stored products, lane (q, c)
+// with the entries q + 4 jb of image c; wavefront k sums RBM k's, the first one
+// weights the sums.  Latency bound: the first walk's products are loaded before
+// the length of the list is known.
+template <int N>
+__global__ __launch_bounds__(64 * kRecK) void wide_join_kernel(const int8_t* __restrict__ spins,
+                                                               int K,
+                                                               const int32_t* __restrict__ bonds,
+                                                               const double* __restrict__ chi,
+                                                               double* __restrict__ part) {
+  constexpr int NB = 4 * N, nblk = N / 2, kWB = wide_bonds<N>();
+  static_assert(4 * kWB <= NB, "a walk's entries lie in the block's products");
+  __shared__ double2 sums[kRecK][2][64];         // head and later entries
+  const int64_t ib = blockIdx.x;
+  const int lane = threadIdx.x & 63, q = lane >> 4, c = lane & 15;
+  const int k = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t s = ib / nblk;
+  const int8_t* srow = spins + s * N;
+  const WideSplit in(part, (int64_t)gridDim.x, K);
+  const float2* pk = in.prod + (size_t)(ib * K + k) * NB * 16;
+  const WideRaw* raw = in.raw + ib * K;
+  const float ch_g = (float)chi[(int)(ib - s * nblk) * 16 + c];
+  WideSums sum;
+  sum.init();
+  float2 v[kWB];
+#pragma unroll
+  for (int jb = 0; jb < kWB; ++jb) v[jb] = (pk + 64 * jb)[lane];
+  int n = 0;
+#pragma unroll
+  for (int base = 0; base < NB; base += 64) {
+    const int b = base + lane;
+    n += __popcll(__ballot(b < NB && srow[bonds[2 * b]] != srow[bonds[2 * b + 1]]));
+  }
+  for (int e0 = 0; e0 == 0 || e0 < n; e0 += 4 * kWB) {
+    const int nv = n > e0 + q ? min(kWB, (n - e0 - q + 3) / 4) : 0;
+    const int head = K == 1 || e0 > 0 ? kWB : wide_head<N, false>() / 4;
+    if (e0 > 0) {
+#pragma unroll
+      for (int jb = 0; jb < kWB; ++jb)
+        if (jb < nv) v[jb] = (pk + 16 * e0 + 64 * jb)[lane];
+    }
+    double2 h = make_double2(0.0, 0.0), t = h;
+#pragma unroll
+    for (int jb = 0; jb < kWB; ++jb) {
+      const double vr = jb < nv ? (double)v[jb].x : 0.0, vi = jb < nv ? (double)v[jb].y : 0.0;
+      if (jb < head) {
+        h.x += vr;
+        h.y += vi;
+      } else {
+        t.x += vr;
+        t.y += vi;
+      }
+    }
+    sums[k][0][lane] = h;
+    sums[k][1][lane] = t;
+    __syncthreads();
+    if (k == 0) {
+      for (int kk = 0; kk < K; ++kk) {
+        const WideRaw& o = raw[kk];
+        sum.raise(o.Er[c]);
+        const float2 u = sum.weight(o.Er[c], o.axi[c], o.pr[lane], o.pi[lane], ch_g);
+        sum.add(u, sums[kk][0][lane].x, sums[kk][0][lane].y);
+        if (e0 == 0 && q == 0) sum.count(u);
+      }
+      for (int kk = 0; K > 1 && e0 == 0 && kk < K; ++kk) {
+        const WideRaw& o = raw[kk];
+        sum.add(sum.weight(o.Er[c], o.axi[c], o.pr[lane], o.pi[lane], ch_g), sums[kk][1][lane].x,
+                sums[kk][1][lane].y);
+      }
+    }
+    __syncthreads();
+  }
+  if (k == 0) store_partial(sum, part + ib * 6, lane);
+}
+
+size_t split_block_bytes(const nqs_ctx* c) {
+  return 48 + (size_t)c->K * (sizeof(WideRaw) + (size_t)c->NB * 16 * sizeof(float2));
+}
+constexpr size_t kSplitCap = size_t(128) << 20;
+
+// Shares of the bond list per (configuration, column block): as many as leave
+// each wavefront slot of the device at most one item, at most eight (every
+// share evaluates theta again), if the products fit in cap bytes.
+int wide_nsplit(const nqs_ctx* c, int64_t S, size_t cap) {
+  const int64_t blocks = std::max<int64_t>(S, 1) * (c->G / 16);
+  if (c->K > kRecK || (size_t)blocks * split_block_bytes(c) > std::min(cap, kSplitCap)) return 1;
+  return (int)std::max<int64_t>(
+      1, std::min<int64_t>(8, (int64_t)fused_max_split_items(c) / blocks));
+}
+
 template <int N, int PREC>
-hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, hipStream_t st,
-               const int16_t* parent, double* Lout, bool split) {
-  const int nsplit = split ? wide_nsplit(c, S) : 1;
+hipError_t run(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part, size_t part_cap,
+               hipStream_t st, const int16_t* parent, double* Lout) {
+  const int nsplit = parent ? 1 : wide_nsplit(c, S, part_cap);
   const int64_t n_cu = c->n_cu > 0 ? c->n_cu : 256, items = S * (c->G / 16) * nsplit;
   // fewer items than wavefront slots: the same number in every workgroup
   const int per = (int)std::min<int64_t>(kWideWaves, (items + n_cu - 1) / n_cu);
   const int64_t blocks = std::min<int64_t>((items + per - 1) / per, n_cu);
   const auto* wf = (const typename ThetaTraits<PREC>::AFrag*)(PREC == kPrecF32X3 ? c->par.wfrag3
                                                                                  : c->par.wfrag);
-#define NQS_WIDE_ARGS                                                                     \
-  spins, S, nsplit, per, c->dev.perm, c->K, c->M, wf, (const float*)c->par.bias,          \
-      (const float*)c->par.avec, c->dev.bonds, c->dev.wmap, c->dev.wrow, c->dev.chi,      \
-      (const float*)c->par.Tpm, (const float*)c->par.F, part
-  if (parent)
-    eloc_wide_kernel<N, PREC, true><<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
-        NQS_WIDE_ARGS, parent, nullptr);
-  else
-    eloc_wide_kernel<N, PREC, false><<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
-        NQS_WIDE_ARGS, nullptr, Lout);
-#undef NQS_WIDE_ARGS
+  auto kernel = parent       ? eloc_wide_kernel<N, PREC, Wide::Pairs>
+                : nsplit > 1 ? eloc_wide_kernel<N, PREC, Wide::Split>
+                             : eloc_wide_kernel<N, PREC, Wide::Plain>;
+  kernel<<<(unsigned)blocks, 64 * kWideWaves, 0, st>>>(
+      spins, S, nsplit, per, c->dev.perm, c->K, c->M, wf, (const float*)c->par.bias,
+      (const float*)c->par.avec, c->dev.bonds, c->dev.wmap, c->dev.wrow, c->dev.chi,
+      (const float*)c->par.Tpm, (const float*)c->par.F, part, parent, Lout);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || nsplit == 1) return e;
+  wide_join_kernel<N><<<(unsigned)(S * (c->G / 16)), 64 * c->K, 0, st>>>(
+      spins, c->K, c->dev.bonds, c->dev.chi, part);
   return hipGetLastError();
 }
 
@@ -520,41 +677,39 @@ bool eloc_wide_supported(const nqs_ctx* c) {
   return c->N == 36 || c->N == 64 || c->N == 100;
 }
 
-// Shares of the bond list per (configuration, column block): as many as leave
-// each wavefront slot of the device at most one item, at most eight (every
-// share evaluates theta again).
-int wide_nsplit(const nqs_ctx* c, int64_t S) {
-  if (c->K > kRecK) return 1;
-  const int64_t items = std::max<int64_t>(S, 1) * (c->G / 16);
-  return (int)std::max<int64_t>(
-      1, std::min<int64_t>(8, (int64_t)fused_max_split_items(c) / items));
+size_t wide_split_part_bytes(const nqs_ctx* c, int64_t S) {
+  if (c->K > kRecK) return 0;
+  const int64_t nblk = c->G / 16;
+  const int64_t most = std::min<int64_t>((int64_t)fused_max_split_items(c) / 2 / nblk,
+                                         (int64_t)(kSplitCap / split_block_bytes(c)) / nblk);
+  return (size_t)(std::min<int64_t>(S, most) * nblk) * split_block_bytes(c);
 }
 
 namespace {
 hipError_t dispatch(const nqs_ctx* c, const int8_t* spins, int64_t S, const int16_t* parent,
-                    double* part, double* Lout, bool split, hipStream_t st) {
+                    double* part, size_t cap, double* Lout, hipStream_t st) {
   if (S <= 0) return hipSuccess;
   const bool bf = c->prec == NQS_BF16X2;
   switch (c->N) {
-    case 36: return bf ? run<36, NQS_BF16X2>(c, spins, S, part, st, parent, Lout, split)
-                       : run<36, kPrecF32X3>(c, spins, S, part, st, parent, Lout, split);
-    case 64: return bf ? run<64, NQS_BF16X2>(c, spins, S, part, st, parent, Lout, split)
-                       : run<64, kPrecF32X3>(c, spins, S, part, st, parent, Lout, split);
-    case 100: return bf ? run<100, NQS_BF16X2>(c, spins, S, part, st, parent, Lout, split)
-                        : run<100, kPrecF32X3>(c, spins, S, part, st, parent, Lout, split);
+    case 36: return bf ? run<36, NQS_BF16X2>(c, spins, S, part, cap, st, parent, Lout)
+                       : run<36, kPrecF32X3>(c, spins, S, part, cap, st, parent, Lout);
+    case 64: return bf ? run<64, NQS_BF16X2>(c, spins, S, part, cap, st, parent, Lout)
+                       : run<64, kPrecF32X3>(c, spins, S, part, cap, st, parent, Lout);
+    case 100: return bf ? run<100, NQS_BF16X2>(c, spins, S, part, cap, st, parent, Lout)
+                        : run<100, kPrecF32X3>(c, spins, S, part, cap, st, parent, Lout);
     default: return hipErrorNotSupported;
   }
 }
 }  // namespace
 
 hipError_t launch_eloc_wide(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                            hipStream_t st, double* Lout, bool split) {
-  return dispatch(c, spins, S, nullptr, part, Lout, split, st);
+                            size_t part_cap, hipStream_t st, double* Lout) {
+  return dispatch(c, spins, S, nullptr, part, part_cap, Lout, st);
 }
 
 hipError_t launch_eloc_wide_pairs(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                   const int16_t* parent, double* part, hipStream_t st) {
-  return dispatch(c, spins, S, parent, part, nullptr, false, st);
+  return dispatch(c, spins, S, parent, part, 0, nullptr, st);
 }
 
 }  // namespace nqs

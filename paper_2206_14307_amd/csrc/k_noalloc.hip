@@ -90,7 +90,7 @@ extern "C" nqs_status nqs_eloc_noalloc(nqs_ctx* c, const int8_t* spins, int64_t 
   if (fused) {
     e = launch_eloc_fused(c, spins, S, part, kScratchBytes, logpsi_out, eloc_out, 2, st);
   } else {
-    e = launch_eloc_wide(c, spins, S, part, st);
+    e = launch_eloc_wide(c, spins, S, part, kScratchBytes, st);
     if (e == hipSuccess) e = launch_fused_finish(c, spins, S, part, logpsi_out, eloc_out, 2, st);
   }
   if (e != hipSuccess) return fail(NQS_ERR_DEVICE, hipGetErrorString(e));

@@ -168,17 +168,16 @@ bool eloc_fused_supported(const nqs_ctx* c);
 bool grad_fused_supported(const nqs_ctx* c);
 hipError_t launch_enum_sz0(const nqs_ctx* c, int64_t count, int8_t* out, hipStream_t st);
 bool eloc_wide_supported(const nqs_ctx* c);
-// split = false keeps one share: sums in an order that does not depend on S.
+// part and part_cap as for launch_eloc_fused (wide_split_part_bytes).
 // Lout (optional): the per-image log amplitudes [S][K][G], unreduced (four
 // reals each, see launch_lse), for a gradient pass on the same configurations
 hipError_t launch_eloc_wide(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,
-                            hipStream_t st, double* Lout = nullptr, bool split = true);
-// shares of the bond list per (configuration, column block) in a launch of S configurations
-int wide_nsplit(const nqs_ctx* c, int64_t S);
+                            size_t part_cap, hipStream_t st, double* Lout = nullptr);
+size_t wide_split_part_bytes(const nqs_ctx* c, int64_t S);   // of any launch of at most S
 // combines the partials of launch_eloc_wide
 hipError_t launch_fused_finish(const nqs_ctx* c, const int8_t* spins, int64_t S,
                                const double* part, double* logpsi, double* eloc, int eloc_stride,
-                               hipStream_t st, bool split = true);
+                               hipStream_t st);
 hipError_t launch_grad_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, void* O,
                              double* logpsi, hipStream_t st);
 hipError_t launch_eloc_fused(const nqs_ctx* c, const int8_t* spins, int64_t S, double* part,

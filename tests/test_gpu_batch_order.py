@@ -55,3 +55,28 @@ def test_eloc_fused(L, K, M, prec):
         assert torch.equal(m.eloc_grad(x)[1], e1), S
         if K > 1:
             assert torch.equal(m.lanczos_moments(x)[1][:, 0], e1), S
+
+
+@pytest.mark.parametrize("L,K,M,prec", [(6, 1, 144, "fp32"), (6, 4, 40, "bf16x2"),
+                                        (6, 5, 32, "fp32"), (8, 1, 136, "bf16x2"),
+                                        (8, 3, 48, "fp32"), (10, 1, 136, "fp32"),
+                                        (10, 2, 72, "bf16x2"), (10, 4, 40, "fp32")])
+def test_eloc_wide(L, K, M, prec):
+    """Row 0 has more antiparallel bonds than one walk of the kernel holds."""
+    from paper_2206_14307_amd.nqs import _ptr, _stream
+    m = _model(L, K, M, prec)
+    sp = _rows(L, 2200 * 2 // (L * L))
+    lp, el = m.eloc(sp)
+    for S in (1, 2, 3, 5, 7, 10, 16, 24, 40, 60, 90):
+        if S > sp.shape[0]:
+            break
+        x = sp[:S].contiguous()
+        l1, e1 = m.eloc(x)
+        assert torch.equal(e1, el[:S]) and torch.equal(l1, lp[:S]), S
+        e2 = torch.empty_like(e1)
+        assert m.lib.nqs_eloc_noalloc(m._ctx, _ptr(x), S, None, _ptr(e2), _stream()) == 0
+        assert torch.equal(e2, e1), S
+        lg, eg, _ = m.eloc_grad(x)
+        assert torch.equal(eg, e1) and torch.equal(lg, l1), S
+        if S < 4:
+            assert torch.equal(m.lanczos_moments(x)[1][:, 0], e1), S
