@@ -264,7 +264,8 @@ __global__ __launch_bounds__(1024) void sample_kernel(
 // left, up to the first that differs from the assumed outcome: proposals behind
 // it are drawn again by the next pass, and accepted exchanges that are not in
 // the current cache become pending.  Every ratio and every entry is formed by
-// the operations, in the order, of one proposal at a time.
+// the operations, in the order and with the roundings, of one proposal at a time
+// (the FMAs are written out).
 constexpr int kMaxRows = 4;        // pending exchanges and proposals in a pass
 
 // One pass over the cache of RBM k of an image: entries tp, rows T[NR] of the
@@ -279,8 +280,11 @@ __device__ __forceinline__ void stream_rows(const float* __restrict__ tp, float*
     pr[r] = 1;
     pi[r] = 0;
   }
-  // the 8 factors of a row's tile into its product, the entries updated
+  // the 8 factors of a row's tile into its product, the entries updated.  No
+  // contraction beyond the FMAs written out: a row's T - t' would otherwise take
+  // the t' of the row before it unrounded.
   auto tile = [&](float (&tt)[16], const float (&TT)[16], int r) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float tr = tt[2 * e], ti = tt[2 * e + 1];
@@ -294,7 +298,7 @@ __device__ __forceinline__ void stream_rows(const float* __restrict__ tp, float*
         // t' = (t - T) / (1 - t T) = (T - t) / (a + ib)
         const float dr = Tr - tr, di = Ti - ti;
         const float inv = rcp_fast(fmaf(a, a, b * b));
-        tt[2 * e] = fmaf(dr, a, di * b) * inv;
+        tt[2 * e] = fmaf(di, b, dr * a) * inv;
         tt[2 * e + 1] = fmaf(di, a, -(dr * b)) * inv;
       }
     }
@@ -457,8 +461,8 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
           if (q >= np && q < rows) {
             const float* f = Fpair + ((size_t)k * N * N + l[q]) * 2;
             float* o = Rg + ((size_t)((q - np) * G + g) * K + k) * 2;
-            o[0] = f[0] * pr[q] - f[1] * pi[q];
-            o[1] = f[0] * pi[q] + f[1] * pr[q];
+            o[0] = fmaf(f[0], pr[q], -(f[1] * pi[q]));
+            o[1] = fmaf(f[0], pi[q], f[1] * pr[q]);
           }
       }
     }
@@ -472,8 +476,8 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
         for (int k = 0; k < K; ++k) {
           const float rr = Rd[2 * k], ri = Rd[2 * k + 1];
           const float wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
-          cr += (double)(wr * rr - wi * ri);
-          ci += (double)(wr * ri + wi * rr);
+          cr += (double)fmaf(wr, rr, -(wi * ri));
+          ci += (double)fmaf(wr, ri, wi * rr);
         }
       }
       cr = wave_sum(cr);
@@ -491,18 +495,18 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
       }
       const double u = (double)(lane64(rnd[2], r - rbase) >> 11) * (1.0 / 9007199254740992.0);
       // every lane holds the same sums: a wave-uniform decision
-      const bool accept = __builtin_amdgcn_readfirstlane((int)(u < sr * sr + si * si)) != 0;
+      const double den = fma(si, si, sr * sr);  // |psi'/psi|^2
+      const bool accept = __builtin_amdgcn_readfirstlane((int)(u < den)) != 0;
       if (accept) {
         ++acc;
         ++n_acc;
         if (active) {
-          const double den = sr * sr + si * si;
           for (int k = 0; k < K; ++k) {
             const float wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
             const float rr = Rd[2 * k], ri = Rd[2 * k + 1];
-            const double qr = (double)(wr * rr - wi * ri), qi = (double)(wr * ri + wi * rr);
-            wc[2 * (k * G + g)] = (float)((qr * sr + qi * si) / den);
-            wc[2 * (k * G + g) + 1] = (float)((qi * sr - qr * si) / den);
+            const double qr = (double)fmaf(wr, rr, -(wi * ri)), qi = (double)fmaf(wi, rr, wr * ri);
+            wc[2 * (k * G + g)] = (float)(fma(qr, sr, qi * si) / den);
+            wc[2 * (k * G + g) + 1] = (float)(fma(qi, sr, -(qr * si)) / den);
           }
         }
         int i = ei[0], j = ej[0];
