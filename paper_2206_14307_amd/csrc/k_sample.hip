@@ -59,6 +59,12 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c0, uint64_t c1, uint64_t
 // from the spins every segment)
 __device__ __forceinline__ float rcp_fast(float v) { return __builtin_amdgcn_rcpf(v); }
 
+// reciprocal of the squared modulus in the cache update: hardware rcp in
+// FP32 (the cache is rebuilt from the spins every segment), a division in
+// FP64
+__device__ __forceinline__ float recip_t(float v) { return rcp_fast(v); }
+__device__ __forceinline__ double recip_t(double v) { return 1.0 / v; }
+
 // one cache or row tile of 8 complex values, moved in 16-byte pieces (the
 // tiles are 64-byte aligned)
 template <typename R>
@@ -79,6 +85,24 @@ __device__ __forceinline__ void store_tile(R* p, const R (&d)[16]) {
 #pragma unroll
   for (int i = 0; i < NV; ++i) q[i] = v[i];
 }
+
+// Launches of one segment that share the chains' caches: `mode` (nullable) says on
+// the device which of the two streaming kernels runs (0: one proposal in a pass, 1:
+// several), buf_in / buf_out (nullable) carry which of a chain's two caches is the
+// current one from one launch to the next (null: the first).
+struct Handoff {
+  const int* mode = nullptr;
+  const int* buf_in = nullptr;
+  int* buf_out = nullptr;
+  int max_rows = 1;                // rows of a pass whose ratios fit in LDS
+  __device__ __forceinline__ bool skip(int kernel) const { return mode && *mode != kernel; }
+  __device__ __forceinline__ bool second(int64_t c) const {
+    return buf_in && __builtin_amdgcn_readfirstlane(buf_in[c]) != 0;
+  }
+  __device__ __forceinline__ void keep(int64_t c, bool second) const {
+    if (buf_out) buf_out[c] = second;
+  }
+};
 
 // position of the k-th (0-based) set bit of a 64-bit word (k < popcount)
 __device__ __forceinline__ int select64(uint64_t x, int k) {
@@ -101,22 +125,25 @@ __device__ __forceinline__ int select128(uint64_t lo, uint64_t hi, int k) {
   return k < c ? select64(lo, k) : 64 + select64(hi, k - c);
 }
 
-// FP64 (small lattices, caches in L2): one proposal in a pass.  It is bound by
-// the update's divisions and not by the caches' traffic: the passes of several
-// proposals below gained 3 % at 4x4 M = 16 at an acceptance near 1 and took
-// 1.6 times as long at 0.3.
+// One proposal in a pass.  FP64 (small lattices, caches in L2) always: it is
+// bound by the update's divisions and not by the caches' traffic, and the passes
+// of several proposals below gained 3 % at 4x4 M = 16 at an acceptance near 1 and
+// took 1.6 times as long at 0.3.  FP32 between the acceptances at which several
+// pay (sample_mode_kernel).
+template <typename R>
 __global__ __launch_bounds__(1024) void sample_kernel(
     int N, int G, int K, int M, int n_htiles, const uint8_t* __restrict__ perminv,
-    const double* __restrict__ Tpair, const double* __restrict__ Fpair, double* __restrict__ t,
-    double* __restrict__ t2, double* __restrict__ w, uint64_t* __restrict__ state, int n_prop, int phase, int64_t p0,
+    const R* __restrict__ Tpair, const R* __restrict__ Fpair, R* __restrict__ t, R* __restrict__ t2,
+    R* __restrict__ w, uint64_t* __restrict__ state, int n_prop, int phase, int64_t p0,
     const int32_t* nskip_dev,
     int n_skip_host, uint64_t seed, int8_t* __restrict__ spins_out, int64_t n_per_chain,
-    int64_t* __restrict__ acc_out, int8_t* __restrict__ cur_spins) {
+    int64_t* __restrict__ acc_out, int8_t* __restrict__ cur_spins, Handoff ho) {
+  if (ho.skip(0)) return;
   extern __shared__ __align__(16) unsigned char smem[];
-  double* Rg = reinterpret_cast<double*>(smem);                        // [G][K] complex
+  R* Rg = reinterpret_cast<R*>(smem);                                  // [G][K] complex
   // per-wave ratio sums [2][32], double-buffered by proposal parity (see the
   // register kernel): one barrier per proposal
-  double* red = reinterpret_cast<double*>(smem + (size_t)G * K * 2 * sizeof(double));
+  double* red = reinterpret_cast<double*>(smem + (size_t)G * K * 2 * sizeof(R));
   const int64_t c = blockIdx.x;
   const int g = threadIdx.x, lane = g & 63, wv = g >> 6, nw = (blockDim.x + 63) >> 6;
   const bool active = g < G;
@@ -133,9 +160,14 @@ __global__ __launch_bounds__(1024) void sample_kernel(
   // ratio pass also writes the tanh-addition update of every entry to tn, and
   // an accepted proposal swaps the two (the acceptance rate is close to 1, so
   // this reads the cache once per proposal instead of twice)
-  double* tc = t + (size_t)c * n_htiles * G * 16;
-  double* tn = t2 + (size_t)c * n_htiles * G * 16;
-  double* wc = w + (size_t)c * K * G * 2;
+  R* tc = t + (size_t)c * n_htiles * G * 16;
+  R* tn = t2 + (size_t)c * n_htiles * G * 16;
+  if (ho.second(c)) {
+    R* const sw = tc;
+    tc = tn;
+    tn = sw;
+  }
+  R* wc = w + (size_t)c * K * G * 2;
   int64_t acc = 0;
   for (int r = 0; r < n_prop && valid; ++r) {
     uint64_t rnd[4];
@@ -149,47 +181,71 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     if (active) {
       l1 = perminv[(size_t)g * N + i];
       l2 = perminv[(size_t)g * N + j];
-      const double* Trow = Tpair + ((size_t)l1 * N + l2) * KM * 2;
+      const R* Trow = Tpair + ((size_t)l1 * N + l2) * KM * 2;
       for (int k = 0; k < K; ++k) {
-        double pr = 1, pi = 0;
+        R pr = 1, pi = 0;
         // tiles of 8 units: this image's 16 cache values (one contiguous
-        // piece of the [tile][G][16] layout) and 16 row values
+        // piece of the [tile][G][16] layout) and 16 row values, each tile's
+        // loads issued one tile ahead of its use, its updates stored whole
         const int nt = M / 8;
-        const double* tp = tc + ((size_t)(k * nt) * G + g) * 16;
-        double* up = tn + ((size_t)(k * nt) * G + g) * 16;
-        const double* Tq = Trow + (size_t)2 * k * M;
+        const R* tp = tc + ((size_t)(k * nt) * G + g) * 16;
+        R* up = tn + ((size_t)(k * nt) * G + g) * 16;
+        const R* Tq = Trow + (size_t)2 * k * M;
         // the 8 factors of a tile into the product, the updated tile stored
-        auto tile = [&](double (&tt)[16], const double (&TT)[16], double* dst) {
+        auto tile = [&](R (&tt)[16], const R (&TT)[16], R* dst) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const double tr = tt[2 * e], ti = tt[2 * e + 1];
-            const double Tr = TT[2 * e], Ti = TT[2 * e + 1];
-            const double a = fmaf_t(tr, Tr, fmaf_t(-ti, Ti, -1.0));   // a + ib = t T - 1
-            const double b = fmaf_t(tr, Ti, ti * Tr);
-            const double nr = fmaf_t(pr, a, -(pi * b));
+            const R tr = tt[2 * e], ti = tt[2 * e + 1];
+            const R Tr = TT[2 * e], Ti = TT[2 * e + 1];
+            const R a = fmaf_t(tr, Tr, fmaf_t(-ti, Ti, R(-1)));   // a + ib = t T - 1
+            const R b = fmaf_t(tr, Ti, ti * Tr);
+            const R nr = fmaf_t(pr, a, -(pi * b));
             pi = fmaf_t(pr, b, pi * a);
             pr = nr;
             // t' = (t - T) / (1 - t T) = (T - t) / (a + ib)
-            const double dr = Tr - tr, di = Ti - ti;
-            const double inv = 1.0 / fmaf_t(a, a, b * b);
+            const R dr = Tr - tr, di = Ti - ti;
+            const R inv = recip_t(fmaf_t(a, a, b * b));
             tt[2 * e] = (dr * a + di * b) * inv;
             tt[2 * e + 1] = (di * a - dr * b) * inv;
           }
           store_tile(dst, tt);
         };
-        double tt[16], TT[16];
-        for (int ht = 0; ht < nt; ++ht) {
-          load_tile(tt, tp + (size_t)ht * G * 16);
-          load_tile(TT, Tq + 16 * ht);
-          tile(tt, TT, up + (size_t)ht * G * 16);
+        // FP32: two register buffers, the next tile always in flight (FP64,
+        // for small lattices only, keeps one: its tiles would not fit twice
+        // in the 128 VGPRs of a 1024-lane workgroup)
+        R t0[16], T0[16], t1[16], T1[16];
+        if constexpr (sizeof(R) == 8) {
+          for (int ht = 0; ht < nt; ++ht) {
+            load_tile(t0, tp + (size_t)ht * G * 16);
+            load_tile(T0, Tq + 16 * ht);
+            tile(t0, T0, up + (size_t)ht * G * 16);
+          }
+        } else {
+          // the loop body is free of conditions (the last prefetch reads the
+          // last tile again): a conditional load is sunk to its use, and a
+          // conditional path makes the wait before a tile cover the next
+          // one's loads too
+          load_tile(t0, tp);
+          load_tile(T0, Tq);
+          int ht = 0;
+          for (; ht + 1 < nt; ht += 2) {
+            load_tile(t1, tp + (size_t)(ht + 1) * G * 16);
+            load_tile(T1, Tq + 16 * (ht + 1));
+            tile(t0, T0, up + (size_t)ht * G * 16);
+            const int h2 = min(ht + 2, nt - 1);
+            load_tile(t0, tp + (size_t)h2 * G * 16);
+            load_tile(T0, Tq + 16 * h2);
+            tile(t1, T1, up + (size_t)(ht + 1) * G * 16);
+          }
+          if (ht < nt) tile(t0, T0, up + (size_t)ht * G * 16);   // odd tile count
         }
-        const double* f = Fpair + (((size_t)k * N + l1) * N + l2) * 2;
-        const double rr = f[0] * pr - f[1] * pi, ri = f[0] * pi + f[1] * pr;
+        const R* f = Fpair + (((size_t)k * N + l1) * N + l2) * 2;
+        const R rr = f[0] * pr - f[1] * pi, ri = f[0] * pi + f[1] * pr;
         Rg[2 * (g * K + k)] = rr;
         Rg[2 * (g * K + k) + 1] = ri;
-        const double wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
-        cr += wr * rr - wi * ri;
-        ci += wr * ri + wi * rr;
+        const R wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
+        cr += (double)(wr * rr - wi * ri);
+        ci += (double)(wr * ri + wi * rr);
       }
     }
     cr = wave_sum(cr);
@@ -209,17 +265,17 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     const bool accept = u < sr * sr + si * si;
     if (accept) {
       ++acc;
-      double* const sw = tc;                   // the updated cache becomes current
+      R* const sw = tc;                        // the updated cache becomes current
       tc = tn;
       tn = sw;
       if (active) {
         const double den = sr * sr + si * si;
         for (int k = 0; k < K; ++k) {
-          const double wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
-          const double rr = Rg[2 * (g * K + k)], ri = Rg[2 * (g * K + k) + 1];
-          const double qr = wr * rr - wi * ri, qi = wr * ri + wi * rr;
-          wc[2 * (k * G + g)] = (qr * sr + qi * si) / den;
-          wc[2 * (k * G + g) + 1] = (qi * sr - qr * si) / den;
+          const R wr = wc[2 * (k * G + g)], wi = wc[2 * (k * G + g) + 1];
+          const R rr = Rg[2 * (g * K + k)], ri = Rg[2 * (g * K + k) + 1];
+          const double qr = (double)(wr * rr - wi * ri), qi = (double)(wr * ri + wi * rr);
+          wc[2 * (k * G + g)] = (R)((qr * sr + qi * si) / den);
+          wc[2 * (k * G + g) + 1] = (R)((qi * sr - qr * si) / den);
         }
       }
       const int b0 = i < 64 ? i : i - 64, b1 = j < 64 ? j : j - 64;
@@ -242,6 +298,7 @@ __global__ __launch_bounds__(1024) void sample_kernel(
     state[4 * c] = lo;
     state[4 * c + 1] = hi;
     state[4 * c + 2] = ctr;
+    ho.keep(c, tc != t + (size_t)c * n_htiles * G * 16);
     acc_out[c] += valid ? acc : -((int64_t)1 << 40);   // marks a chain outside Sz = 0
   }
   if (g < N) {
@@ -265,15 +322,19 @@ __global__ __launch_bounds__(1024) void sample_kernel(
 // it are drawn again by the next pass, and accepted exchanges that are not in
 // the current cache become pending.  Every ratio and every entry is formed by
 // the operations, in the order and with the roundings, of one proposal at a time
-// (the FMAs are written out).
+// (explicit FMAs where the other kernel's expressions contract to them): the
+// trajectories do not depend on which of the two kernels runs.
 constexpr int kMaxRows = 4;        // pending exchanges and proposals in a pass
 
-// One pass over the cache of RBM k of an image: entries tp, rows T[NR] of the
-// site-pair table, products out (prod_h (t T - 1) per row).  The first NU rows
-// update the entry; the entry after NW of them is written to up (0: none).
+// One pass over the cache of RBM k of an image: entries at tc + go, rows T + ro[q]
+// of the site-pair table (bases the same in every lane, byte offsets per lane, so
+// that the addresses take a register each), products out (prod_h (t T - 1) per
+// row).  The first NU rows update the entry; the entry after NW of them is written
+// at tn + go (0: none).
 template <int NR, int NU, int NW>
-__device__ __forceinline__ void stream_rows(const float* __restrict__ tp, float* __restrict__ up,
-                                            const float* const (&T)[kMaxRows], int nt, size_t step,
+__device__ __forceinline__ void stream_rows(const char* __restrict__ tc, char* __restrict__ tn,
+                                            uint32_t go, const char* __restrict__ T,
+                                            const uint32_t (&ro)[kMaxRows], int nt, uint32_t step,
                                             float (&pr)[kMaxRows], float (&pi)[kMaxRows]) {
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -308,21 +369,21 @@ __device__ __forceinline__ void stream_rows(const float* __restrict__ tp, float*
   // the last tile again): a conditional load is sunk to its use, and a
   // conditional path makes the wait before a tile cover the next one's loads
   float t0[16], t1[16], T0[16], T1[16];
-  auto tiles = [&](float (&tt)[16], float (&tn)[16], float (&TA)[16], float (&TB)[16], int ht,
+  auto tiles = [&](float (&tt)[16], float (&tx)[16], float (&TA)[16], float (&TB)[16], int ht,
                    int hn) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       float (&Tc)[16] = (r & 1) ? TB : TA;
       float (&Tn)[16] = (r & 1) ? TA : TB;
-      if (r + 1 < NR) load_tile(Tn, T[r + 1 < NR ? r + 1 : 0] + 16 * ht);
-      else load_tile(Tn, T[0] + 16 * hn);
-      if (r == 0) load_tile(tn, tp + (size_t)hn * step);
+      if (r + 1 < NR) load_tile(Tn, reinterpret_cast<const float*>(T + 64 * ht + ro[r + 1 < NR ? r + 1 : 0]));
+      else if (hn >= 0) load_tile(Tn, reinterpret_cast<const float*>(T + 64 * hn + ro[0]));
+      if (r == 0 && hn >= 0) load_tile(tx, reinterpret_cast<const float*>(tc + (size_t)hn * step + go));
       tile(tt, Tc, r);
-      if (r + 1 == NW) store_tile(up + (size_t)ht * step, tt);
+      if (r + 1 == NW) store_tile(reinterpret_cast<float*>(tn + (size_t)ht * step + go), tt);
     }
   };
-  load_tile(t0, tp);
-  load_tile(T0, T[0]);
+  load_tile(t0, reinterpret_cast<const float*>(tc + go));
+  load_tile(T0, reinterpret_cast<const float*>(T + ro[0]));
   int ht = 0;
   for (; ht + 1 < nt; ht += 2) {
     const int h2 = min(ht + 2, nt - 1);
@@ -330,31 +391,75 @@ __device__ __forceinline__ void stream_rows(const float* __restrict__ tp, float*
     if constexpr (NR & 1) tiles(t1, t0, T1, T0, ht + 1, h2);
     else tiles(t1, t0, T0, T1, ht + 1, h2);
   }
-  if (ht < nt) tiles(t0, t1, T0, T1, ht, ht);              // odd tile count
+  if (ht < nt) tiles(t0, t1, T0, T1, ht, -1);              // odd tile count
 }
 
-// a value that is the same in every lane, or lane l's, as a scalar
+// Which streaming kernel runs next, from the acceptance of all chains over the
+// n_new proposals since the last choice (acc: accepted per chain so far, negative
+// outside Sz = 0; *seen: their sum at the last choice, 0 if `first`).  Several
+// proposals in a pass pay where most passes come out as assumed: nearly all
+// accepted, or (rows permitting, max_rows = 4) nearly all rejected; more so for
+// caches that stream from HBM.  Times of 260 proposals of 256 chains, this choice
+// against one proposal in a pass always (ms), at acceptances of about 0.99 / 0.5 to
+// 0.8 / 0.2 / 0.08: 6x6 M = 40 2.0 of 3.2 / 3.2 of 3.1 / 3.1 of 3.1 / 2.9 of 3.1,
+// 8x8 M = 64 4.5 of 8.0 / 8.0 of 8.0 / 7.9 of 7.9 / 7.4 of 7.9, 10x10 M = 104 13.5
+// of 29.0 / 28.4 of 29.1 / 27.0 of 29.0 / 15.4 of 29.1, 8x8 K = 4 M = 32 11.4 of
+// 23.2 / - / 22.1 of 22.0 / 22.1 of 22.0.  Several in a pass always took 3.8 at 6x6
+// and 0.7, 9.6 at 8x8 and 0.5, 26.6 at K = 4 and 0.16: a pass that ends early has
+// read rows and updated entries in vain.
+__global__ __launch_bounds__(256) void sample_mode_kernel(const int64_t* __restrict__ acc,
+                                                          int64_t n_chains, int64_t n_new,
+                                                          bool first, int64_t* seen, int big,
+                                                          int rejections, int* mode) {
+  __shared__ int64_t red[2][4];
+  int64_t a = 0, n = 0;
+  for (int64_t c = threadIdx.x; c < n_chains; c += 256)
+    if (acc[c] >= 0) {
+      a += acc[c];
+      ++n;
+    }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, 64);
+    n += __shfl_xor(n, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = a;
+    red[1][threadIdx.x >> 6] = n;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int64_t sum = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    a = sum - (first ? 0 : *seen);
+    *seen = sum;
+    n = (red[1][0] + red[1][1] + red[1][2] + red[1][3]) * n_new;
+    const bool high = 100 * a >= (big ? 80 : 85) * n;
+    const bool low = rejections && 100 * a <= (big ? 30 : 15) * n;
+    *mode = high || low ? 1 : 0;
+  }
+}
+
+// a value that is the same in every lane, as a scalar
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
   return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
-__device__ __forceinline__ uint64_t lane64(uint64_t v, int l) {
-  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
-         (uint32_t)__builtin_amdgcn_readlane((int)v, l);
-}
-
 __global__ __launch_bounds__(1024) void sample_stream_kernel(
-    int N, int G, int K, int M, int n_htiles, int max_rows, const uint8_t* __restrict__ perminv,
+    int N, int G, int K, int M, int n_htiles, const uint8_t* __restrict__ perminv,
     const float* __restrict__ Tpair, const float* __restrict__ Fpair, float* __restrict__ t,
     float* __restrict__ t2, float* __restrict__ w, uint64_t* __restrict__ state, int n_prop, int phase, int64_t p0,
     const int32_t* nskip_dev,
     int n_skip_host, uint64_t seed, int8_t* __restrict__ spins_out, int64_t n_per_chain,
-    int64_t* __restrict__ acc_out, int8_t* __restrict__ cur_spins) {
+    int64_t* __restrict__ acc_out, int8_t* __restrict__ cur_spins, Handoff ho) {
+  if (ho.skip(1)) return;
+  const int max_rows = ho.max_rows;
   extern __shared__ __align__(16) unsigned char smem[];
   // per-wave ratio sums [2][32], double-buffered by proposal parity (see the
   // register kernel): one barrier per proposal
   double* red = reinterpret_cast<double*>(smem);
-  float* Rg = reinterpret_cast<float*>(red + 64);                      // [max_rows][G][K] complex
+  // Philox words of 64 proposals from rbase on (they depend on the index alone)
+  uint64_t* words = reinterpret_cast<uint64_t*>(red + 64);             // [64][3]
+  float* Rg = reinterpret_cast<float*>(words + 64 * 3);                // [max_rows][G][K] complex
   const int64_t c = blockIdx.x;
   const int g = threadIdx.x, lane = g & 63, wv = g >> 6, nw = (blockDim.x + 63) >> 6;
   const bool active = g < G;
@@ -369,13 +474,15 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
   const int KM = K * M, nt = M / 8;
   float* tc = t + (size_t)c * n_htiles * G * 16;   // tanh(theta), without the pending exchanges
   float* tn = t2 + (size_t)c * n_htiles * G * 16;
+  if (ho.second(c)) {
+    float* const sw = tc;
+    tc = tn;
+    tn = sw;
+  }
   float* wc = w + (size_t)c * K * G * 2;
   int64_t acc = 0;
   // accepted so far in this phase
   const int64_t acc0 = p0 > 0 ? (int64_t)uniform64((uint64_t)acc_out[c]) : 0;
-  // Philox depends only on the proposal index: lane l draws the words of
-  // proposal rbase + l
-  uint64_t rnd[4];
   int rbase = -64;
   // the exchanges of a pass, pending ones first: sites i (up) and j (down)
   int ei[kMaxRows], ej[kMaxRows];
@@ -385,32 +492,42 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
     a ^= i < 64 ? 1ull << (i & 63) : 0ull;
     b ^= i < 64 ? 0ull : 1ull << (i & 63);
   };
-  for (int r = 0; r < n_prop && valid;) {
-    // Proposals of the pass by the acceptance rate a so far (three accepted of
-    // four at the start): following acceptances four above 0.8, three above 2/3
-    // and two from 1/2 on, following rejections (which write nothing unless an
-    // exchange is pending) four below 1/6, three below 1/3 and two between:
-    // each advances by 1.5 to 3.7 proposals on the average.  What a pass costs
-    // is its rows (from the last-level cache) and a read and a write of the
-    // cache.  10x10 M = 400, 256 chains, 124 proposals: 52.5 ms at any a with
-    // one proposal in a pass; now 25.2 ms at a = 1, 34.5 at 0.92, 41.2 at 0.17,
-    // 33.5 at 0.07.
+  // what is pending at the end of a launch that is not a segment's last is written
+  for (int r = 0; valid && (r < n_prop || (np > 0 && ho.buf_out));) {
+    // Proposals of the pass by the acceptance rate a of the chain so far (three
+    // accepted of four at the start): following acceptances four above 0.8, three
+    // above 2/3 and two from 1/2 on, following rejections (which write nothing
+    // unless an exchange is pending) four below 1/6, three below 1/3 and two
+    // between.  What a pass costs is its rows (from the last-level cache) and a
+    // read and a write of the cache: four accepted in a pass take 0.49 of the time
+    // of four passes at 8x8 K = 4 M = 32, 0.44 at 10x10 M = 104 (256 chains).
     const int64_t na = acc0 + acc + 3, nn = p0 + r + 4;
-    const bool chain = 2 * na >= nn || max_rows < kMaxRows;   // assume acceptance
-    const int want = chain ? (5 * na > 4 * nn ? 4 : 3 * na > 2 * nn ? 3 : 2 * na >= nn ? 2 : 1)
-                           : (6 * na < nn ? 4 : 3 * na < nn ? 3 : 2);
+    bool chain = 2 * na >= nn || max_rows < kMaxRows;   // assume acceptance
+    int want = chain ? (5 * na > 4 * nn ? 4 : 3 * na > 2 * nn ? 3 : 2 * na >= nn ? 2 : 1)
+                     : (6 * na < nn ? 4 : 3 * na < nn ? 3 : 2);
+    if (np > 1 && (!chain || want == 1)) {
+      chain = true;
+      want = 0;                                // only write the pending exchanges
+    }
     const int nd = min(min(want, max_rows - np), n_prop - r);
+    if (nd <= 1) chain = true;
     if (r + kMaxRows > rbase + 64) {
       rbase = r;
-      philox4x64_10(ctr + (uint64_t)(r + lane), 0, 0, 0, seed, id, rnd);
+      __syncthreads();                         // the older words are read
+      if (wv == 0) {
+        uint64_t rnd[4];
+        philox4x64_10(ctr + (uint64_t)(r + lane), 0, 0, 0, seed, id, rnd);
+        for (int e = 0; e < 3; ++e) words[3 * lane + e] = rnd[e];
+      }
+      __syncthreads();
     }
     slo = lo;
     shi = hi;
 #pragma unroll
     for (int q = 0; q < kMaxRows; ++q) {
       if (q >= np && q < np + nd) {
-        const uint64_t r0 = lane64(rnd[0], r + q - np - rbase);
-        const uint64_t r1 = lane64(rnd[1], r + q - np - rbase);
+        const uint64_t* wd = words + 3 * (r + q - np - rbase);
+        const uint64_t r0 = uniform64(wd[0]), r1 = uniform64(wd[1]);
         const int kup = (int)(((r0 >> 11) * (uint64_t)half) >> 53);
         const int kdn = (int)(((r1 >> 11) * (uint64_t)half) >> 53);
         ei[q] = select128(slo, shi, kup);
@@ -428,33 +545,27 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
       for (int q = 0; q < kMaxRows; ++q)
         l[q] = q < rows ? (int)perminv[(size_t)g * N + ei[q]] * N + perminv[(size_t)g * N + ej[q]]
                         : l[0];
-      for (int k = 0; k < K; ++k) {
-        const float* Tq[kMaxRows];
+      uint32_t ro[kMaxRows];                   // byte offsets in the tanh table (< 2^29)
 #pragma unroll
-        for (int q = 0; q < kMaxRows; ++q) Tq[q] = Tpair + ((size_t)l[q] * KM + (size_t)k * M) * 2;
-        const float* tp = tc + ((size_t)(k * nt) * G + g) * 16;
-        float* to = tn + ((size_t)(k * nt) * G + g) * 16;
-        const size_t step = (size_t)G * 16;
+      for (int q = 0; q < kMaxRows; ++q) ro[q] = (uint32_t)l[q] * (uint32_t)KM * 8u;
+      const uint32_t go = (uint32_t)g * 64u, step = (uint32_t)G * 64u;
+      for (int k = 0; k < K; ++k) {
+        const char* T = reinterpret_cast<const char*>(Tpair) + (size_t)k * M * 8;
+        const char* ti = reinterpret_cast<const char*>(tc) + (size_t)(k * nt) * step;
+        char* to = reinterpret_cast<char*>(tn) + (size_t)(k * nt) * step;
         float pr[kMaxRows], pi[kMaxRows];
         if (chain) {
-          if (rows == 1) stream_rows<1, 1, 1>(tp, to, Tq, nt, step, pr, pi);
-          else if (rows == 2) stream_rows<2, 2, 2>(tp, to, Tq, nt, step, pr, pi);
-          else if (rows == 3) stream_rows<3, 3, 3>(tp, to, Tq, nt, step, pr, pi);
-          else stream_rows<4, 4, 4>(tp, to, Tq, nt, step, pr, pi);
-        } else if (np == 0) {
-          if (rows == 1) stream_rows<1, 0, 0>(tp, to, Tq, nt, step, pr, pi);
-          else if (rows == 2) stream_rows<2, 0, 0>(tp, to, Tq, nt, step, pr, pi);
-          else if (rows == 3) stream_rows<3, 0, 0>(tp, to, Tq, nt, step, pr, pi);
-          else stream_rows<4, 0, 0>(tp, to, Tq, nt, step, pr, pi);
-        } else if (np == 1) {
-          if (rows == 2) stream_rows<2, 1, 1>(tp, to, Tq, nt, step, pr, pi);
-          else if (rows == 3) stream_rows<3, 1, 1>(tp, to, Tq, nt, step, pr, pi);
-          else stream_rows<4, 1, 1>(tp, to, Tq, nt, step, pr, pi);
-        } else if (np == 2) {
-          if (rows == 3) stream_rows<3, 2, 2>(tp, to, Tq, nt, step, pr, pi);
-          else stream_rows<4, 2, 2>(tp, to, Tq, nt, step, pr, pi);
-        } else {
-          stream_rows<4, 3, 3>(tp, to, Tq, nt, step, pr, pi);
+          if (rows == 1) stream_rows<1, 1, 1>(ti, to, go, T, ro, nt, step, pr, pi);
+          else if (rows == 2) stream_rows<2, 2, 2>(ti, to, go, T, ro, nt, step, pr, pi);
+          else if (rows == 3) stream_rows<3, 3, 3>(ti, to, go, T, ro, nt, step, pr, pi);
+          else stream_rows<4, 4, 4>(ti, to, go, T, ro, nt, step, pr, pi);
+        } else if (np == 0) {                  // two proposals or more
+          if (rows == 2) stream_rows<2, 0, 0>(ti, to, go, T, ro, nt, step, pr, pi);
+          else if (rows == 3) stream_rows<3, 0, 0>(ti, to, go, T, ro, nt, step, pr, pi);
+          else stream_rows<4, 0, 0>(ti, to, go, T, ro, nt, step, pr, pi);
+        } else {                               // one pending, two proposals or more
+          if (rows == 3) stream_rows<3, 1, 1>(ti, to, go, T, ro, nt, step, pr, pi);
+          else stream_rows<4, 1, 1>(ti, to, go, T, ro, nt, step, pr, pi);
         }
 #pragma unroll
         for (int q = 0; q < kMaxRows; ++q)
@@ -493,7 +604,7 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
         sr += rb[q];
         si += rb[16 + q];
       }
-      const double u = (double)(lane64(rnd[2], r - rbase) >> 11) * (1.0 / 9007199254740992.0);
+      const double u = (double)(uniform64(words[3 * (r - rbase) + 2]) >> 11) * (1.0 / 9007199254740992.0);
       // every lane holds the same sums: a wave-uniform decision
       const double den = fma(si, si, sr * sr);  // |psi'/psi|^2
       const bool accept = __builtin_amdgcn_readfirstlane((int)(u < den)) != 0;
@@ -555,6 +666,7 @@ __global__ __launch_bounds__(1024) void sample_stream_kernel(
     state[4 * c] = lo;
     state[4 * c + 1] = hi;
     state[4 * c + 2] = ctr + (valid ? (uint64_t)n_prop : 0ull);
+    ho.keep(c, tc != t + (size_t)c * n_htiles * G * 16);
     acc_out[c] += valid ? acc : -((int64_t)1 << 40);   // marks a chain outside Sz = 0
   }
   if (g < N) {
@@ -1198,16 +1310,25 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
   const int threads = std::max(64, (c->G + 63) / 64 * 64);
   // the streaming kernel's ratios: rows of a pass as far as they fit 64 KiB
   const size_t row_lds = (size_t)c->G * c->K * 2 * rs;
+  const size_t words = c->prec == NQS_FP64 ? 0 : 64 * 3 * sizeof(uint64_t);
+  const size_t sums = 64 * sizeof(double) + words;
   const int max_rows = (int)std::max<size_t>(1, std::min<size_t>(
-      c->prec == NQS_FP64 ? 1 : kMaxRows, 65024 / row_lds));
-  const size_t lds = max_rows * row_lds + 64 * sizeof(double);
+      c->prec == NQS_FP64 ? 1 : kMaxRows, (65536 - sums) / row_lds));
+  const size_t lds = max_rows * row_lds + sums, lds1 = row_lds + 64 * sizeof(double);
+  const int big = (size_t)c->G * c->KM * 8 > 512 * 1024;   // bytes of a chain's FP32 cache
+  const int n_probe = n_chains >= 64 ? 2 : 4;  // proposals before the first choice of a kernel
+  int* const mode = nsk + 1;
+  int64_t* const seen = (int64_t*)(nsk + 2);
+  int* const buf = (int*)lp;                  // log psi of the refresh is not read
   auto refresh = [&]() -> hipError_t {
     hipError_t r = launch_theta(c, cur, n_chains, L, t, st);
     if (r == hipSuccess) r = launch_lse(c, L, n_chains, lp, w, st);
     return r;
   };
-  auto run = [&](int phase, int64_t total, int ns_host, const int32_t* ns_dev,
-                 int64_t* acc) -> hipError_t {
+  // prior: acceptances of an earlier phase (n_burn proposals), if there was one
+  auto run = [&](int phase, int64_t total, int ns_host, const int32_t* ns_dev, int64_t* acc,
+                 const int64_t* prior) -> hipError_t {
+    int64_t chosen = 0;                        // proposals before the last choice of a kernel
     for (int64_t p0 = 0; p0 < total; p0 += kSegment) {
       const int cnt = (int)std::min<int64_t>(kSegment, total - p0);
       hipError_t r = refresh();
@@ -1216,18 +1337,44 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
       r = try_reg(c, (int64_t)n, t, w, chain_state, cnt, phase, p0, ns_host, seed, spins_out,
                   n_per_chain, acc, cur, st);
       if (r == hipErrorNotSupported) {
-        if (c->prec == NQS_FP64)
-          sample_kernel<<<(unsigned)n, threads, lds, st>>>(
-              c->N, c->G, c->K, c->M, c->n_htiles, c->dev.perminv, (const double*)c->par.Tpair,
-              (const double*)c->par.Fpair, (double*)t, (double*)t2, (double*)w, chain_state, cnt,
-              phase, p0,
-              ns_dev, ns_host, seed, spins_out, n_per_chain, acc, cur);
-        else
-          sample_stream_kernel<<<(unsigned)n, threads, lds, st>>>(
-              c->N, c->G, c->K, c->M, c->n_htiles, max_rows, c->dev.perminv, (const float*)c->par.Tpair,
-              (const float*)c->par.Fpair, (float*)t, (float*)t2, (float*)w, chain_state, cnt,
-              phase, p0,
-              ns_dev, ns_host, seed, spins_out, n_per_chain, acc, cur);
+        auto launch = [&](auto kernel, auto real, size_t bytes, int64_t q0, int m, Handoff ho) {
+          using R = decltype(real);
+          kernel<<<(unsigned)n, threads, bytes, st>>>(
+              c->N, c->G, c->K, c->M, c->n_htiles, c->dev.perminv, (const R*)c->par.Tpair,
+              (const R*)c->par.Fpair, (R*)t, (R*)t2, (R*)w, chain_state, m, phase, q0, ns_dev,
+              ns_host, seed, spins_out, n_per_chain, acc, cur, ho);
+        };
+        if (c->prec == NQS_FP64) {
+          launch(sample_kernel<double>, 0.0, lds1, p0, cnt, Handoff{});
+        } else if (max_rows == 1) {
+          launch(sample_kernel<float>, 0.f, lds1, p0, cnt, Handoff{});
+        } else {
+          // A phase's first segment in pieces: the acceptance of a chain that is not
+          // in equilibrium changes within a few proposals.  A few of them first where
+          // nothing is known.  A cut costs up to a pass (of 250 us at 10x10 M = 400, 256
+          // chains: 4 % of 100 proposals), so there are none near the end.
+          Handoff ho;
+          for (int q = 0; q < cnt;) {
+            const bool known = q > 0 || p0 > 0 || prior;
+            int end = p0 > 0 ? cnt : !known ? n_probe : q < 32 ? 32 : cnt;
+            if (cnt < 4 * end) end = cnt;
+            ho.buf_out = end < cnt ? buf : nullptr;
+            if (known) {
+              // accepted in this phase, before its first proposal in the burn-in
+              const bool own = p0 + q > 0;
+              sample_mode_kernel<<<1, 256, 0, st>>>(own ? acc : prior, n_chains,
+                                                    own ? p0 + q - chosen : n_burn, chosen == 0,
+                                                    seen, big, max_rows == kMaxRows, mode);
+              chosen = p0 + q;
+              ho.mode = mode;
+              ho.max_rows = max_rows;
+              launch(sample_stream_kernel, 0.f, lds, p0 + q, end - q, ho);
+            }
+            launch(sample_kernel<float>, 0.f, lds1, p0 + q, end - q, ho);
+            ho.buf_in = buf;
+            q = end;
+          }
+        }
         r = hipGetLastError();
       }
       prof_end(c, K_SAMPLE, st);
@@ -1235,7 +1382,7 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
     }
     return hipSuccess;
   };
-  if (e == hipSuccess) e = run(0, n_burn, 1, nullptr, acc_burn);
+  if (e == hipSuccess) e = run(0, n_burn, 1, nullptr, acc_burn, nullptr);
   int ns = n_skip;
   if (e == hipSuccess && n_skip == 0) {
     nskip_kernel<<<1, 256, 0, st>>>(acc_burn, n_chains, n_burn, nsk);
@@ -1244,7 +1391,7 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
     if (e == hipSuccess) e = hipStreamSynchronize(st);
   }
   const int64_t total = n_per_chain * (int64_t)ns;
-  if (e == hipSuccess) e = run(1, total, ns, nullptr, acc_samp);
+  if (e == hipSuccess) e = run(1, total, ns, nullptr, acc_samp, n_burn > 0 ? acc_burn : nullptr);
   if (e == hipSuccess && acc_rate_out) {
     acc_rate_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(acc_samp, n_chains, total,
                                                                  acc_rate_out);
