@@ -399,13 +399,13 @@ __device__ __forceinline__ void quad_gram(const double2* __restrict__ T, int64_t
   }
 }
 
-// 1 / d from the hardware estimate and two Newton steps; d is a positive finite
-// pivot (outside 2^+-1000 the plain division)
+// 1 / d from the hardware estimate and two Newton steps (about 1 ulp), d within
+// 2^+-1000
 __device__ __forceinline__ double rcp_pivot(double d) {
   double r = __builtin_amdgcn_rcp(d);
   r = fma(fma(-d, r, 1.0), r, r);
   r = fma(fma(-d, r, 1.0), r, r);
-  return d > 0x1p-1000 && d < 0x1p1000 ? r : 1.0 / d;
+  return r;
 }
 
 // Diagonal block k: apply the panel's earlier columns [c0, 32 k), factor it
@@ -470,8 +470,15 @@ __global__ __launch_bounds__(kDT) void potrf_diag_kernel(double2* __restrict__ T
         if (bad) flag[0] = 1;
       }
       const double2 cv = col[jb][i];
-      const double inv = rcp_pivot(d);
-      const double fr = i > j ? cv.x * inv : 0.0, fi = i > j ? cv.y * inv : 0.0;   // row multiplier
+      double fr = 0.0, fi = 0.0;               // row multiplier
+      if (d > 0x1p-1000 && d < 0x1p1000) {
+        const double inv = rcp_pivot(d);
+        fr = i > j ? cv.x * inv : 0.0;
+        fi = i > j ? cv.y * inv : 0.0;
+      } else if (i > j) {                      // 1 / d may be out of range where cv / d is not
+        fr = cv.x / d;
+        fi = cv.y / d;
+      }
 #pragma unroll
       for (int e = 0; e < kDE; ++e) {
         const int l = kDE * lg + e;
