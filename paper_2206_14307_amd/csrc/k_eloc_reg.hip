@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
     const int32_t* __restrict__ fmap, const int32_t* __restrict__ frow,
     const R* __restrict__ t, const R* __restrict__ w, const R* __restrict__ Tpm,
     const R* __restrict__ F, double* __restrict__ partial2,
-    int allow_ratio, int tpi) {
+    int allow_ratio, int tpi, int blk) {
   using Cfg = RegCfg<R, N, 1, M>;
   constexpr int NB = Cfg::NB, MH = M / 2;
   constexpr int CAP = fused_cap16(NB, fused_row16(1, M, sizeof(R))) * 16 / (int)sizeof(R);
@@ -276,16 +276,16 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
     return reinterpret_cast<const f32x4*>(Tl) + (off >> 2);
   };
   for (int64_t item = (int64_t)blockIdx.x * kRegWaves + wv; item < n_items; item += stride) {
-    // items in blocks of 16 configurations, the slots slowest within a block and
-    // rotated from block to block: the block's t stays in L2, and a wavefront's
-    // items spread over the slots, whose lists shorten from the first to the last
+    // items in blocks of blk configurations, the slots slowest within a block and
+    // rotated from block to block: a wavefront's items spread over the slots, whose
+    // lists shorten from the first to the last (about half are empty)
     const int64_t sp = item / parts;
     const int part = (int)(item - sp * parts);
-    const int64_t s0 = sp / (16 * NB) * 16;
-    const int ns = (int)min((int64_t)16, S - s0), r = (int)(sp - s0 * NB);
+    const int64_t s0 = sp / (blk * NB) * blk;
+    const int ns = (int)min((int64_t)blk, S - s0), r = (int)(sp - s0 * NB);
     const int rs = r / ns;
     const int64_t s = s0 + (r - rs * ns);
-    const int slot = (int)((rs + 37 * (s0 / 16)) % NB);
+    const int slot = (int)((rs + 37 * (s0 / blk)) % NB);
     const int8_t* srow = spins + s * N;
     // up spins of s; its antiparallel bonds as masks; the slot-th of them is b1
     const uint64_t up = __builtin_amdgcn_ballot_w64(lane < N && srow[lane < N ? lane : 0] > 0);
@@ -523,18 +523,24 @@ __global__ __launch_bounds__(64 * kRegWaves) void twohop_reg_kernel(
 template <typename R, int N, int M>
 hipError_t run_twohop(const nqs_ctx* c, const int8_t* spins, int64_t S, const void* t,
                       const void* w, double* partial2, hipStream_t st) {
-  // tiles of an item, which share its lists: three (two at 4x4) unless the call
-  // is too small to give every wavefront several items
+  // tiles of an item, which share its lists: three (two at 4x4) unless that leaves
+  // a wavefront under 64 items, of which about half are empty and the last one may
+  // be the longest: at 6x6 M = 72 (three / one, us) 76 configurations 1700 / 1430,
+  // 150 2870 / 2640, 300 5310 / 5210; three save 3 % of a large call
   const int64_t slots = (int64_t)kRegWaves * (c->n_cu > 0 ? c->n_cu : 256);
   const int ntiles = c->G / 32, tmax = ntiles % 3 == 0 ? 3 : 2;
-  const int tpi = S * c->NB * (ntiles / tmax) >= 16 * slots ? tmax : 1;
+  const int tpi = S * c->NB * (ntiles / tmax) >= 64 * slots ? tmax : 1;
+  // configurations whose items are ordered by slot: 16, whose t stays in L2; all of
+  // a call with single tiles (under 304 configurations at 6x6), whose last items
+  // are then the empty ones (37 configurations 840 -> 820 us)
+  const int blk = tpi == 1 ? (int)S : 16;
   const int64_t items = S * c->NB * (ntiles / tpi);
   // two workgroups per compute unit at 4x4 (128 VGPRs, 18 KiB of LDS)
   int64_t blocks = (items + kRegWaves - 1) / kRegWaves;
   blocks = std::min<int64_t>(blocks, (c->n_cu > 0 ? c->n_cu : 256) * (N == 16 ? 2 : 1));
   twohop_reg_kernel<R, N, M><<<(unsigned)blocks, 64 * kRegWaves, 0, st>>>(
       spins, S, c->G, c->n_htiles, c->dev.bonds, c->dev.bond_J, c->dev.fmap, c->dev.frow,
-      (const R*)t, (const R*)w, (const R*)c->par.Tpm, (const R*)c->par.F, partial2, c->direct_only ? 0 : 1, tpi);
+      (const R*)t, (const R*)w, (const R*)c->par.Tpm, (const R*)c->par.F, partial2, c->direct_only ? 0 : 1, tpi, blk);
   return hipGetLastError();
 }
 

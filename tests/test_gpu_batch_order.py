@@ -35,6 +35,18 @@ def test_e2_4x4_fp64(M):
         assert torch.equal(e12, ref[:S]), S
 
 
+@pytest.mark.parametrize("L,M,sizes", [(6, 72, (1, 15, 16, 17, 76, 303, 304, 310)),
+                                       (4, 16, (1, 16, 17, 511, 512, 1023, 1024, 1030))])
+def test_e2_fp32(L, M, sizes):
+    """Across the sizes at which a wavefront's item takes one image tile or several."""
+    m = _model(L, 1, M, "fp32")
+    sp = _rows(L, sizes[-1])
+    _, ref = m.lanczos_moments(sp)
+    for S in sizes:
+        _, e12 = m.lanczos_moments(sp[:S])
+        assert torch.equal(e12, ref[:S]), S
+
+
 @pytest.mark.parametrize("L,K,M,prec", [(6, 1, 72, "fp32"), (6, 1, 72, "bf16x2"),
                                         (6, 2, 16, "fp32"), (6, 2, 16, "fp64"),
                                         (6, 1, 16, "bf16x2"), (4, 1, 16, "fp64"),
