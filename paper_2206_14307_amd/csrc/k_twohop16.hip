@@ -54,11 +54,22 @@ __global__ __launch_bounds__(64 * kWaves16, 3) void twohop16_kernel(
   __shared__ double2 Tl[kNB16 * ST];
   __shared__ double2 Fl[kNB16 * 2];
   __shared__ uint8_t bm[kG16 * BS];
-  for (int i = threadIdx.x; i < kNB16 * M; i += blockDim.x)
+  // (loads of a loop in flight together: a small call waits for the tables)
+  constexpr int TH = 64 * kWaves16;
+  int v[kG16 * kNB16 / TH];
+#pragma unroll
+  for (int u = 0; u < kG16 * kNB16 / TH; ++u) v[u] = bmap[threadIdx.x + u * TH];
+#pragma unroll
+  for (int u = 0; u < kNB16 * M / TH; ++u) {
+    const int i = threadIdx.x + u * TH;
     Tl[(i / M) * ST + i % M] = Tpm[(size_t)(i / M) * 2 * M + i % M];
-  for (int i = threadIdx.x; i < kNB16 * 2; i += blockDim.x) Fl[i] = F[i];
-  for (int i = threadIdx.x; i < kG16 * kNB16; i += blockDim.x)
-    bm[(i / kNB16) * BS + i % kNB16] = (uint8_t)bmap[i];
+  }
+  if (threadIdx.x < kNB16 * 2) Fl[threadIdx.x] = F[threadIdx.x];
+#pragma unroll
+  for (int u = 0; u < kG16 * kNB16 / TH; ++u) {
+    const int i = threadIdx.x + u * TH;
+    bm[(i / kNB16) * BS + i % kNB16] = (uint8_t)v[u];
+  }
   __syncthreads();
 
   const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -67,12 +78,15 @@ __global__ __launch_bounds__(64 * kWaves16, 3) void twohop16_kernel(
   const double J = bond_J[lane];
   const int64_t n_items = S * 4 * parts, stride = (int64_t)gridDim.x * kWaves16;
   for (int64_t item = (int64_t)blockIdx.x * kWaves16 + wv; item < n_items; item += stride) {
-    const int64_t s = item >> (2 + lg_parts);
-    const int sub = (int)item & (4 * parts - 1), share = sub >> 2;
+    // the shares slowest: those without a first hop (there are 48 at most, often
+    // 32) lie at the end, and the others spread over the wavefronts
+    const int share = parts == 1 ? 0 : (int)(item / (4 * S));
+    const int64_t s = (item >> 2) - share * S;
+    const int sub = (int)item & 3;
     // the 16 lanes of a row take the 16 translations of one point-group element:
     // a bond's pre-images under them are the 16 bonds of one kind, rows in
     // distinct bank groups
-    const int g = (lane & 15) * 8 + (sub & 3) * 2 + ((lane >> 4) & 1);
+    const int g = (lane & 15) * 8 + sub * 2 + ((lane >> 4) & 1);
     const uint32_t m =
         (uint32_t)__builtin_amdgcn_ballot_w64(lane < 16 && spins[s * 16 + (lane & 15)] < 0);
     uint64_t l1 = __builtin_amdgcn_ballot_w64(((m >> bi) ^ (m >> bj)) & 1u);
@@ -199,7 +213,7 @@ __global__ __launch_bounds__(64 * kWaves16, 3) void twohop16_kernel(
       er += ei;
 #pragma unroll
       for (int o = 16; o > 0; o >>= 1) er += __shfl_xor(er, o, 64);
-      if ((lane & 31) == 0) part[2 * ((s * kNB16 + n) * 4 + (sub & 3)) + half] = er;
+      if ((lane & 31) == 0) part[2 * ((s * kNB16 + n) * 4 + sub) + half] = er;
     }
   }
 }
