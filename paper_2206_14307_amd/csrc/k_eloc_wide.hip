@@ -353,13 +353,20 @@ __global__ __launch_bounds__(64 * kWideWaves) void eloc_wide_kernel(
       asm volatile("" : "+s"(nvu), "+v"(nv), "+s"(head));
       if (act) {
         if (cin == 0) {                        // RBM start: products begin at F_s
+          // (in halves: the two walks of K > 4 rarely use the upper one, and without
+          // the condition took 4-6 % longer at K = 5 M = 40 than 18 bonds a lane did)
+          constexpr int kHalf = (kWB / 2 + 1) & ~1;
 #pragma unroll
-          for (int jb = 0; jb < kWB; ++jb) {
-            const uint32_t o = PACK ? (jb & 1 ? offs[jb / 2] >> 16 : offs[jb / 2]) : offs[jb];
-            const f32x2 f = *(lds_f32x2_ptr)(((o & 0xfff0u) | base) + 8u * kHC + 8u * (o & 1u));
-            Pr[jb] = f.x;
-            Pi[jb] = f.y;
-          }
+          for (int j0 = 0; j0 < kWB; j0 += kHalf)
+            if (j0 < nvu) {
+#pragma unroll
+              for (int jb = j0; jb < min(j0 + kHalf, kWB); ++jb) {
+                const uint32_t o = PACK ? (jb & 1 ? offs[jb / 2] >> 16 : offs[jb / 2]) : offs[jb];
+                const f32x2 f = *(lds_f32x2_ptr)(((o & 0xfff0u) | base) + 8u * kHC + 8u * (o & 1u));
+                Pr[jb] = f.x;
+                Pi[jb] = f.y;
+              }
+            }
         }
         // theta of the chunk's hidden tile, epilogue, tanh to LDS
         const int h0 = 8 * ch + 2 * q;
