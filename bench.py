@@ -280,6 +280,51 @@ def kernel_ms(m, names, fn, steps):
     return out
 
 
+def sampler_traffic(acc, row_bytes, cache_bytes, n=20000):
+    """Site-pair rows read, and reads and writes of a chain's cache, per proposal
+    of the FP32 streaming sampler at an acceptance `acc`, by its rules (k_sample.hip):
+    which kernel runs, how many proposals a pass follows, exchanges pending between
+    passes.  row_bytes: the ratios of a proposal in LDS (G K x 8), cache_bytes:
+    G K M x 8.  Returns (kernel, rows, reads, writes)."""
+    import random
+    max_rows = max(1, min(4, (65536 - 64 * 8 - 64 * 24) // row_bytes))
+    big = cache_bytes > 512 * 1024
+    high = acc >= (0.80 if big else 0.85)
+    low = max_rows == 4 and acc <= (0.30 if big else 0.15)
+    if max_rows == 1 or not (high or low):
+        return "sample_kernel", 1.0, 1.0, 1.0
+    rng = random.Random(0)
+    r = accepted = pending = rows = reads = writes = 0
+    while r < n:
+        a = (accepted + 3) / (r + 4)
+        chain = a >= 0.5 or max_rows < 4
+        if chain:
+            want = 4 if a > 0.8 else 3 if a > 2 / 3 else 2 if a >= 0.5 else 1
+        else:
+            want = 4 if a < 1 / 6 else 3 if a < 1 / 3 else 2
+        if pending > 1 and (not chain or want == 1):
+            chain, want = True, 0                 # only writes the pending exchanges
+        nd = min(want, max_rows - pending)
+        chain = chain or nd <= 1
+        rows += pending + nd
+        reads += 1
+        writes += chain or pending > 0
+        took, expected = 0, True
+        for _ in range(nd):
+            r += 1
+            yes = rng.random() < acc
+            took += yes
+            expected = yes == chain
+            if not expected:
+                break
+        accepted += took
+        if not chain:
+            pending = 1 if took else 0
+        else:
+            pending = 0 if expected else pending + took
+    return "sample_stream_kernel", rows / r, reads / r, writes / r
+
+
 def sample_spins(m, w, seed=2002):
     """nqs_sample: w.n_chains chains from uniformly random Sz = 0 starts,
     burn-in 20 N proposals, automatic N_skip, w.n_per_chain samples each."""
@@ -304,14 +349,14 @@ def sample_spins(m, w, seed=2002):
     fl = props * w.G * w.n_rbm * w.n_hidden * (FLOPS_PER_FACTOR + 20.0 * acc)
     # one RBM with M in {8, 16, 32, 72} (FP32) keeps tanh(theta) in registers
     # (6x6 M = 72: eight lanes per image); otherwise the chain's cache
-    # [G][K M] complex is streamed: FP32 models read and write it once for
-    # several proposals (four above an acceptance of 0.8), FP64 once for each
+    # [G][K M] complex is streamed: by FP32 models once for several proposals
+    # where nearly all are accepted or rejected, else once for each
     reg = w.n_rbm == 1 and w.n_hidden in (8, 16, 32, 72) and w.precision != "fp64" and w.G <= 512
     reg8 = reg and w.G == 288 and w.n_hidden == 72
     leg = {"workload": w.name, "chains": w.n_chains, "per_chain": w.n_per_chain,
            "burn_in": 20 * w.N, "n_skip": nskip, "acceptance": acc, "seconds": t,
            "kernel": ("sample_reg8_kernel" if reg8 else "sample_reg_kernel") if reg
-                     else "sample_kernel" if w.precision == "fp64" else "sample_stream_kernel",
+                     else "sample_kernel",
            "sampler_kernel_ms": k_ms, "sampler_launches": k_n,
            "proposals_per_s": props / t,
            "roofline": {"bound": "alu", "achieved": fl / t / 1e12,
@@ -319,18 +364,19 @@ def sample_spins(m, w, seed=2002):
                         "frac": fl / t / 1e12 / PEAK_FP32_VECTOR_TFLOPS,
                         "flops_per_image_hidden_proposal": "10 + 20 x acceptance"}}
     if not reg:
-        # the image's site-pair rows (tables far larger than the L2) read for
-        # every proposal, the cache read and written once per pass: at most four
-        # proposals, up to the first rejection
-        one = w.precision == "fp64"
-        per_pass = 1.0 if one else sum(acc ** d for d in range(4))
-        nb = (props * w.G * w.n_rbm * w.n_hidden * (16.0 if one else 8.0)
-              * (1.0 + 2.0 / per_pass))
+        # site-pair rows (tables far larger than the L2), cache reads and writes
+        kr, rows, rd, wr = (("sample_kernel", 1.0, 1.0, 1.0) if w.precision == "fp64" else
+                            sampler_traffic(acc, w.G * w.n_rbm * 8,
+                                            w.G * w.n_rbm * w.n_hidden * 8))
+        leg["kernel"] = kr
+        nb = (props * w.G * w.n_rbm * w.n_hidden * (16.0 if w.precision == "fp64" else 8.0)
+              * (rows + rd + wr))
         leg["roofline"] = {"bound": "hbm", "achieved": nb / t / 1e9, "peak": PEAK_HBM_GBS,
                            "unit": "GB/s", "frac": nb / t / 1e9 / PEAK_HBM_GBS,
-                           "bytes_per_proposal": "G K M x 8 B (FP64: 16) x (1 + 2 / proposals "
-                                                 "per pass): the site-pair rows read for each, "
-                                                 "the cache read and written once per pass",
+                           "bytes_per_proposal": "G K M x 8 B (FP64: 16) x (%.3f site-pair rows, "
+                                                 "%.3f reads and %.3f writes of the cache), the "
+                                                 "kernel's rules at this acceptance"
+                                                 % (rows, rd, wr),
                            "alu_frac": fl / t / 1e12 / PEAK_FP32_VECTOR_TFLOPS}
     return sp, leg
 
