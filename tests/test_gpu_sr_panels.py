@@ -1,6 +1,6 @@
 """nqs_sr_solve where the factorisation takes several panels of eight 32-row
 blocks (full, partial and single-block last panels) and the FP32 Gram each of
-its tile sizes (64, 96 and 128 rows, partial last tiles), against the
+its tile sizes (64 and 96 rows, partial last tiles), against the
 parameter-space solve (equal by the push-through identity).  The ridge keeps
 the systems well conditioned: FP64 1e-9, FP32 (Gram in FP32) 1e-4."""
 import numpy as np
