@@ -396,9 +396,10 @@ __device__ __forceinline__ void stream_rows(const char* __restrict__ tc, char* _
 
 // Which streaming kernel runs next, from the acceptance of all chains over the
 // n_new proposals since the last choice (acc: accepted per chain so far, negative
-// outside Sz = 0; *seen: their sum at the last choice, 0 if `first`).  Several
-// proposals in a pass pay where most passes come out as assumed: nearly all
-// accepted, or (rows permitting, max_rows = 4) nearly all rejected; more so for
+// outside Sz = 0; *seen: their sum at the last choice, 0 if `first`): several in a
+// pass from `high` % and up to `low` % (none: -1).  They pay where most passes come
+// out as assumed: nearly all proposals accepted, or (rows permitting, max_rows = 4)
+// nearly all rejected; more so for
 // caches that stream from HBM.  Times of 260 proposals of 256 chains, this choice
 // against one proposal in a pass always (ms), at acceptances of about 0.99 / 0.5 to
 // 0.8 / 0.2 / 0.08: 6x6 M = 40 2.0 of 3.2 / 3.2 of 3.1 / 3.1 of 3.1 / 2.9 of 3.1,
@@ -409,8 +410,8 @@ __device__ __forceinline__ void stream_rows(const char* __restrict__ tc, char* _
 // read rows and updated entries in vain.
 __global__ __launch_bounds__(256) void sample_mode_kernel(const int64_t* __restrict__ acc,
                                                           int64_t n_chains, int64_t n_new,
-                                                          bool first, int64_t* seen, int big,
-                                                          int rejections, int* mode) {
+                                                          bool first, int64_t* seen, int high,
+                                                          int low, int* mode) {
   __shared__ int64_t red[2][4];
   int64_t a = 0, n = 0;
   for (int64_t c = threadIdx.x; c < n_chains; c += 256)
@@ -433,9 +434,7 @@ __global__ __launch_bounds__(256) void sample_mode_kernel(const int64_t* __restr
     a = sum - (first ? 0 : *seen);
     *seen = sum;
     n = (red[1][0] + red[1][1] + red[1][2] + red[1][3]) * n_new;
-    const bool high = 100 * a >= (big ? 80 : 85) * n;
-    const bool low = rejections && 100 * a <= (big ? 30 : 15) * n;
-    *mode = high || low ? 1 : 0;
+    *mode = 100 * a >= high * n || 100 * a <= low * n ? 1 : 0;
   }
 }
 
@@ -1315,8 +1314,10 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
   const int max_rows = (int)std::max<size_t>(1, std::min<size_t>(
       c->prec == NQS_FP64 ? 1 : kMaxRows, (65536 - sums) / row_lds));
   const size_t lds = max_rows * row_lds + sums, lds1 = row_lds + 64 * sizeof(double);
-  const int big = (size_t)c->G * c->KM * 8 > 512 * 1024;   // bytes of a chain's FP32 cache
-  const int n_probe = n_chains >= 64 ? 2 : 4;  // proposals before the first choice of a kernel
+  // the chains' FP32 caches stream from HBM (a few chains' stay in the L2s)
+  const int big = (size_t)c->G * c->KM * 8 > 512 * 1024 && n_chains >= 64;
+  // proposals before the first choice of a kernel
+  const int n_probe = n_chains >= 64 ? 2 : n_chains >= 4 ? 4 : 8;
   int* const mode = nsk + 1;
   int64_t* const seen = (int64_t*)(nsk + 2);
   int* const buf = (int*)lp;                  // log psi of the refresh is not read
@@ -1362,9 +1363,13 @@ nqs_status nqs_sample(nqs_ctx* c, int64_t n_chains, int64_t n_per_chain, int32_t
             if (known) {
               // accepted in this phase, before its first proposal in the burn-in
               const bool own = p0 + q > 0;
+              // (the first proposals from a state out of equilibrium are accepted
+              // more often than later ones: 95 % of them where nothing else is known)
+              const int high = chosen == 0 && own && !prior ? 95 : big ? 80 : 85;
+              const int low = max_rows < kMaxRows ? -1 : big ? 30 : 15;
               sample_mode_kernel<<<1, 256, 0, st>>>(own ? acc : prior, n_chains,
                                                     own ? p0 + q - chosen : n_burn, chosen == 0,
-                                                    seen, big, max_rows == kMaxRows, mode);
+                                                    seen, high, low, mode);
               chosen = p0 + q;
               ho.mode = mode;
               ho.max_rows = max_rows;
