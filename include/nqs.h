@@ -153,16 +153,19 @@ nqs_status nqs_logpsi(nqs_ctx* ctx, const int8_t* spins, int64_t S, double* logp
 /* Local energies E_loc(sigma) = <sigma|H|psi>/<sigma|psi> (Sec. 3.2, Eq. (10))
  * over the antiparallel J1 and J2 bonds: eloc_out complex [S]; logpsi_out
  * (complex [S]) is written too unless NULL.  Configurations with psi = 0
- * (possible for non-A1 irreps) give non-finite E_loc. */
+ * (possible for non-A1 irreps) give non-finite E_loc.  A configuration's
+ * results do not depend on the other rows of the call or their number, here and
+ * in the calls below that return E_loc or e2. */
 nqs_status nqs_eloc(nqs_ctx* ctx, const int8_t* spins, int64_t S, double* logpsi_out,
                     double* eloc_out, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid allocation): nqs_eloc without
  * a workspace.  Same results as nqs_eloc (the same kernels); eloc_out and
- * logpsi_out (optional) as there.  The kernels' per-configuration partials,
- * (N/2) x 6 doubles each, live in a 64 MiB device array that the library
- * holds on each GPU it runs on until the process ends, so S is limited to
+ * logpsi_out (optional) as there.  The kernels' partials live in a 64 MiB
+ * device array that the library holds on each GPU it runs on until the process
+ * ends: (N/2) x 6 doubles per configuration (calls small enough to leave the
+ * device idle use more of it per configuration), so S is limited to
  * floor(2^26 / (24 N)) configurations (174762 at 4x4, 77672 at 6x6, 43690 at
  * 8x8, 27962 at 10x10): larger S returns NQS_ERR_ARG with nothing launched.
  * Only models with a fused (K*M <= 128) or wide (K*M > 128, FP32 or
@@ -217,10 +220,11 @@ nqs_status nqs_grad(nqs_ctx* ctx, const int8_t* spins, int64_t S, void* O_out, d
 /* log psi, E_loc and O_k of the same configurations in one call: the outputs of
  * nqs_eloc (logpsi_out optional, eloc_out) and of nqs_grad (O_out), as one
  * VMC step needs them (Sec. 3.2: Eq. (10) and the O_k below Eq. (12)).  For
- * models on the wide E_loc and gradient kernels (K*M > 128) the gradient
- * takes the per-image log amplitudes of psi_s(g sigma) from the E_loc pass
- * instead of a theta pass of its own; other models run nqs_eloc, then
- * nqs_grad.  Results agree with the two separate calls to rounding.
+ * models on the wide E_loc and gradient kernels (K*M > 128, K <= 4) the
+ * gradient takes the per-image log amplitudes of psi_s(g sigma) from the E_loc
+ * pass instead of a theta pass of its own; for models whose E_loc and gradient
+ * both read stored tanh(theta) one theta pass feeds the two; other models run
+ * nqs_eloc, then nqs_grad.  Results agree with the two separate calls to rounding.
  * Workspace: nqs_workspace_bytes(NQS_OP_ELOC_GRAD, S). */
 nqs_status nqs_eloc_grad(nqs_ctx* ctx, const int8_t* spins, int64_t S, double* logpsi_out,
                          double* eloc_out, void* O_out, void* ws, size_t ws_bytes,

@@ -51,6 +51,9 @@ template <int N>
 constexpr int wide_bonds() { return N == 36 ? 22 : N == 64 ? 36 : 56; }
 // The list entries whose sums over several RBMs are rescaled as the running
 // maximum m rises; those of later entries are weighted once, with the final m.
+// The line lies where the first of several walks of 18 (16) bonds a lane ended: the
+// sums of K > 1 keep that split's grouping and roundings.  The price is WideRec in
+// LDS, two sums a lane and, for K > 4, a walk of the first entries by themselves.
 template <int N, bool PAIRS>
 constexpr int wide_head() { return N >= 64 && !(PAIRS && N >= 100) ? 72 : 64; }
 constexpr int kHC = 8;             // hidden units per chunk

@@ -4,9 +4,12 @@
 //
 // It runs the same kernels as nqs_eloc for models with a fused (K*M <= 128)
 // or wide (K*M > 128) E_loc kernel; the per-(configuration, 16-image block)
-// partials those kernels exchange, (G/16) x 6 doubles per configuration, live
-// in `scratch`, a file-scope device array of kScratchBytes instead of a
-// caller workspace.  Each GPU holds its own copy for the life of the process;
+// partials those kernels exchange live in `scratch`, a file-scope device array of
+// kScratchBytes instead of a caller workspace: (G/16) x 6 doubles per
+// configuration, which bounds S, or where a call is so small that its bond lists
+// are shared out the shares' sums or products, more per configuration.  Both
+// launchers are given kScratchBytes and share lists out only as far as it holds
+// them.  Each GPU holds its own copy for the life of the process;
 // its address on a device is resolved once, with that device current, by
 // noalloc_scratch_init (called from nqs_create, and from the entry point if
 // that failed), and host code uses only that address.  Every partial a

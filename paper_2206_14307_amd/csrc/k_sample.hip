@@ -399,15 +399,14 @@ __device__ __forceinline__ void stream_rows(const char* __restrict__ tc, char* _
 // outside Sz = 0; *seen: their sum at the last choice, 0 if `first`): several in a
 // pass from `high` % and up to `low` % (none: -1).  They pay where most passes come
 // out as assumed: nearly all proposals accepted, or (rows permitting, max_rows = 4)
-// nearly all rejected; more so for
-// caches that stream from HBM.  Times of 260 proposals of 256 chains, this choice
-// against one proposal in a pass always (ms), at acceptances of about 0.99 / 0.5 to
-// 0.8 / 0.2 / 0.08: 6x6 M = 40 2.0 of 3.2 / 3.2 of 3.1 / 3.1 of 3.1 / 2.9 of 3.1,
-// 8x8 M = 64 4.5 of 8.0 / 8.0 of 8.0 / 7.9 of 7.9 / 7.4 of 7.9, 10x10 M = 104 13.5
-// of 29.0 / 28.4 of 29.1 / 27.0 of 29.0 / 15.4 of 29.1, 8x8 K = 4 M = 32 11.4 of
-// 23.2 / - / 22.1 of 22.0 / 22.1 of 22.0.  Several in a pass always took 3.8 at 6x6
-// and 0.7, 9.6 at 8x8 and 0.5, 26.6 at K = 4 and 0.16: a pass that ends early has
-// read rows and updated entries in vain.
+// nearly all rejected; more so for caches that stream from HBM.  Times of 260
+// proposals of 256 chains, this choice against one proposal in a pass always (ms),
+// at acceptances of about 0.99 / 0.5 to 0.8 / 0.2 / 0.08: 6x6 M = 40 2.0 of 3.2 /
+// 3.2 of 3.1 / 3.1 of 3.1 / 2.9 of 3.1, 8x8 M = 64 4.5 of 8.0 / 8.0 of 8.0 / 7.9 of
+// 7.9 / 7.4 of 7.9, 10x10 M = 104 13.5 of 29.0 / 28.4 of 29.1 / 27.0 of 29.0 / 15.4
+// of 29.1, 8x8 K = 4 M = 32 11.4 of 23.2 / - / 22.1 of 22.0 / 22.1 of 22.0.  Several
+// in a pass always took 3.8 at 6x6 and 0.7, 9.6 at 8x8 and 0.5, 26.6 at K = 4 and
+// 0.16: a pass that ends early has read rows and updated entries in vain.
 __global__ __launch_bounds__(256) void sample_mode_kernel(const int64_t* __restrict__ acc,
                                                           int64_t n_chains, int64_t n_new,
                                                           bool first, int64_t* seen, int high,

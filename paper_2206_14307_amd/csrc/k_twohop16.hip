@@ -14,9 +14,10 @@
 //
 // Bound: FP64 VALU issue (3.4e9 wave instructions for the 12 870 configurations
 // of the sector at M = 16, 5.6 ms at four cycles each; with three wavefronts a
-// SIMD they issue at about five).  8.3 ms; the kernel before it, which gave a
-// wavefront one first hop and chased list, map and F through global memory
-// once per pair of second hops, took 33.7 ms.  Measured alternatives: one lane
+// SIMD they issue at about five).  8.3 ms with one partial per share (one per
+// first hop costs half a percent: 9.75 -> 9.80 ms on a slower box); the kernel
+// before it, which gave a wavefront one first hop and chased list, map and F through
+// global memory once per pair of second hops, took 33.7 ms.  Measured alternatives: one lane
 // per image (16 units a lane) 12.5 ms without and 9.3 ms with the next table row
 // prefetched, at two wavefronts a SIMD; four wavefronts (128 VGPRs) 9.0 ms.
 #include "device_common.h"
